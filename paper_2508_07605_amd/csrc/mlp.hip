@@ -20,58 +20,12 @@
 
 #include "common.h"
 #include "dense.h"
+#include "mlp_net.h"
+#include "mlp_train.h"
 
 namespace openk {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-typedef float f2v __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-// float32 -> bfloat16, round to nearest even (NaN stays NaN): the gfx950 conversion
-// instruction v_cvt_pk_bf16_f32, two values at a time; bf16pack(a, b) has a in the low half
-__device__ __forceinline__ uint32_t bf16pack(float a, float b) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{a, b}, bf16x2v));
-}
-__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-__device__ __forceinline__ float bf2f(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
-
-// GELU(z) = z Phi(z) (the erf form), with Phi(z) evaluated as the logistic function of an odd
-// polynomial, Phi(z) ~ 1 / (1 + exp(-(a z + b z^3 + c z^5))), whose three coefficients were
-// fitted to minimise the largest error of GELU over the real line (a = 1.5950157,
-// b = 0.07401132, c = -7.030379e-4; the polynomial is taken at z clamped to [-10, 10], where
-// it is increasing; GELU is taken as 0 below -10).  Largest absolute error of GELU: 2.5e-5,
-// below the bfloat16 rounding of the activations that follows.  One exponential, one
-// reciprocal and eight other instructions.
-// The constants below are -log2(e) times the coefficients (the exponential is exp2).
-constexpr float kGeluC0 = -2.301121234893799f, kGeluC1 = -0.10677576065063477f, kGeluC2 = 0.0010142693063244224f;
-__device__ __forceinline__ float gelu_t(float z) {
-  const float zc = __builtin_amdgcn_fmed3f(z, -10.0f, 10.0f);
-  const float z2 = zc * zc;
-  return zc * __builtin_fmaf(z2, __builtin_fmaf(z2, kGeluC2, kGeluC1), kGeluC0);
-}
-__device__ __forceinline__ float gelu(float z) {
-  const float v = z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(gelu_t(z)));
-  return z < -10.0f ? 0.0f : v;  // below -10 the clamped polynomial would leave z 9e-13
-}
-// SELU (Klambauer et al. 2017) and its derivative (the right-hand value at 0 is not taken: z > 0)
-constexpr float kSeluA = 1.6732632423543772f, kSeluL = 1.0507009873554805f;
-__device__ __forceinline__ float selu(float z) { return z > 0.f ? kSeluL * z : kSeluL * kSeluA * (__expf(z) - 1.f); }
-__device__ __forceinline__ float selu_grad(float z) { return z > 0.f ? kSeluL : kSeluL * kSeluA * __expf(z); }
-// derivative of the GELU above: s + z s'(z), s = 1 / (1 + e), e = 2^t(z),
-// s' = -s^2 e ln2 t'(z), t' = C0 + 3 C1 z^2 + 5 C2 z^4 (0 where z is clamped)
-__device__ __forceinline__ float gelu_grad(float z) {
-  const float e = __builtin_amdgcn_exp2f(gelu_t(z));
-  const float sg = __builtin_amdgcn_rcpf(1.0f + e);
-  const float z2 = z * z;
-  const float tp = __builtin_fabsf(z) < 10.0f
-                       ? __builtin_fmaf(z2, __builtin_fmaf(z2, 5.0f * kGeluC2, 3.0f * kGeluC1), kGeluC0)
-                       : 0.0f;
-  return sg - z * sg * sg * e * 0.69314718055994531f * tp;
-}
-
 // ---------------------------------------------------------------- bfloat16 weight copies
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
 // First-layer weights as one 32-bit pair per (setting j, hidden unit h): low half
 // bf16(W1[h][j]) (the weight of the value r_j), high half bf16(W1[h][n + j]) (the weight of the
 // mask bit).  A lane's four units of one setting are one 16-byte load.
@@ -83,89 +37,15 @@ __global__ void k_pack_w1p(const float *__restrict__ W1, int H, int n, uint32_t 
   }
 }
 
-// W2 as the B operands of the inference kernel's second layer: entry ((w*2 + cb)*16 + ks)*64 +
-// lane (lane = 32 g + i) holds W2[64w + 32cb + i][16ks + 8g .. +8] as 8 bfloat16.
-__global__ void k_pack_w2p(const float *__restrict__ W2, uint4 *__restrict__ W2P) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= 8192) return;
-  const int lane = e & 63, ks = (e >> 6) & 15, cb = (e >> 10) & 1, w = e >> 11;
-  const int i = lane & 31, g = lane >> 5;
-  const float *src = W2 + (int64_t)(64 * w + 32 * cb + i) * 256 + 16 * ks + 8 * g;
-  uint32_t pk[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) pk[q] = bf16pack(src[2 * q], src[2 * q + 1]);
-  W2P[e] = uint4{pk[0], pk[1], pk[2], pk[3]};
-}
-
-// W3 (K x 256) as the B operands of the inference kernel's output layer: entry
-// (cb*16 + ks)*64 + lane (lane = 32 g + i) holds W3[32cb + i][16ks + 8g .. +8] as 8 bfloat16,
-// zero for output rows past K.
-__global__ void k_pack_w3p(const float *__restrict__ W3, int K, uint4 *__restrict__ W3P) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  const int cbs = (K + 31) / 32;
-  if (e >= cbs * 1024) return;
-  const int lane = e & 63, ks = (e >> 6) & 15, cb = e >> 10;
-  const int o = 32 * cb + (lane & 31), g = lane >> 5;
-  uint32_t pk[4] = {0, 0, 0, 0};
-  if (o < K) {
-    const float *src = W3 + (int64_t)o * 256 + 16 * ks + 8 * g;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) pk[q] = bf16pack(src[2 * q], src[2 * q + 1]);
-  }
-  W3P[e] = uint4{pk[0], pk[1], pk[2], pk[3]};
-}
-
-// The value r of an observed entry as the pair (bf16(r), 1) that multiplies a weight pair
-// (value weight, mask weight): one dot product adds a r + c.  The value is rounded to bfloat16
-// like the weights (relative error at most 2^-9).  An entry whose column is outside [0, n)
-// takes the pair (0, 0): it adds nothing.
-__device__ __forceinline__ uint32_t value_pair(float r, bool valid) {
-  return valid ? (uint32_t)f2bf(r) | (0x3f80u << 16) : 0u;
-}
-
-// The lane's weight pairs of setting j (four units, 16 bytes) from the packed first layer
-// through a buffer resource over n settings: j outside [0, n) reads zeros.
-__device__ __forceinline__ uint4 w1_pairs(__amdgpu_buffer_rsrc_t rs, int j, int lane) {
-  const uint32_t off = ((uint32_t)j << 10) + 16u * (uint32_t)lane;  // j = -1 wraps out of range
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
-}
-
-// z += a r + c for the lane's four units (w: their weight pairs), one bfloat16 dot product
-// per unit with float32 accumulation.  Every first-layer evaluation (training and inference)
-// takes exactly these steps in the row's entry order.
-__device__ __forceinline__ void layer1_step(f4 &z, uint4 w, uint32_t p) {
-  const bf16x2 y = __builtin_bit_cast(bf16x2, p);
-  const uint32_t wq[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) z[q] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, wq[q]), y, z[q], false);
-}
-
-// ---------------------------------------------------------------- sparse first layer
-// One wavefront per batch row, lane l owns hidden units 4l..4l+3 (H = 256).
-// rows (nullable) maps batch index b -> CSR row.  Writes z1 (nullable) and h1 = GELU(z1).
-__global__ __launch_bounds__(256) void k_layer1(int64_t B, const int64_t *__restrict__ rows,
-                                                const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
-                                                const float *__restrict__ val, int n,
-                                                const uint32_t *__restrict__ W1P, const float *__restrict__ b1,
-                                                float *__restrict__ z1, float *__restrict__ h1) {
-  const int lane = threadIdx.x & 63;
-  const __amdgpu_buffer_rsrc_t rs = make_rsrc(W1P, (uint64_t)n * 1024);
-  const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-  for (int64_t b = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); b < B; b += nw) {
-    const int64_t i = rows ? rows[b] : b;
-    f4 z = *reinterpret_cast<const f4 *>(b1 + 4 * lane);
-    for (int64_t t = ptr[i]; t < ptr[i + 1]; ++t) {
-      const int j = col[t];
-      const bool ok = j >= 0 && j < n;
-      layer1_step(z, w1_pairs(rs, ok ? j : -1, lane), value_pair(val[t], ok));
-    }
-    if (z1) *reinterpret_cast<f4 *>(z1 + b * 256 + 4 * lane) = z;
-    f4 hv;
-    hv[0] = gelu(z[0]);
-    hv[1] = gelu(z[1]);
-    hv[2] = gelu(z[2]);
-    hv[3] = gelu(z[3]);
-    *reinterpret_cast<f4 *>(h1 + b * 256 + 4 * lane) = hv;
+// W (N x Kd, row-major; with T its transpose) as MFMA operands in the order of mfma_slot, zero
+// past its edges: rows padded to 32, k to 16.
+template <bool T>
+__global__ void k_pack_mfma(const float *__restrict__ W, int N, int Kd, uint16_t *__restrict__ P) {
+  const int KS = (Kd + 15) / 16, total = (N + 31) / 32 * 32 * KS * 16;
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
+    const int o = e / (16 * KS), i = e % (16 * KS);
+    const float x = o < N && i < Kd ? (T ? W[(int64_t)i * N + o] : W[(int64_t)o * Kd + i]) : 0.f;
+    P[mfma_slot(o, i, KS)] = f2bf(x);
   }
 }
 
@@ -341,33 +221,6 @@ __global__ __launch_bounds__(256) void k_reduce_slices(int64_t total, int S, con
   }
 }
 
-// Dense input rows of a batch, x_b = [r * mask ; mask] (Bsz x 2n float32), one wavefront per
-// row: the row is assembled in LDS (zeros, then its observed entries), then written out whole.
-// Entries with a column outside [0, n) are left out, as in the sparse first layer.
-__global__ __launch_bounds__(64) void k_dense_x(int64_t Bsz, const int64_t *__restrict__ rows,
-                                                const int64_t *__restrict__ ptr, const int32_t *__restrict__ col,
-                                                const float *__restrict__ val, int n, float *__restrict__ X) {
-  extern __shared__ float xs[];
-  const int lane = threadIdx.x;
-  const int twon = 2 * n;
-  for (int64_t b = blockIdx.x; b < Bsz; b += gridDim.x) {
-    for (int c = lane; c < twon; c += 64) xs[c] = 0.f;
-    __syncthreads();
-    const int64_t i = rows ? rows[b] : b;
-    for (int64_t t = ptr[i] + lane; t < ptr[i + 1]; t += 64) {
-      const int j = col[t];
-      if (j >= 0 && j < n) {
-        xs[j] = val[t];
-        xs[n + j] = 1.0f;
-      }
-    }
-    __syncthreads();
-    float *dst = X + b * twon;
-    for (int c = lane; c < twon; c += 64) dst[c] = xs[c];
-    __syncthreads();
-  }
-}
-
 template <int EPI>
 static open_status gemm(open_ctx *ctx, const char *name, int M, int N, int Kd, const float *A, int64_t sam,
                         int64_t sak, const float *Bm, int64_t sbn, int64_t sbk, float *C, int64_t ldc,
@@ -378,30 +231,6 @@ static open_status gemm(open_ctx *ctx, const char *name, int M, int N, int Kd, c
 }
 
 // ---------------------------------------------------------------- loss, reductions, Adam
-// d_out = 2 (out - target) / (B k); block partial sums of (out - target)^2 in float64
-__global__ __launch_bounds__(256) void k_loss(int64_t B, int k, const float *__restrict__ out,
-                                              const int64_t *__restrict__ rows, const float *__restrict__ target,
-                                              float *__restrict__ dout, double *__restrict__ part) {
-  __shared__ double red[256];
-  double acc = 0.0;
-  const int64_t total = B * k;
-  const float scale = 2.0f / (float)total;
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-    const int64_t b = e / k, o = e % k;
-    const int64_t i = rows ? rows[b] : b;
-    const float d = out[e] - target[i * k + o];
-    dout[e] = scale * d;
-    acc += (double)d * (double)d;
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < (unsigned)s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
 // Optimizer state on the device, so that a recorded training step can be replayed as is:
 // t = Adam steps taken, cursor = batch index within the epoch, c1/c2 = bias corrections of
 // the next step, 1 - beta1^(t+1) and 1 - beta2^(t+1).
@@ -841,16 +670,15 @@ struct open_mlp {
   int64_t off_b1 = 0, off_w2 = 0, off_b2 = 0, off_w3 = 0, off_b3 = 0;
   float *w = nullptr, *g = nullptr, *am = nullptr, *av = nullptr;  // masters, gradient, Adam moments
   uint32_t *w1p = nullptr;                                         // W1 weight pairs, bfloat16 (n x H)
-  uint4 *w2p = nullptr;                                            // W2 as inference MFMA operands
-  uint4 *w3p = nullptr;                                            // W3 as inference MFMA operands
+  uint4 *w2p = nullptr, *w3p = nullptr;                            // W2, W3 as MFMA operands
+  uint4 *w2t = nullptr, *w3t = nullptr;                            // and their transposes (training)
   openk::TrainState *tstate = nullptr;                             // device optimizer state
-  // activations for a batch of up to cap rows
+  // a training batch of up to cap rows: packed operands of the weight gradients, output
+  // gradients, partial losses
   int64_t cap = 0;
-  float *z1 = nullptr, *h1 = nullptr, *z2 = nullptr, *h2 = nullptr, *out = nullptr, *dout = nullptr;
-  float *d2 = nullptr, *d1 = nullptr;
-  float *xd = nullptr;     // dense input rows of the batch (batch x 2n), for the W1 gradient
-  float *wpart = nullptr;  // split-over-the-batch partials of the weight and bias gradients
-  double *part = nullptr, *loss = nullptr;
+  uint16_t *x = nullptr, *h1 = nullptr, *h2 = nullptr, *d1p = nullptr, *d2p = nullptr, *d3p = nullptr;
+  float *d1 = nullptr, *d2 = nullptr, *d3 = nullptr;
+  double *lpart = nullptr, *loss = nullptr;
   // inference scratch
   int64_t icap = 0;
   float *rho = nullptr;
@@ -861,7 +689,6 @@ struct open_mlp {
 namespace openk {
 
 constexpr int kMaxBatchRows = 16384;
-constexpr int kLossBlocks = 256;
 
 // batch slices of the weight-gradient product of an M x N layer: about 1024 blocks over the
 // 64 x 64 output tiles, each slice a multiple of 32 batch rows
@@ -886,9 +713,16 @@ static int64_t wgrad_part_floats(int64_t B, int M, int N) {
 }
 
 static void mlp_free_batch(open_mlp *p) {
-  float *fs[] = {p->z1, p->h1, p->z2, p->h2, p->out, p->dout, p->d2, p->d1, p->xd, p->wpart};
-  for (float *f : fs) (void)hipFree(f);
-  p->z1 = p->h1 = p->z2 = p->h2 = p->out = p->dout = p->d2 = p->d1 = p->xd = p->wpart = nullptr;
+  for (uint16_t **f : {&p->x, &p->h1, &p->h2, &p->d1p, &p->d2p, &p->d3p}) {
+    (void)hipFree(*f);
+    *f = nullptr;
+  }
+  for (float **f : {&p->d1, &p->d2, &p->d3}) {
+    (void)hipFree(*f);
+    *f = nullptr;
+  }
+  (void)hipFree(p->lpart);
+  p->lpart = nullptr;
   p->cap = 0;
 }
 
@@ -898,14 +732,15 @@ static open_status mlp_batch_buffers(open_mlp *p, int64_t B) {
   if (ctx->capturing) return fail(ctx, OPEN_E_UNSUPPORTED, "buffer growth during graph capture");
   OPEN_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   mlp_free_batch(p);
-  const size_t a = sizeof(float) * (size_t)B * p->H, o = sizeof(float) * (size_t)B * p->k;
-  const size_t x = sizeof(float) * (size_t)B * 2 * p->n;
-  int64_t wp = wgrad_part_floats(B, p->k, p->H);
-  if (wgrad_part_floats(B, p->H, p->H) > wp) wp = wgrad_part_floats(B, p->H, p->H);
-  if (wgrad_part_floats(B, p->H, 2 * p->n) > wp) wp = wgrad_part_floats(B, p->H, 2 * p->n);
-  if (hipMalloc(&p->z1, a) || hipMalloc(&p->h1, a) || hipMalloc(&p->z2, a) || hipMalloc(&p->h2, a) ||
-      hipMalloc(&p->out, o) || hipMalloc(&p->dout, o) || hipMalloc(&p->d2, a) || hipMalloc(&p->d1, a) ||
-      hipMalloc(&p->xd, x) || hipMalloc(&p->wpart, sizeof(float) * (size_t)wp)) {
+  const size_t R = (size_t)pad_rows(B), H = (size_t)p->H;
+  const size_t h = sizeof(uint16_t) * R * H, f = sizeof(float) * R * H;
+  // partial losses: one per block of at least 16 rows and 32 outputs
+  const size_t parts = R / 16 * ((size_t)pad_units(p->k) / 32);
+  if (hipMalloc(&p->x, sizeof(uint16_t) * R * (size_t)pad_units(2 * p->n)) || hipMalloc(&p->h1, h) ||
+      hipMalloc(&p->h2, h) || hipMalloc(&p->d1p, h) || hipMalloc(&p->d2p, h) ||
+      hipMalloc(&p->d3p, sizeof(uint16_t) * R * (size_t)pad_units(p->k)) || hipMalloc(&p->d1, f) ||
+      hipMalloc(&p->d2, f) || hipMalloc(&p->d3, sizeof(float) * R * (size_t)p->k) ||
+      hipMalloc(&p->lpart, sizeof(double) * parts)) {
     (void)hipGetLastError();
     mlp_free_batch(p);
     return fail(ctx, OPEN_E_NOMEM, "surrogate batch buffers");
@@ -916,86 +751,80 @@ static open_status mlp_batch_buffers(open_mlp *p, int64_t B) {
 
 static open_status mlp_repack(open_mlp *p) {
   OPEN_LAUNCH(p->ctx, "mlp_pack_w1p", k_pack_w1p, dim3(1024), dim3(256), 0, p->w, p->H, p->n, p->w1p);
-  OPEN_LAUNCH(p->ctx, "mlp_pack_w2p", k_pack_w2p, dim3(32), dim3(256), 0, p->w + p->off_w2, p->w2p);
-  OPEN_LAUNCH(p->ctx, "mlp_pack_w3p", k_pack_w3p, dim3(8), dim3(256), 0, p->w + p->off_w3, p->k, p->w3p);
-  return OPEN_OK;
-}
-
-// forward over B rows (rows nullable) into p->out; saves z1, h1, z2, h2
-static open_status mlp_forward_batch(open_mlp *p, int64_t B, const int64_t *rows, const int64_t *ptr,
-                                     const int32_t *col, const float *val, float *out) {
-  open_ctx *ctx = p->ctx;
   const int H = p->H, k = p->k;
-  int64_t blocks = (B + 3) / 4;
-  if (blocks > ctx->num_cu * 8) blocks = ctx->num_cu * 8;
-  OPEN_LAUNCH(ctx, "mlp_layer1", k_layer1, dim3((unsigned)blocks), dim3(256), 0, B, rows, ptr, col, val, p->n, p->w1p,
-              p->w + p->off_b1, p->z1, p->h1);
-  open_status st;
-  if ((st = gemm<EPI_BIAS_GELU>(ctx, "mlp_gemm_l2", (int)B, H, H, p->h1, H, 1, p->w + p->off_w2, H, 1, p->h2, H,
-                                p->w + p->off_b2, p->z2, H)))
-    return st;
-  return gemm<EPI_BIAS>(ctx, "mlp_gemm_l3", (int)B, k, H, p->h2, H, 1, p->w + p->off_w3, H, 1, out, k,
-                        p->w + p->off_b3);
-}
-
-// weight and bias gradient of a dense layer (M outputs, N inputs) into g_w (M*N weights
-// followed by M biases), split over the batch and reduced in slice order
-static open_status wgrad(open_mlp *p, const char *name, int M, int N, int64_t B, const float *dY, const float *X,
-                         float *g_w) {
-  open_ctx *ctx = p->ctx;
-  int kc;
-  const int S = wgrad_slices(B, M, N, &kc);
-  const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)S);
-  OPEN_LAUNCH(ctx, name, k_gemm_wgrad, grid, dim3(256), 0, M, N, (int)B, kc, dY, X, p->wpart);
-  const int64_t tot = (int64_t)M * N + M;
-  int64_t blocks = (tot + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  OPEN_LAUNCH(ctx, "mlp_reduce_slices", k_reduce_slices, dim3((unsigned)blocks), dim3(256), 0, tot, S, p->wpart, g_w);
+  OPEN_LAUNCH(p->ctx, "mlp_pack_w2p", k_pack_mfma<false>, dim3(64), dim3(256), 0, p->w + p->off_w2, H, H,
+              (uint16_t *)p->w2p);
+  OPEN_LAUNCH(p->ctx, "mlp_pack_w2t", k_pack_mfma<true>, dim3(64), dim3(256), 0, p->w + p->off_w2, H, H,
+              (uint16_t *)p->w2t);
+  OPEN_LAUNCH(p->ctx, "mlp_pack_w3p", k_pack_mfma<false>, dim3(16), dim3(256), 0, p->w + p->off_w3, k, H,
+              (uint16_t *)p->w3p);
+  OPEN_LAUNCH(p->ctx, "mlp_pack_w3t", k_pack_mfma<true>, dim3(16), dim3(256), 0, p->w + p->off_w3, H, k,
+              (uint16_t *)p->w3t);
   return OPEN_OK;
 }
 
-// loss + gradient of the batch into p->g (and the loss scalar into loss_d / loss_f / the
-// per-step record)
-static open_status mlp_backward_batch(open_mlp *p, int64_t B, const int64_t *rows, const int64_t *ptr,
-                                      const int32_t *col, const float *val, const float *target, double *loss_d,
-                                      float *loss_f, float *loss_steps) {
+static MlpBatch mlp_batch(const open_mlp *p, int64_t B, const int64_t *rows, int use_cursor, const int64_t *ptr,
+                          const int32_t *col, const float *val) {
+  MlpBatch b = {};
+  b.B = B;
+  b.rows = rows;
+  b.use_cursor = use_cursor;
+  b.ptr = ptr;
+  b.col = col;
+  b.val = val;
+  b.n = p->n;
+  b.k = p->k;
+  b.W1P = p->w1p;
+  b.b1 = p->w + p->off_b1;
+  b.b2 = p->w + p->off_b2;
+  b.b3 = p->w + p->off_b3;
+  b.W2P = p->w2p;
+  b.W3P = p->w3p;
+  b.W2T = p->w2t;
+  b.W3T = p->w3t;
+  b.st = p->tstate;
+  return b;
+}
+
+// Loss and gradients of a batch, in two launches: forward and backward, then the weight
+// gradients, with the Adam update (lr > 0) or into p->g (lr = 0).
+static open_status mlp_step(open_mlp *p, int64_t B, const int64_t *rows, int use_cursor, const int64_t *ptr,
+                            const int32_t *col, const float *val, const float *target, float lr, float *loss_out,
+                            float *loss_steps) {
   open_ctx *ctx = p->ctx;
   const int H = p->H, k = p->k, n = p->n;
+  MlpBatch b = mlp_batch(p, B, rows, use_cursor, ptr, col, val);
+  b.target = target;
+  b.X = p->x;
+  b.h1 = p->h1;
+  b.h2 = p->h2;
+  b.d1p = p->d1p;
+  b.d2p = p->d2p;
+  b.d3p = p->d3p;
+  b.d1 = p->d1;
+  b.d2 = p->d2;
+  b.d3 = p->d3;
+  b.lpart = p->lpart;
   open_status st;
-  OPEN_LAUNCH(ctx, "mlp_loss", k_loss, dim3(kLossBlocks), dim3(256), 0, B, k, p->out, rows, target, p->dout, p->part);
-  OPEN_LAUNCH(ctx, "mlp_loss_final", k_loss_final, dim3(1), dim3(64), 0, p->part, kLossBlocks, B * k, loss_d, loss_f,
-              p->tstate, loss_steps);
-  float *g = p->g;
-  // layer 3: gW3[o][i] = sum_b dout[b][o] h2[b][i], gb3 = sum_b dout[b]
-  if ((st = wgrad(p, "mlp_wgrad_l3", k, H, B, p->dout, p->h2, g + p->off_w3))) return st;
-  // d2 = (dout W3) * GELU'(z2)
-  if ((st = gemm<EPI_GELU_GRAD>(ctx, "mlp_gemm_dh2", (int)B, H, k, p->dout, k, 1, p->w + p->off_w3, 1, H, p->d2, H,
-                                nullptr, p->z2, H)))
-    return st;
-  // layer 2: gW2[o][i] = sum_b d2[b][o] h1[b][i], gb2 = sum_b d2[b]
-  if ((st = wgrad(p, "mlp_wgrad_l2", H, H, B, p->d2, p->h1, g + p->off_w2))) return st;
-  // d1 = (d2 W2) * GELU'(z1)
-  if ((st = gemm<EPI_GELU_GRAD>(ctx, "mlp_gemm_dh1", (int)B, H, H, p->d2, H, 1, p->w + p->off_w2, 1, H, p->d1, H,
-                                nullptr, p->z1, H)))
-    return st;
-  // layer 1: gW1[o][c] = sum_b d1[b][o] x_b[c] over the dense input rows, gb1 = sum_b d1[b]
-  // (W1 and b1 are adjacent in the packing)
-  int64_t xb = B < (int64_t)ctx->num_cu * 8 ? B : (int64_t)ctx->num_cu * 8;
-  OPEN_LAUNCH(ctx, "mlp_dense_x", k_dense_x, dim3((unsigned)xb), dim3(64), sizeof(float) * 2 * n, B, rows, ptr, col,
-              val, n, p->xd);
-  return wgrad(p, "mlp_wgrad_l1", H, 2 * n, B, p->d1, p->xd, g);
-}
-
-// one Adam step on a batch (rows nullable: the first B rows), then the step counter
-static open_status mlp_step(open_mlp *p, int64_t B, const int64_t *rows, const int64_t *ptr, const int32_t *col,
-                            const float *val, const float *target, float lr, float *loss_out, float *loss_steps) {
-  open_ctx *ctx = p->ctx;
-  open_status st;
-  if ((st = mlp_forward_batch(p, B, rows, ptr, col, val, p->out))) return st;
-  if ((st = mlp_backward_batch(p, B, rows, ptr, col, val, target, p->loss, loss_out, loss_steps))) return st;
-  OPEN_LAUNCH(ctx, "mlp_adam", k_adam, dim3(1024), dim3(256), 0, p->np, p->w, p->g, p->am, p->av, lr, p->tstate);
-  OPEN_LAUNCH(ctx, "mlp_step_end", k_step_end, dim3(1), dim3(64), 0, p->tstate);
-  return mlp_repack(p);
+  if ((st = mlp_batch_launch(ctx, b, false))) return st;
+  WgradStep g = {};
+  g.l[0] = {p->d1p, p->x, p->d1, H, 2 * n, 0, nullptr, nullptr, (uint16_t *)p->w1p};
+  g.l[1] = {p->d2p, p->h1, p->d2, H, H, p->off_w2, (uint16_t *)p->w2p, (uint16_t *)p->w2t, nullptr};
+  g.l[2] = {p->d3p, p->h2, p->d3, k, H, p->off_w3, (uint16_t *)p->w3p, (uint16_t *)p->w3t, nullptr};
+  g.B = B;
+  g.w = p->w;
+  g.g = p->g;
+  g.m = p->am;
+  g.v = p->av;
+  g.lr = lr;
+  g.st = p->tstate;
+  g.lpart = p->lpart;
+  g.nlpart = mlp_batch_loss_parts(ctx, B, k);
+  g.ltotal = B * k;
+  g.loss_d = p->loss;
+  g.loss_f = loss_out;
+  g.loss_steps = loss_steps;
+  return wgrad_step(ctx, "mlp_wgrad_adam", g, lr > 0.f);
 }
 
 // ---------------------------------------------------------------- shared dense-training entry
@@ -1118,7 +947,8 @@ open_status open_mlp_create(open_ctx *ctx, open_mlp **out, int32_t n, int32_t k,
   if (hipMalloc(&p->w, bytes) || hipMalloc(&p->g, bytes) || hipMalloc(&p->am, bytes) || hipMalloc(&p->av, bytes) ||
       hipMalloc(&p->w1p, sizeof(uint32_t) * (size_t)hidden * n) || hipMalloc(&p->w2p, sizeof(uint4) * 8192) ||
       hipMalloc(&p->w3p, sizeof(uint4) * 2048) ||
-      hipMalloc(&p->part, sizeof(double) * (kLossBlocks + 8)) || hipMalloc(&p->loss, sizeof(double) * 8) ||
+      hipMalloc(&p->w2t, sizeof(uint4) * 8192) || hipMalloc(&p->w3t, sizeof(uint4) * 2048) ||
+      hipMalloc(&p->loss, sizeof(double) * 8) ||
       hipMalloc(&p->tstate, sizeof(TrainState))) {
     (void)hipGetLastError();
     open_mlp_destroy(p);
@@ -1156,8 +986,9 @@ open_status open_mlp_destroy(open_mlp *p) {
   (void)hipFree(p->w1p);
   (void)hipFree(p->w2p);
   (void)hipFree(p->w3p);
+  (void)hipFree(p->w2t);
+  (void)hipFree(p->w3t);
   (void)hipFree(p->tstate);
-  (void)hipFree(p->part);
   (void)hipFree(p->loss);
   (void)hipFree(p->rho);
   (void)hipFree(p->flag);
@@ -1194,13 +1025,10 @@ open_status open_mlp_forward(open_mlp *p, int64_t m, const int64_t *row_ptr, con
   if (m < 0 || m >= INT32_MAX || (m > 0 && (!row_ptr || !col || !val || !U_hat)))
     return fail(ctx, OPEN_E_INVALID, "bad shape or pointer");
   OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
-  open_status st;
-  for (int64_t b0 = 0; b0 < m; b0 += kMaxBatchRows) {
-    const int64_t B = m - b0 < kMaxBatchRows ? m - b0 : kMaxBatchRows;
-    if ((st = mlp_batch_buffers(p, B))) return st;
-    if ((st = mlp_forward_batch(p, B, nullptr, row_ptr + b0, col, val, U_hat + b0 * p->k))) return st;
-  }
-  return OPEN_OK;
+  if (m == 0) return OPEN_OK;
+  MlpBatch b = mlp_batch(p, m, nullptr, 0, row_ptr, col, val);
+  b.out = U_hat;
+  return mlp_batch_launch(ctx, b, true);
 }
 
 open_status open_mlp_loss_grad(open_mlp *p, int64_t m, const int64_t *row_ptr, const int32_t *col,
@@ -1212,8 +1040,7 @@ open_status open_mlp_loss_grad(open_mlp *p, int64_t m, const int64_t *row_ptr, c
   OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
   open_status st;
   if ((st = mlp_batch_buffers(p, m))) return st;
-  if ((st = mlp_forward_batch(p, m, nullptr, row_ptr, col, val, p->out))) return st;
-  if ((st = mlp_backward_batch(p, m, nullptr, row_ptr, col, val, target, p->loss, nullptr, nullptr))) return st;
+  if ((st = mlp_step(p, m, nullptr, 0, row_ptr, col, val, target, 0.f, nullptr, nullptr))) return st;
   OPEN_HIP_TRY(ctx, hipMemcpyAsync(grads_host, p->g, sizeof(float) * p->np, hipMemcpyDeviceToHost, ctx->stream));
   double *h;
   if ((st = pinned_get(ctx, 64, (void **)&h))) return st;
@@ -1235,7 +1062,7 @@ open_status open_mlp_train_step(open_mlp *p, int64_t m, const int64_t *row_ptr, 
   OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
   open_status st;
   if ((st = mlp_batch_buffers(p, batch))) return st;
-  return mlp_step(p, batch, rows, row_ptr, col, val, target, lr, loss_out, nullptr);
+  return mlp_step(p, batch, rows, 0, row_ptr, col, val, target, lr, loss_out, nullptr);
 }
 
 open_status open_mlp_train(open_mlp *p, int64_t m, const int64_t *row_ptr, const int32_t *col, const float *val,
@@ -1257,28 +1084,24 @@ open_status open_mlp_train(open_mlp *p, int64_t m, const int64_t *row_ptr, const
   while (h < 31 && (int64_t(1) << (2 * h)) < m) ++h;
   open_status st;
   if ((st = mlp_batch_buffers(p, batch))) return st;
-  int64_t *perm = nullptr, *rows = nullptr;
+  int64_t *perm = nullptr;
   float *losses = nullptr;
   int64_t *t0h = nullptr;
-  if (hipMalloc(&perm, sizeof(int64_t) * (size_t)m) || hipMalloc(&rows, sizeof(int64_t) * (size_t)batch) ||
-      hipMalloc(&losses, sizeof(float) * (size_t)total)) {
+  if (hipMalloc(&perm, sizeof(int64_t) * (size_t)m) || hipMalloc(&losses, sizeof(float) * (size_t)total)) {
     (void)hipGetLastError();
     (void)hipFree(perm);
-    (void)hipFree(rows);
     (void)hipFree(losses);
     return fail(ctx, OPEN_E_NOMEM, "training buffers");
   }
   // the per-step losses are indexed by the Adam step count, which may not start at zero
   if ((st = pinned_get(ctx, 64, (void **)&t0h))) {
     (void)hipFree(perm);
-    (void)hipFree(rows);
     (void)hipFree(losses);
     return st;
   }
   if (hipMemcpyAsync(t0h, p->tstate, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
       hipStreamSynchronize(ctx->stream) != hipSuccess) {
     (void)hipFree(perm);
-    (void)hipFree(rows);
     (void)hipFree(losses);
     return fail(ctx, OPEN_E_DEVICE, "reading the step counter");
   }
@@ -1287,9 +1110,7 @@ open_status open_mlp_train(open_mlp *p, int64_t m, const int64_t *row_ptr, const
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   auto one_step = [&]() -> open_status {
-    OPEN_LAUNCH(ctx, "mlp_rows_of_step", k_rows_of_step, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, perm,
-                batch, p->tstate, rows);
-    return mlp_step(p, batch, rows, row_ptr, col, val, target, lr, nullptr, loss_rec);
+    return mlp_step(p, batch, perm, 1, row_ptr, col, val, target, lr, nullptr, loss_rec);
   };
   const int64_t sblocks = (m + 255) / 256 < 4096 ? (m + 255) / 256 : 4096;
   for (int32_t e = 0; e < epochs && st == OPEN_OK; ++e) {
@@ -1333,7 +1154,6 @@ open_status open_mlp_train(open_mlp *p, int64_t m, const int64_t *row_ptr, const
   }
   (void)hipStreamSynchronize(ctx->stream);
   (void)hipFree(perm);
-  (void)hipFree(rows);
   (void)hipFree(losses);
   return st;
 }
