@@ -9,9 +9,8 @@
 // nearest even) for the products.  The sparse first layer accumulates value x weight in
 // float32 from a transposed bfloat16 copy of W1 (one contiguous hidden vector per input
 // feature).  The dense products run on BF16 MFMA (v_mfma_f32_32x32x16_bf16) with float32
-// accumulation through one tiled GEMM kernel whose epilogue adds the bias and applies GELU,
-// or multiplies by GELU'(z) in the backward pass.  The sparse W1 gradient is accumulated per
-// input feature over a column view of the batch, in a fixed order (no float atomics).
+// accumulation.  The batched forward and the training step are in mlp_train.hip and
+// wgrad.hip; here are the fused inference, the weight copies, the seeded shuffle and the handle.
 #include <limits.h>
 #include <math.h>
 #include <string.h>
@@ -49,228 +48,9 @@ __global__ void k_pack_mfma(const float *__restrict__ W, int N, int Kd, uint16_t
   }
 }
 
-// ---------------------------------------------------------------- tiled BF16 MFMA GEMM
-// C[m][n] = sum_k A(m, k) B(n, k), A(m, k) = A[m*sam + k*sak], B(n, k) = B[n*sbn + k*sbk],
-// float32 operands rounded to bfloat16 when staged in LDS, float32 accumulation.
-// Block tile 64 x 64, four wavefronts of 32 x 32 (v_mfma_f32_32x32x16_bf16), K chunks of 32.
-
-
-// Operand staging of the BF16 MFMA products.  A 64-row tile of X(r, k) = X[r*sr + k*sk] is
-// staged one strip of up to kStripK k values at a time: every thread first issues all of its
-// loads (8 chunks of 32 k, 8 values each, zero outside R x Kd), then packs each group of 8
-// consecutive k into one 16-byte LDS store (bfloat16, round to nearest even, k-fast rows of
-// pitch kLdk).  Threads are laid out so that global reads are contiguous across lanes: four
-// threads per row when k is the fast index, 64 rows per k-group when the row is.
-constexpr int kStripK = 256;
-constexpr int kLdk = kStripK + 8;  // LDS row pitch in bf16 (pads banks)
-
-__device__ __forceinline__ void strip_load(float (&v)[8][8], const float *__restrict__ X, int64_t sr, int64_t sk,
-                                           int64_t r0, int64_t R, int k0, int Kd, bool kfast) {
-  const int t = threadIdx.x;
-  const int row = kfast ? t >> 2 : t & 63, kg = kfast ? t & 3 : t >> 6;
-  const int64_t gr = r0 + row;
-  const bool rok = gr < R;
-  const float *base = X + (rok ? gr : 0) * sr;
-#pragma unroll
-  for (int c = 0; c < 8; ++c)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int gk = k0 + 32 * c + 8 * kg + e;
-      v[c][e] = (rok && gk < Kd) ? base[(int64_t)gk * sk] : 0.f;
-    }
-}
-
-__device__ __forceinline__ void strip_store(uint16_t *__restrict__ Xs, const float (&v)[8][8], bool kfast, int nch) {
-  const int t = threadIdx.x;
-  const int row = kfast ? t >> 2 : t & 63, kg = kfast ? t & 3 : t >> 6;
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    if (c < nch) {
-      uint32_t pk[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) pk[e] = bf16pack(v[c][2 * e], v[c][2 * e + 1]);
-      *reinterpret_cast<uint4 *>(Xs + row * kLdk + 32 * c + 8 * kg) = uint4{pk[0], pk[1], pk[2], pk[3]};
-    }
-  }
-}
-
-// acc += As[wm*32 .., 0..klen) x Bs[wn*32 .., 0..klen)^T on v_mfma_f32_32x32x16_bf16; lane (i, g)
-// supplies A[i][ks + 8g .. +8] and B[j][ks + 8g .. +8]
-__device__ __forceinline__ void strip_mfma(f16 &acc, const uint16_t *__restrict__ As, const uint16_t *__restrict__ Bs,
-                                           int wm, int wn, int klen) {
-  const int lane = threadIdx.x & 63, i = lane & 31, g = lane >> 5;
-  const uint16_t *pa = As + (wm * 32 + i) * kLdk + 8 * g, *pb = Bs + (wn * 32 + i) * kLdk + 8 * g;
-  for (int ks = 0; ks < klen; ks += 16) {
-    const uint4 av = *reinterpret_cast<const uint4 *>(pa + ks);
-    const uint4 bv = *reinterpret_cast<const uint4 *>(pb + ks);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv),
-                                                  acc, 0, 0, 0);
-  }
-}
-
-// C[m][n] = epilogue(sum_k A(m, k) B(n, k)), A(m, k) = A[m*sam + k*sak], B(n, k) = B[n*sbn + k*sbk];
-// block tile 64 x 64, four wavefronts of 32 x 32.
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm(int M, int N, int Kd, const float *__restrict__ A, int64_t sam,
-                                              int64_t sak, const float *__restrict__ Bm, int64_t sbn, int64_t sbk,
-                                              float *__restrict__ C, int64_t ldc, const float *__restrict__ bias,
-                                              float *__restrict__ Z, int64_t ldz) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[64 * kLdk];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[64 * kLdk];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wm = w >> 1, wn = w & 1;
-  const int64_t m0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
-  f16 acc = {};
-  for (int k0 = 0; k0 < Kd; k0 += kStripK) {
-    const int klen = Kd - k0 < kStripK ? Kd - k0 : kStripK;
-    float va[8][8], vb[8][8];
-    strip_load(va, A, sam, sak, m0, M, k0, Kd, sak == 1);
-    strip_load(vb, Bm, sbn, sbk, n0, N, k0, Kd, sbk == 1);
-    if (k0 > 0) __syncthreads();  // the previous strip's LDS reads are done
-    strip_store(As, va, sak == 1, (klen + 31) / 32);
-    strip_store(Bs, vb, sbk == 1, (klen + 31) / 32);
-    __syncthreads();
-    strip_mfma(acc, As, Bs, wm, wn, klen);
-  }
-  const int jc = lane & 31, hf = lane >> 5;
-  const int64_t gn = n0 + wn * 32 + jc;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int64_t gm = m0 + wm * 32 + 8 * (v / 4) + 4 * hf + (v % 4);
-    if (gm >= M || gn >= N) continue;
-    float x = acc[v];
-    if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_SELU) x += bias[gn];
-    if (EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_SELU) {
-      Z[gm * ldz + gn] = x;
-      x = EPI == EPI_BIAS_GELU ? gelu(x) : selu(x);
-    }
-    if (EPI == EPI_GELU_GRAD) x *= gelu_grad(Z[gm * ldz + gn]);
-    if (EPI == EPI_SELU_GRAD) x *= selu_grad(Z[gm * ldz + gn]);
-    C[gm * ldc + gn] = x;
-  }
-}
-
-// Weight gradient of a dense layer over a batch, split over the batch: slice s = blockIdx.z
-// of kc batch rows writes
-//   part[s][m][n] = sum_{b in s} A[b][m] Bv[b][n]     (bfloat16 products, float32 accumulation)
-//   part[s][M*N + m] = sum_{b in s} A[b][m]            (the bias gradient, float32)
-// with A = the layer's output gradient (Bsz x M, row-major) and Bv = its input (Bsz x N).  The
-// slices are added in order by k_reduce_slices, so the result does not depend on scheduling.
-__global__ __launch_bounds__(256) void k_gemm_wgrad(int M, int N, int Bsz, int kc, const float *__restrict__ A,
-                                                    const float *__restrict__ Bv, float *__restrict__ part) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[64 * kLdk];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[64 * kLdk];
-  __shared__ float bred[4][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wm = w >> 1, wn = w & 1;
-  const int64_t m0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
-  const int s = blockIdx.z;
-  const int b0 = s * kc, b1 = b0 + kc < Bsz ? b0 + kc : Bsz;
-  const float *Ag = A + (int64_t)b0 * M, *Bg = Bv + (int64_t)b0 * N;
-  const int kd = b1 - b0;
-  float bsum = 0.f;  // thread (row t % 64, k-group t / 64): its staged values of A, in order
-  f16 acc = {};
-  for (int k0 = 0; k0 < kd; k0 += kStripK) {
-    const int klen = kd - k0 < kStripK ? kd - k0 : kStripK;
-    float va[8][8], vb[8][8];
-    // rows are the fast index of both operands (also when M or N is 1)
-    strip_load(va, Ag, 1, M, m0, M, k0, kd, false);
-    strip_load(vb, Bg, 1, N, n0, N, k0, kd, false);
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) bsum += va[c][e];
-    if (k0 > 0) __syncthreads();
-    strip_store(As, va, false, (klen + 31) / 32);
-    strip_store(Bs, vb, false, (klen + 31) / 32);
-    __syncthreads();
-    strip_mfma(acc, As, Bs, wm, wn, klen);
-  }
-  float *dst = part + (int64_t)s * ((int64_t)M * N + M);
-  const int jc = lane & 31, hf = lane >> 5;
-  const int64_t gn = n0 + wn * 32 + jc;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int64_t gm = m0 + wm * 32 + 8 * (v / 4) + 4 * hf + (v % 4);
-    if (gm < M && gn < N) dst[gm * N + gn] = acc[v];
-  }
-  if (blockIdx.x == 0) {
-    bred[threadIdx.x >> 6][threadIdx.x & 63] = bsum;
-    __syncthreads();
-    if (threadIdx.x < 64 && m0 + threadIdx.x < M)
-      dst[(int64_t)M * N + m0 + threadIdx.x] =
-          ((bred[0][threadIdx.x] + bred[1][threadIdx.x]) + bred[2][threadIdx.x]) + bred[3][threadIdx.x];
-  }
-}
-
-// out[i] = sum_{s = 0..S-1} part[s][i] in slice order (eight slices' loads in flight)
-__global__ __launch_bounds__(256) void k_reduce_slices(int64_t total, int S, const float *__restrict__ part,
-                                                       float *__restrict__ out) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    float acc = 0.f;
-    int s = 0;
-    for (; s + 8 <= S; s += 8) {
-      float x[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = part[(int64_t)(s + e) * total + i];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc += x[e];
-    }
-    for (; s < S; ++s) acc += part[(int64_t)s * total + i];
-    out[i] = acc;
-  }
-}
-
-template <int EPI>
-static open_status gemm(open_ctx *ctx, const char *name, int M, int N, int Kd, const float *A, int64_t sam,
-                        int64_t sak, const float *Bm, int64_t sbn, int64_t sbk, float *C, int64_t ldc,
-                        const float *bias = nullptr, float *Z = nullptr, int64_t ldz = 0) {
-  const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-  OPEN_LAUNCH(ctx, name, k_gemm<EPI>, grid, dim3(256), 0, M, N, Kd, A, sam, sak, Bm, sbn, sbk, C, ldc, bias, Z, ldz);
-  return OPEN_OK;
-}
-
-// ---------------------------------------------------------------- loss, reductions, Adam
-// Optimizer state on the device, so that a recorded training step can be replayed as is:
-// t = Adam steps taken, cursor = batch index within the epoch, c1/c2 = bias corrections of
-// the next step, 1 - beta1^(t+1) and 1 - beta2^(t+1).
-
-__device__ __forceinline__ void train_state_set(TrainState *st, int64_t t) {
-  st->t = t;
-  st->c1 = (float)(1.0 - pow(0.9, (double)(t + 1)));
-  st->c2 = (float)(1.0 - pow(0.999, (double)(t + 1)));
-}
-
+// ---------------------------------------------------------------- step state, shuffle, fallback
 __global__ void k_train_state_reset(TrainState *st) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    train_state_set(st, 0);
-    st->cursor = 0;
-  }
-}
-
-// end of a training step: one more Adam step, next batch
-__global__ void k_step_end(TrainState *st) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    train_state_set(st, st->t + 1);
-    st->cursor += 1;
-  }
-}
-
-__global__ void k_loss_final(const double *__restrict__ part, int nparts, int64_t total, double *__restrict__ loss_d,
-                             float *__restrict__ loss_f, const TrainState *__restrict__ st,
-                             float *__restrict__ loss_steps) {
-  // lane l adds partials l, l + 64, ... in order, then a fixed butterfly combines the lanes
-  const int lane = threadIdx.x;
-  double s = 0.0;
-  for (int i = lane; i < nparts; i += 64) s += part[i];
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (lane == 0) {
-    s /= (double)total;
-    if (loss_d) loss_d[0] = s;
-    if (loss_f) loss_f[0] = (float)s;
-    if (loss_steps) loss_steps[st->t] = (float)s;
-  }
+  if (threadIdx.x == 0 && blockIdx.x == 0) *st = TrainState{0, 0, 0.f, 0.f, 0};
 }
 
 // ---- seeded shuffle of the training rows, on the device
@@ -309,33 +89,6 @@ __global__ __launch_bounds__(256) void k_shuffle(int64_t m, int h, uint64_t seed
     perm[i] = (int64_t)x;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) st->cursor = 0;
-}
-
-// the rows of the current batch: rows[t] = perm[cursor * batch + t]
-__global__ __launch_bounds__(256) void k_rows_of_step(const int64_t *__restrict__ perm, int batch,
-                                                      const TrainState *__restrict__ st, int64_t *__restrict__ rows) {
-  const int64_t off = st->cursor * (int64_t)batch;
-  for (int t = blockIdx.x * 256 + threadIdx.x; t < batch; t += gridDim.x * 256) rows[t] = perm[off + t];
-}
-
-__global__ void k_adam(int64_t np, float *__restrict__ w, const float *__restrict__ g, float *__restrict__ m,
-                       float *__restrict__ v, float lr, const TrainState *__restrict__ st) {
-  const float c1 = st->c1, c2 = st->c2;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < np; i += (int64_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = 0.9f * m[i] + 0.1f * gi;
-    const float vi = 0.999f * v[i] + 0.001f * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
-  }
-}
-
-// fallback decision: used[i] = !(rho_i <= tau) (NaN falls back), nonempty rows only
-__global__ void k_fallback_flag(int64_t m, const int64_t *__restrict__ ptr, const float *__restrict__ rho, float tau,
-                                uint8_t *__restrict__ used) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-    used[i] = (ptr[i + 1] > ptr[i]) && !(rho[i] <= tau);
 }
 
 __global__ void k_count_u8(int64_t m, const uint8_t *__restrict__ f, int64_t *__restrict__ out) {
@@ -690,28 +443,6 @@ namespace openk {
 
 constexpr int kMaxBatchRows = 16384;
 
-// batch slices of the weight-gradient product of an M x N layer: about 1024 blocks over the
-// 64 x 64 output tiles, each slice a multiple of 32 batch rows
-static int wgrad_slices(int64_t B, int M, int N, int *kc) {
-  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-  int64_t S = (1024 + tiles - 1) / tiles;
-  if (S > 256) S = 256;
-  int64_t c = (B + S - 1) / S;
-  c = (c + 31) / 32 * 32;
-  *kc = (int)c;
-  return (int)((B + c - 1) / c);
-}
-
-// partial floats of an M x N weight gradient for any batch of at most B rows (the slice count
-// does not grow with B, but a smaller batch can take up to its target count)
-static int64_t wgrad_part_floats(int64_t B, int M, int N) {
-  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-  int64_t S = (1024 + tiles - 1) / tiles;
-  if (S > 256) S = 256;
-  const int64_t smax = (B + 31) / 32;  // slices are at least 32 rows
-  return (S < smax ? S : smax) * ((int64_t)M * N + M);
-}
-
 static void mlp_free_batch(open_mlp *p) {
   for (uint16_t **f : {&p->x, &p->h1, &p->h2, &p->d1p, &p->d2p, &p->d3p}) {
     (void)hipFree(*f);
@@ -827,53 +558,10 @@ static open_status mlp_step(open_mlp *p, int64_t B, const int64_t *rows, int use
   return wgrad_step(ctx, "mlp_wgrad_adam", g, lr > 0.f);
 }
 
-// ---------------------------------------------------------------- shared dense-training entry
-// points (declared in dense.h; the NCF training composes them)
-open_status dense_gemm(open_ctx *ctx, const char *name, int epi, int M, int N, int Kd, const float *A, int64_t sam,
-                       int64_t sak, const float *Bm, int64_t sbn, int64_t sbk, float *C, int64_t ldc, const float *bias,
-                       float *Z, int64_t ldz) {
-  switch (epi) {
-    case EPI_STORE: return gemm<EPI_STORE>(ctx, name, M, N, Kd, A, sam, sak, Bm, sbn, sbk, C, ldc, bias, Z, ldz);
-    case EPI_BIAS: return gemm<EPI_BIAS>(ctx, name, M, N, Kd, A, sam, sak, Bm, sbn, sbk, C, ldc, bias, Z, ldz);
-    case EPI_BIAS_SELU:
-      return gemm<EPI_BIAS_SELU>(ctx, name, M, N, Kd, A, sam, sak, Bm, sbn, sbk, C, ldc, bias, Z, ldz);
-    case EPI_SELU_GRAD:
-      return gemm<EPI_SELU_GRAD>(ctx, name, M, N, Kd, A, sam, sak, Bm, sbn, sbk, C, ldc, bias, Z, ldz);
-    default: return fail(ctx, OPEN_E_INVALID, "unknown GEMM epilogue");
-  }
-}
-
-int64_t dense_wgrad_part_floats(int64_t B, int M, int N) { return wgrad_part_floats(B, M, N); }
-
-open_status dense_wgrad(open_ctx *ctx, const char *name, int M, int N, int64_t B, const float *dY, const float *X,
-                        float *part, float *g_w) {
-  int kc;
-  const int S = wgrad_slices(B, M, N, &kc);
-  const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)S);
-  OPEN_LAUNCH(ctx, name, k_gemm_wgrad, grid, dim3(256), 0, M, N, (int)B, kc, dY, X, part);
-  const int64_t tot = (int64_t)M * N + M;
-  int64_t blocks = (tot + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  OPEN_LAUNCH(ctx, "reduce_slices", k_reduce_slices, dim3((unsigned)blocks), dim3(256), 0, tot, S, part, g_w);
-  return OPEN_OK;
-}
-
+// ---------------------------------------------------------------- shared with the NCF training
+// (declared in dense.h)
 open_status dense_train_state_reset(open_ctx *ctx, TrainState *st) {
   OPEN_LAUNCH(ctx, "train_state_reset", k_train_state_reset, dim3(1), dim3(64), 0, st);
-  return OPEN_OK;
-}
-
-open_status dense_adam_step(open_ctx *ctx, int64_t np, float *w, const float *g, float *am, float *av, float lr,
-                            TrainState *st) {
-  OPEN_LAUNCH(ctx, "adam", k_adam, dim3(1024), dim3(256), 0, np, w, g, am, av, lr, st);
-  OPEN_LAUNCH(ctx, "step_end", k_step_end, dim3(1), dim3(64), 0, st);
-  return OPEN_OK;
-}
-
-open_status dense_loss_final(open_ctx *ctx, const double *part, int nparts, int64_t total, double *loss_d,
-                             float *loss_f, const TrainState *st, float *loss_steps) {
-  OPEN_LAUNCH(ctx, "loss_final", k_loss_final, dim3(1), dim3(64), 0, part, nparts, total, loss_d, loss_f, st,
-              loss_steps);
   return OPEN_OK;
 }
 
@@ -882,12 +570,6 @@ open_status dense_shuffle(open_ctx *ctx, int64_t m, uint64_t seed, int64_t epoch
   while (h < 31 && (int64_t(1) << (2 * h)) < m) ++h;
   const int64_t blocks = (m + 255) / 256 < 4096 ? (m + 255) / 256 : 4096;
   OPEN_LAUNCH(ctx, "shuffle", k_shuffle, dim3((unsigned)blocks), dim3(256), 0, m, h, seed, epoch, perm, st);
-  return OPEN_OK;
-}
-
-open_status dense_rows_of_step(open_ctx *ctx, const int64_t *perm, int batch, const TrainState *st, int64_t *rows) {
-  OPEN_LAUNCH(ctx, "rows_of_step", k_rows_of_step, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, perm, batch,
-              st, rows);
   return OPEN_OK;
 }
 

@@ -65,6 +65,20 @@ __device__ __forceinline__ f16 mfma_bf16_32(uint4 a, uint4 b, f16 c) {
                                                  0);
 }
 
+// four consecutive batch rows (4 hf .. 4 hf + 3 of group b8) of one unit, rounded, into an operand
+// of the weight gradients ([batch / 8][units][8], wgrad.h)
+__device__ __forceinline__ void store_pack4(uint16_t *P, int64_t b8, int units, int unit, int hf, const float *x) {
+  const uint2 v = uint2{bf16pack(x[0], x[1]), bf16pack(x[2], x[3])};
+  *reinterpret_cast<uint2 *>(P + ((b8 * units + unit) * 8 + 4 * hf)) = v;
+}
+// eight consecutive batch rows (row r at x + r * pitch) of one unit as an operand's 16-byte word
+__device__ __forceinline__ uint4 gather_pack8(const uint16_t *x, int pitch) {
+  uint32_t q[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) q[c] = (uint32_t)x[2 * c * pitch] | ((uint32_t)x[(2 * c + 1) * pitch] << 16);
+  return uint4{q[0], q[1], q[2], q[3]};
+}
+
 // The value r of an observed entry as the pair (bf16(r), 1) that multiplies a weight pair
 // (value weight, mask weight): one dot product adds a r + c.  The value is rounded to bfloat16
 // like the weights (relative error at most 2^-9).  An entry whose column is outside [0, n)

@@ -29,12 +29,6 @@ constexpr int kTrWaves = 8, kTrThreads = 64 * kTrWaves;
 constexpr int kTrHP = 256 + 8;  // LDS pitch of an activation row (bfloat16)
 constexpr int kTrZP = 256 + 4;  // LDS pitch of a z1 row (float32)
 
-// four consecutive batch rows of one unit, rounded, into a packed operand
-__device__ __forceinline__ void store_pack4(uint16_t *P, int64_t b8, int units, int unit, int hf, const float *x) {
-  const uint2 v = uint2{bf16pack(x[0], x[1]), bf16pack(x[2], x[3])};
-  *reinterpret_cast<uint2 *>(P + ((b8 * units + unit) * 8 + 4 * hf)) = v;
-}
-
 template <int R, int CB3, bool FWD>
 __global__ __launch_bounds__(kTrThreads) void k_mlp_fwd_bwd(MlpBatch p) {
   constexpr int RW = R / kTrWaves;  // rows of a wavefront in the first layer
@@ -130,11 +124,7 @@ __global__ __launch_bounds__(kTrThreads) void k_mlp_fwd_bwd(MlpBatch p) {
       }
     }
     for (int e = threadIdx.x; e < R / 8 * 256; e += kTrThreads) {
-      const uint16_t *src = Ha + (e >> 8) * 8 * kTrHP + (e & 255);
-      uint32_t q[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) q[c] = (uint32_t)src[2 * c * kTrHP] | ((uint32_t)src[(2 * c + 1) * kTrHP] << 16);
-      reinterpret_cast<uint4 *>(p.h1)[b0 / 8 * 256 + e] = uint4{q[0], q[1], q[2], q[3]};
+      reinterpret_cast<uint4 *>(p.h1)[b0 / 8 * 256 + e] = gather_pack8(Ha + (e >> 8) * 8 * kTrHP + (e & 255), kTrHP);
     }
   }
   // ---- second layer: column 32 w + i32 of rows 8 (v / 4) + 4 g + v % 4
@@ -216,11 +206,7 @@ __global__ __launch_bounds__(kTrThreads) void k_mlp_fwd_bwd(MlpBatch p) {
       b3w[ks] = ks < KS3 ? p.W3T[(w * KS3 + ks) * 64 + lane] : uint4{0u, 0u, 0u, 0u};
 #pragma unroll
     for (int ks = 0; ks < 16; ++ks) bw[ks] = p.W2T[(w * 16 + ks) * 64 + lane];
-    // bias corrections of this step, for the optimizer's launch (which reads them, not t)
-    if (blockIdx.x == 0 && threadIdx.x == kTrThreads - 1) {
-      p.st->c1 = (float)(1.0 - pow(0.9, (double)(p.st->t + 1)));
-      p.st->c2 = (float)(1.0 - pow(0.999, (double)(p.st->t + 1)));
-    }
+    if (blockIdx.x == 0 && threadIdx.x == kTrThreads - 1) train_state_begin(p.st);
     __syncthreads();
     // ---- dz2 = (dout W3) GELU'(z2); h1 is no longer needed
     f16 acc = {};

@@ -12,7 +12,8 @@
 #include <new>
 
 #include "common.h"
-#include "dense.h"
+#include "mlp_net.h"
+#include "wgrad.h"
 
 namespace openk {
 
@@ -245,67 +246,194 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 
 // ---------------------------------------------------------------- offline training
 // The model is trained on the dense offline matrix R (applications x settings, every entry
-// observed) in batches of whole applications: batch entry b = g n + j pairs application
-// apps[g] with setting j.  The products run through the shared BF16 MFMA GEMMs (SELU
-// epilogues) and the batch-split weight gradients; the kernels here gather the inputs, form
-// the loss and sum the embedding gradients in a fixed order.
+// observed) in batches of whole applications: batch row b = g n + j pairs application
+// apps[g] with setting j.  A step is two launches: k_ncf_fwd_bwd takes R rows per block (one
+// wavefront per 32 of the 64 hidden units) through the forward and backward pass on
+// v_mfma_f32_32x32x16_bf16 with the activations in LDS and registers, and wgrad_step contracts
+// the weight gradients over the batch, sums the embedding gradients in order and applies Adam.
+// Bound by launch and load latency: 3840 rows are 0.2 GFLOP.  At 8 x 480: 12 us, and 18 us for
+// the second launch; a step takes 37 us against 250 us as sixteen launches, of which the
+// embedding sums took 129 (one thread per sum, each read waited for).
+struct NcfBatch {
+  int64_t B;                 // batch rows, G n
+  int G, n;
+  const int64_t *apps;       // the batch's applications, from apps + st->cursor * G with use_cursor
+  int use_cursor;
+  const float *E, *S, *W1, *b1, *W2, *b2, *w3, *b3, *R;
+  uint16_t *X, *h1, *h2, *d1p, *d2p, *dyp;  // packed operands, 64 (dyp: 32) wide
+  float *d1, *d2, *dy, *dX;                 // output gradients and the input gradient
+  double *lpart;             // one per block
+  int64_t *apps_out, *mark;  // the batch's applications and their step tag, for wgrad_step
+  TrainState *st;
+};
 
-// X[b] = [E[apps[g]] ; S[j]] (batch x 64)
-__global__ void k_ncf_gather(int64_t B, int n, const int64_t *__restrict__ apps, const float *__restrict__ E,
-                             const float *__restrict__ S, float *__restrict__ X) {
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < B * 2 * kNcfD;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t b = t / (2 * kNcfD);
-    const int c = (int)(t % (2 * kNcfD));
-    const int64_t g = b / n, j = b % n;
-    X[t] = c < kNcfD ? E[apps[g] * kNcfD + c] : S[j * kNcfD + (c - kNcfD)];
+// this lane's B operands of a 64 x 64 weight matrix, output tile w, four steps of k; T: of its
+// transpose
+template <bool T>
+__device__ __forceinline__ void load_operand(uint4 (&bw)[4], const float *__restrict__ W, int w, int i32, int g) {
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int o = 32 * w + i32, i = 16 * ks + 8 * g + e;
+      x[e] = T ? W[i * 64 + o] : W[o * 64 + i];
+    }
+    bw[ks] = uint4{bf16pack(x[0], x[1]), bf16pack(x[2], x[3]), bf16pack(x[4], x[5]), bf16pack(x[6], x[7])};
   }
 }
 
-// dy[b] = 2 (y_b - r_b) / B, block partial sums of (y_b - r_b)^2 in float64
-__global__ __launch_bounds__(256) void k_ncf_loss(int64_t B, int n, const float *__restrict__ y,
-                                                  const int64_t *__restrict__ apps, const float *__restrict__ R,
-                                                  float *__restrict__ dy, double *__restrict__ part) {
-  __shared__ double red[256];
-  double acc = 0.0;
-  const float scale = 2.0f / (float)B;
-  for (int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x; b < B; b += (int64_t)gridDim.x * 256) {
-    const int64_t g = b / n, j = b % n;
-    const float d = y[b] - R[apps[g] * n + j];
-    dy[b] = scale * d;
-    acc += (double)d * (double)d;
+template <int R>
+__global__ __launch_bounds__(128) void k_ncf_fwd_bwd(NcfBatch p) {
+  constexpr int P = 64 + 8, NV = R / 2;  // LDS pitch (bfloat16), result registers in use
+  __shared__ __attribute__((aligned(16))) uint16_t Xs[R * P];   // the inputs, then dz2
+  __shared__ __attribute__((aligned(16))) uint16_t Hs[R * P];   // h1, then dz1
+  __shared__ __attribute__((aligned(16))) uint16_t H2[R * P];
+  __shared__ float dys[R];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i32 = lane & 31, g = lane >> 5;
+  const int64_t b0 = (int64_t)blockIdx.x * R;
+  const int64_t *apps = p.apps + (p.use_cursor ? p.st->cursor * p.G : 0);
+  const int u = 32 * w + i32, ar = i32 & (R - 1);
+  uint4 bw[4], bw2[4];
+  load_operand<false>(bw, p.W1, w, i32, g);
+  load_operand<false>(bw2, p.W2, w, i32, g);
+  // ---- the inputs [e ; s], eight values per thread and round
+#pragma unroll
+  for (int t = tid; t < R * 8; t += 128) {
+    const int lr = t >> 3, c = (t & 7) * 8;
+    const int64_t b = b0 + lr;
+    uint4 v = uint4{0u, 0u, 0u, 0u};
+    if (b < p.B) {
+      const int64_t a = b / p.n, j = b - a * p.n;
+      // the parameter vector's arrays start at any multiple of four bytes
+      const float *src = c < kNcfD ? p.E + apps[a] * kNcfD + c : p.S + j * kNcfD + (c - kNcfD);
+      v = uint4{bf16pack(src[0], src[1]), bf16pack(src[2], src[3]), bf16pack(src[4], src[5]),
+                bf16pack(src[6], src[7])};
+    }
+    *reinterpret_cast<uint4 *>(Xs + lr * P + c) = v;
   }
-  red[threadIdx.x] = acc;
   __syncthreads();
-  for (int s2 = 128; s2 > 0; s2 >>= 1) {
-    if (threadIdx.x < (unsigned)s2) red[threadIdx.x] += red[threadIdx.x + s2];
+  for (int e = tid; e < R / 8 * 64; e += 128)
+    reinterpret_cast<uint4 *>(p.X)[b0 / 8 * 64 + e] = gather_pack8(Xs + (e >> 6) * 8 * P + (e & 63), P);
+  // ---- forward: z1, z2 of hidden unit u for rows 8 (v / 4) + 4 g + v % 4
+  float s1[NV], s2[NV], hv[NV];  // SELU' of both layers
+  f16 acc = {};
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    acc = mfma_bf16_32(*reinterpret_cast<const uint4 *>(Xs + ar * P + 16 * ks + 8 * g), bw[ks], acc);
+  float bias = p.b1[u];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int lr = 8 * (v / 4) + 4 * g + (v % 4);
+    const float z = acc[v] + bias;
+    s1[v] = selu_grad(z);
+    hv[v] = b0 + lr < p.B ? selu(z) : 0.f;
+    Hs[lr * P + u] = f2bf(hv[v]);
+  }
+#pragma unroll
+  for (int q = 0; q < R / 8; ++q) store_pack4(p.h1, b0 / 8 + q, 64, u, g, hv + 4 * q);
+  __syncthreads();
+  acc = f16{};
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    acc = mfma_bf16_32(*reinterpret_cast<const uint4 *>(Hs + ar * P + 16 * ks + 8 * g), bw2[ks], acc);
+  bias = p.b2[u];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int lr = 8 * (v / 4) + 4 * g + (v % 4);
+    const float z = acc[v] + bias;
+    s2[v] = selu_grad(z);
+    hv[v] = b0 + lr < p.B ? selu(z) : 0.f;
+    H2[lr * P + u] = f2bf(hv[v]);
+  }
+#pragma unroll
+  for (int q = 0; q < R / 8; ++q) store_pack4(p.h2, b0 / 8 + q, 64, u, g, hv + 4 * q);
+  load_operand<true>(bw2, p.W2, w, i32, g);  // for the backward pass
+  load_operand<true>(bw, p.W1, w, i32, g);
+  __syncthreads();
+  // ---- output and loss: w3 as column 0 of the product, on the first wavefront
+  if (w == 0) {
+    acc = f16{};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const float *s = p.w3 + 16 * ks + 8 * g;
+      uint4 b = uint4{0u, 0u, 0u, 0u};
+      if (i32 == 0)
+        b = uint4{bf16pack(s[0], s[1]), bf16pack(s[2], s[3]), bf16pack(s[4], s[5]), bf16pack(s[6], s[7])};
+      acc = mfma_bf16_32(*reinterpret_cast<const uint4 *>(H2 + ar * P + 16 * ks + 8 * g), b, acc);
+    }
+    const float scale = 2.0f / (float)p.B;
+    double sq = 0.0;
+    float dv[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const int lr = 8 * (v / 4) + 4 * g + (v % 4);
+      const int64_t b = b0 + lr;
+      dv[v] = 0.f;
+      if (i32 == 0) {
+        if (b < p.B) {
+          const int64_t a = b / p.n;
+          const float d = (acc[v] + p.b3[0]) - p.R[apps[a] * p.n + (b - a * p.n)];
+          dv[v] = scale * d;
+          p.dy[b] = dv[v];
+          sq += (double)d * (double)d;
+        }
+        dys[lr] = dv[v];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < R / 8; ++q) store_pack4(p.dyp, b0 / 8 + q, 32, i32, g, dv + 4 * q);
+    sq += __shfl_xor(sq, 32, 64);
+    if (lane == 0) p.lpart[blockIdx.x] = sq;
+  }
+  __syncthreads();
+  // ---- backward: dz2 = (dy w3) SELU'(z2), the factors rounded as in a product
+  const float w3u = bf2f(f2bf(p.w3[u]));
+  float dz[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int lr = 8 * (v / 4) + 4 * g + (v % 4);
+    dz[v] = (bf2f(f2bf(dys[lr])) * w3u) * s2[v];
+    if (b0 + lr < p.B) p.d2[(b0 + lr) * 64 + u] = dz[v];
+    Xs[lr * P + u] = f2bf(dz[v]);
+  }
+#pragma unroll
+  for (int q = 0; q < R / 8; ++q) store_pack4(p.d2p, b0 / 8 + q, 64, u, g, dz + 4 * q);
+  __syncthreads();
+  // dz1 = (dz2 W2) SELU'(z1)
+  acc = f16{};
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    acc = mfma_bf16_32(*reinterpret_cast<const uint4 *>(Xs + ar * P + 16 * ks + 8 * g), bw2[ks], acc);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int lr = 8 * (v / 4) + 4 * g + (v % 4);
+    dz[v] = acc[v] * s1[v];
+    if (b0 + lr < p.B) p.d1[(b0 + lr) * 64 + u] = dz[v];
+    Hs[lr * P + u] = f2bf(dz[v]);
+  }
+#pragma unroll
+  for (int q = 0; q < R / 8; ++q) store_pack4(p.d1p, b0 / 8 + q, 64, u, g, dz + 4 * q);
+  __syncthreads();
+  // dX = dz1 W1
+  acc = f16{};
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    acc = mfma_bf16_32(*reinterpret_cast<const uint4 *>(Hs + ar * P + 16 * ks + 8 * g), bw[ks], acc);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int lr = 8 * (v / 4) + 4 * g + (v % 4);
+    if (b0 + lr < p.B) p.dX[(b0 + lr) * 64 + u] = acc[v];
+  }
+  if (blockIdx.x == 0) {
+    for (int a = tid; a < p.G; a += 128) {
+      p.apps_out[a] = apps[a];
+      p.mark[apps[a]] = p.st->t + 1;
+    }
     __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-// gE[apps[g]] = sum_j dX[g n + j][0 .. 32) (j in order), gS[j] = sum_g dX[g n + j][32 .. 64)
-// (g in order); the batch's applications are distinct and gE is zero elsewhere
-__global__ void k_ncf_emb_grad(int G, int n, const int64_t *__restrict__ apps, const float *__restrict__ dX,
-                               float *__restrict__ gE, float *__restrict__ gS) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t nE = (int64_t)G * kNcfD, nS = (int64_t)n * kNcfD;
-  if (t < nE) {
-    const int64_t g = t / kNcfD;
-    const int c = (int)(t % kNcfD);
-    float acc = 0.f;
-    for (int j = 0; j < n; ++j) acc += dX[(g * n + j) * 2 * kNcfD + c];
-    gE[apps[g] * kNcfD + c] = acc;
-  } else if (t < nE + nS) {
-    const int64_t j = (t - nE) / kNcfD;
-    const int c = (int)((t - nE) % kNcfD);
-    float acc = 0.f;
-    for (int g = 0; g < G; ++g) acc += dX[((int64_t)g * n + j) * 2 * kNcfD + kNcfD + c];
-    gS[j * kNcfD + c] = acc;
+    if (tid == 0) train_state_begin(p.st);
   }
 }
-
-constexpr int kNcfLossBlocks = 256;
 
 // Parameter packing of the trained model (float32): E (m_off x d), S (n x d), W1 (H x 2d),
 // b1 (H), W2 (H x H), b2 (H), w3 (H), b3 (1).
@@ -326,80 +454,110 @@ struct NcfLayout {
 
 // Device buffers of one training call.
 struct NcfTrainBufs {
-  int64_t B = 0;
-  float *X = nullptr, *Z1 = nullptr, *H1 = nullptr, *Z2 = nullptr, *H2 = nullptr, *y = nullptr, *dy = nullptr;
-  float *dZ2 = nullptr, *dZ1 = nullptr, *dX = nullptr, *part = nullptr, *g = nullptr, *am = nullptr, *av = nullptr;
+  uint16_t *X = nullptr, *h1 = nullptr, *h2 = nullptr, *d1p = nullptr, *d2p = nullptr, *dyp = nullptr;
+  float *d1 = nullptr, *d2 = nullptr, *dy = nullptr, *dX = nullptr, *g = nullptr, *am = nullptr, *av = nullptr;
   double *lpart = nullptr, *loss = nullptr;
+  int64_t *apps = nullptr, *mark = nullptr;
   TrainState *st = nullptr;
   void release() {
-    float *fs[] = {X, Z1, H1, Z2, H2, y, dy, dZ2, dZ1, dX, part, g, am, av};
-    for (float *f : fs) (void)hipFree(f);
+    for (uint16_t *q : {X, h1, h2, d1p, d2p, dyp}) (void)hipFree(q);
+    for (float *q : {d1, d2, dy, dX, g, am, av}) (void)hipFree(q);
+    for (int64_t *q : {apps, mark}) (void)hipFree(q);
     (void)hipFree(lpart);
     (void)hipFree(loss);
     (void)hipFree(st);
   }
-  bool alloc(int64_t Bsz, int64_t np) {
-    B = Bsz;
-    const size_t a = sizeof(float) * (size_t)Bsz * 2 * kNcfD;
-    int64_t wp = dense_wgrad_part_floats(Bsz, kNcfH, kNcfH);
-    if (dense_wgrad_part_floats(Bsz, kNcfH, 2 * kNcfD) > wp) wp = dense_wgrad_part_floats(Bsz, kNcfH, 2 * kNcfD);
-    if (dense_wgrad_part_floats(Bsz, 1, kNcfH) > wp) wp = dense_wgrad_part_floats(Bsz, 1, kNcfH);
-    const bool ok = !hipMalloc(&X, a) && !hipMalloc(&Z1, a) && !hipMalloc(&H1, a) && !hipMalloc(&Z2, a) &&
-                    !hipMalloc(&H2, a) && !hipMalloc(&y, sizeof(float) * Bsz) && !hipMalloc(&dy, sizeof(float) * Bsz) &&
-                    !hipMalloc(&dZ2, a) && !hipMalloc(&dZ1, a) && !hipMalloc(&dX, a) &&
-                    !hipMalloc(&part, sizeof(float) * (size_t)wp) && !hipMalloc(&g, sizeof(float) * (size_t)np) &&
-                    !hipMalloc(&am, sizeof(float) * (size_t)np) && !hipMalloc(&av, sizeof(float) * (size_t)np) &&
-                    !hipMalloc(&lpart, sizeof(double) * (kNcfLossBlocks + 8)) && !hipMalloc(&loss, sizeof(double) * 8) &&
-                    !hipMalloc(&st, sizeof(TrainState));
+  // G n batch rows, np parameters; training: Adam moments, otherwise the gradient
+  bool alloc(int64_t m_off, int G, int n, int64_t np, bool train) {
+    const size_t Bp = (size_t)pad_rows((int64_t)G * n), h = sizeof(uint16_t) * Bp * kNcfH;
+    const size_t f = sizeof(float) * Bp * kNcfH, pb = sizeof(float) * (size_t)np;
+    const bool ok = !hipMalloc(&X, h) && !hipMalloc(&h1, h) && !hipMalloc(&h2, h) && !hipMalloc(&d1p, h) &&
+                    !hipMalloc(&d2p, h) && !hipMalloc(&dyp, h / 2) && !hipMalloc(&d1, f) && !hipMalloc(&d2, f) &&
+                    !hipMalloc(&dy, sizeof(float) * Bp) && !hipMalloc(&dX, f) &&
+                    (train ? !hipMalloc(&am, pb) && !hipMalloc(&av, pb) : !hipMalloc(&g, pb)) &&
+                    !hipMalloc(&lpart, sizeof(double) * (Bp / 16)) && !hipMalloc(&loss, sizeof(double) * 8) &&
+                    !hipMalloc(&apps, sizeof(int64_t) * (size_t)G) &&
+                    !hipMalloc(&mark, sizeof(int64_t) * (size_t)m_off) && !hipMalloc(&st, sizeof(TrainState));
     if (!ok) (void)hipGetLastError();
     return ok;
   }
 };
 
-// Loss and gradient of one batch of G applications (their indices in `apps`, on the device)
-// into b.g; the loss to b.loss and, when given, to loss_steps[t].
-static open_status ncf_batch_grad(open_ctx *ctx, const NcfLayout &L, int n, const float *R, const float *P,
-                                  const int64_t *apps, int G, NcfTrainBufs &b, float *loss_steps) {
+// no application is in a batch yet; the step state starts over
+static open_status ncf_train_begin(open_ctx *ctx, NcfTrainBufs &b, int64_t m_off) {
+  OPEN_LAUNCH(ctx, "fill", k_fill_i32, dim3(64), dim3(256), 0, (int *)b.mark, 2 * m_off, 0);
+  return dense_train_state_reset(ctx, b.st);
+}
+
+// Loss and gradient of one batch of G applications (apps on the device, from the cursor's batch
+// with use_cursor): the Adam step with lr > 0, the gradient in b.g otherwise; the loss to b.loss
+// and, when given, to loss_steps[t].
+static open_status ncf_step(open_ctx *ctx, const NcfLayout &L, int64_t m_off, int n, const float *R, float *P,
+                            const int64_t *apps, int use_cursor, int G, NcfTrainBufs &b, float lr,
+                            float *loss_steps) {
   const int64_t B = (int64_t)G * n;
-  const int D2 = 2 * kNcfD, H = kNcfH;
-  open_status st;
-  int64_t blocks = (B * D2 + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  OPEN_LAUNCH(ctx, "ncf_gather", k_ncf_gather, dim3((unsigned)blocks), dim3(256), 0, B, n, apps, P + L.E, P + L.S,
-              b.X);
-  // forward: Z1 = X W1^T + b1, H1 = SELU(Z1); Z2 = H1 W2^T + b2, H2 = SELU(Z2); y = H2 w3 + b3
-  if ((st = dense_gemm(ctx, "ncf_gemm_l1", EPI_BIAS_SELU, (int)B, H, D2, b.X, D2, 1, P + L.W1, D2, 1, b.H1, H,
-                       P + L.b1, b.Z1, H)))
-    return st;
-  if ((st = dense_gemm(ctx, "ncf_gemm_l2", EPI_BIAS_SELU, (int)B, H, H, b.H1, H, 1, P + L.W2, H, 1, b.H2, H, P + L.b2,
-                       b.Z2, H)))
-    return st;
-  if ((st = dense_gemm(ctx, "ncf_gemm_out", EPI_BIAS, (int)B, 1, H, b.H2, H, 1, P + L.w3, H, 1, b.y, 1, P + L.b3)))
-    return st;
-  OPEN_LAUNCH(ctx, "ncf_loss", k_ncf_loss, dim3(kNcfLossBlocks), dim3(256), 0, B, n, b.y, apps, R, b.dy, b.lpart);
-  if ((st = dense_loss_final(ctx, b.lpart, kNcfLossBlocks, B, b.loss, nullptr, b.st, loss_steps))) return st;
-  // backward
-  float *g = b.g;
-  if ((st = dense_wgrad(ctx, "ncf_wgrad_out", 1, H, B, b.dy, b.H2, b.part, g + L.w3))) return st;  // w3, b3
-  // dZ2 = (dy w3^T) * SELU'(Z2)
-  if ((st = dense_gemm(ctx, "ncf_gemm_dz2", EPI_SELU_GRAD, (int)B, H, 1, b.dy, 1, 1, P + L.w3, 1, 1, b.dZ2, H, nullptr,
-                       b.Z2, H)))
-    return st;
-  if ((st = dense_wgrad(ctx, "ncf_wgrad_l2", H, H, B, b.dZ2, b.H1, b.part, g + L.W2))) return st;  // W2, b2
-  // dZ1 = (dZ2 W2) * SELU'(Z1)
-  if ((st = dense_gemm(ctx, "ncf_gemm_dz1", EPI_SELU_GRAD, (int)B, H, H, b.dZ2, H, 1, P + L.W2, 1, H, b.dZ1, H, nullptr,
-                       b.Z1, H)))
-    return st;
-  if ((st = dense_wgrad(ctx, "ncf_wgrad_l1", H, D2, B, b.dZ1, b.X, b.part, g + L.W1))) return st;  // W1, b1
-  // dX = dZ1 W1, then the embedding gradients
-  if ((st = dense_gemm(ctx, "ncf_gemm_dx", EPI_STORE, (int)B, D2, H, b.dZ1, H, 1, P + L.W1, 1, D2, b.dX, D2)))
-    return st;
-  const int64_t nE = L.S - L.E;
-  OPEN_LAUNCH(ctx, "fill", k_fill_i32, dim3(256), dim3(256), 0, (int *)(g + L.E), nE, 0);
-  const int64_t th = ((int64_t)G + n) * kNcfD;
-  OPEN_LAUNCH(ctx, "ncf_emb_grad", k_ncf_emb_grad, dim3((unsigned)((th + 255) / 256)), dim3(256), 0, G, n, apps, b.dX,
-              g + L.E, g + L.S);
-  return OPEN_OK;
+  NcfBatch k = {};
+  k.B = B;
+  k.G = G;
+  k.n = n;
+  k.apps = apps;
+  k.use_cursor = use_cursor;
+  k.E = P + L.E;
+  k.S = P + L.S;
+  k.W1 = P + L.W1;
+  k.b1 = P + L.b1;
+  k.W2 = P + L.W2;
+  k.b2 = P + L.b2;
+  k.w3 = P + L.w3;
+  k.b3 = P + L.b3;
+  k.R = R;
+  k.X = b.X;
+  k.h1 = b.h1;
+  k.h2 = b.h2;
+  k.d1p = b.d1p;
+  k.d2p = b.d2p;
+  k.dyp = b.dyp;
+  k.d1 = b.d1;
+  k.d2 = b.d2;
+  k.dy = b.dy;
+  k.dX = b.dX;
+  k.lpart = b.lpart;
+  k.apps_out = b.apps;
+  k.mark = b.mark;
+  k.st = b.st;
+  // rows per block: 16 where blocks of 32 would not cover the compute units
+  const int rows = B <= 16 * (int64_t)ctx->num_cu ? 16 : 32;
+  const unsigned blocks = (unsigned)(pad_rows(B) / rows);
+  if (rows == 16) {
+    OPEN_LAUNCH(ctx, "ncf_fwd_bwd", k_ncf_fwd_bwd<16>, dim3(blocks), dim3(128), 0, k);
+  } else {
+    OPEN_LAUNCH(ctx, "ncf_fwd_bwd", k_ncf_fwd_bwd<32>, dim3(blocks), dim3(128), 0, k);
+  }
+  WgradStep w = {};
+  w.l[0] = {b.d1p, b.X, b.d1, kNcfH, 2 * kNcfD, L.W1};
+  w.l[1] = {b.d2p, b.h1, b.d2, kNcfH, kNcfH, L.W2};
+  w.l[2] = {b.dyp, b.h2, b.dy, 1, kNcfH, L.w3};
+  w.emb.G = G;
+  w.emb.n = n;
+  w.emb.m = m_off;
+  w.emb.dX = b.dX;
+  w.emb.apps = b.apps;
+  w.emb.mark = b.mark;
+  w.emb.e = L.E;
+  w.emb.s = L.S;
+  w.B = B;
+  w.w = P;
+  w.g = b.g;
+  w.m = b.am;
+  w.v = b.av;
+  w.lr = lr;
+  w.st = b.st;
+  w.lpart = b.lpart;
+  w.nlpart = (int)blocks;
+  w.ltotal = B;
+  w.loss_d = b.loss;
+  w.loss_steps = loss_steps;
+  return wgrad_step(ctx, "ncf_wgrad_adam", w, lr > 0.f);
 }
 
 constexpr int64_t kNcfMaxBatch = int64_t(1) << 20;  // batch entries (applications x settings)
@@ -430,12 +588,12 @@ extern "C" open_status open_ncf_loss_grad(open_ctx *ctx, int64_t m_off, int32_t 
   OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
   const NcfLayout L(m_off, n);
   NcfTrainBufs b;
-  if (!b.alloc((int64_t)G * n, L.total)) {
+  if (!b.alloc(m_off, G, n, L.total, false)) {
     b.release();
     return fail(ctx, OPEN_E_NOMEM, "NCF training buffers");
   }
-  st = dense_train_state_reset(ctx, b.st);
-  if (!st) st = ncf_batch_grad(ctx, L, n, R, params, apps, G, b, nullptr);
+  st = ncf_train_begin(ctx, b, m_off);
+  if (!st) st = ncf_step(ctx, L, m_off, n, R, const_cast<float *>(params), apps, 0, G, b, 0.f, nullptr);
   double *h = nullptr;
   if (!st) st = pinned_get(ctx, 64, (void **)&h);
   if (!st && (hipMemcpyAsync(grads_host, b.g, sizeof(float) * L.total, hipMemcpyDeviceToHost, ctx->stream) ||
@@ -461,27 +619,23 @@ extern "C" open_status open_ncf_train(open_ctx *ctx, int64_t m_off, int32_t n, i
   const int G = apps_per_batch;
   const int64_t spe = m_off / G, total = spe * epochs;
   NcfTrainBufs b;
-  int64_t *perm = nullptr, *rows = nullptr;
+  int64_t *perm = nullptr;
   float *losses = nullptr;
-  if (!b.alloc((int64_t)G * n, L.total) || hipMalloc(&perm, sizeof(int64_t) * m_off) ||
-      hipMalloc(&rows, sizeof(int64_t) * G) || hipMalloc(&losses, sizeof(float) * total)) {
+  if (!b.alloc(m_off, G, n, L.total, true) || hipMalloc(&perm, sizeof(int64_t) * m_off) ||
+      hipMalloc(&losses, sizeof(float) * total)) {
     (void)hipGetLastError();
     b.release();
     (void)hipFree(perm);
-    (void)hipFree(rows);
     (void)hipFree(losses);
     return fail(ctx, OPEN_E_NOMEM, "NCF training buffers");
   }
   OPEN_LAUNCH(ctx, "fill", k_fill_i32, dim3(256), dim3(256), 0, (int *)b.am, L.total, 0);
   OPEN_LAUNCH(ctx, "fill", k_fill_i32, dim3(256), dim3(256), 0, (int *)b.av, L.total, 0);
-  st = dense_train_state_reset(ctx, b.st);
+  st = ncf_train_begin(ctx, b, m_off);
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   auto one_step = [&]() -> open_status {
-    open_status e;
-    if ((e = dense_rows_of_step(ctx, perm, G, b.st, rows))) return e;
-    if ((e = ncf_batch_grad(ctx, L, n, R, params, rows, G, b, losses))) return e;
-    return dense_adam_step(ctx, L.total, params, b.g, b.am, b.av, lr, b.st);
+    return ncf_step(ctx, L, m_off, n, R, params, perm, 1, G, b, lr, losses);
   };
   for (int32_t e = 0; e < epochs && st == OPEN_OK; ++e) {
     if ((st = dense_shuffle(ctx, m_off, seed, e, perm, b.st))) break;
@@ -523,7 +677,6 @@ extern "C" open_status open_ncf_train(open_ctx *ctx, int64_t m_off, int32_t n, i
   (void)hipStreamSynchronize(ctx->stream);
   b.release();
   (void)hipFree(perm);
-  (void)hipFree(rows);
   (void)hipFree(losses);
   return st;
 }

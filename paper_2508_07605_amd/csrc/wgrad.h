@@ -25,8 +25,21 @@ struct WgradLayer {
   int S, kc, nt, blocks;
 };
 
+// Embedding gradients of the NCF model, whose batch rows pair each of G applications with each of
+// n settings: dX (batch x 64) holds the gradients of [e ; s], summed per application over the
+// settings and per setting over the applications, each in order.
+struct WgradEmb {
+  int G = 0, n = 0;          // G = 0: no embeddings
+  int64_t m = 0;             // applications of the model
+  const float *dX = nullptr;
+  const int64_t *apps = nullptr;  // the batch's applications
+  const int64_t *mark = nullptr;  // step tag of each application's last batch
+  int64_t e = 0, s = 0;      // offsets of E (m x 32) and S (n x 32) in the parameter vector
+};
+
 struct WgradStep {
   WgradLayer l[3];
+  WgradEmb emb;
   int64_t B;                 // batch rows
   float *w, *g, *m, *v;      // parameters, gradient, Adam moments
   float lr;

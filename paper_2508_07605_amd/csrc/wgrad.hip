@@ -221,6 +221,67 @@ __device__ __forceinline__ void bias_sums(const WgradStep &p, const WgradLayer &
   }
 }
 
+// ---- embeddings
+constexpr int kEmbD = 32;
+
+// gE of application g of the batch: the rows of dX through LDS, summed in setting order by
+// one thread per dimension
+template <bool ADAM>
+__device__ __forceinline__ void app_embedding(const WgradStep &p, int g, float *buf) {
+  const WgradEmb &e = p.emb;
+  constexpr int RS = kWgLdsFloats / kEmbD;  // settings a round
+  float x = 0.f;
+  for (int j0 = 0; j0 < e.n; j0 += RS) {
+    const int left = e.n - j0 < RS ? e.n - j0 : RS;
+    if (j0) __syncthreads();
+    const float *src = e.dX + ((int64_t)g * e.n + j0) * 2 * kEmbD;
+    for (int t = threadIdx.x; t < left * (kEmbD / 4); t += kWgThreads)
+      reinterpret_cast<f4 *>(buf)[t] =
+          *reinterpret_cast<const f4 *>(src + (t / (kEmbD / 4)) * 2 * kEmbD + 4 * (t % (kEmbD / 4)));
+    __syncthreads();
+    if (threadIdx.x < kEmbD) {
+#pragma unroll 16
+      for (int j = 0; j < left; ++j) x += buf[j * kEmbD + threadIdx.x];
+    }
+  }
+  if (threadIdx.x < kEmbD) {
+    const int64_t i = e.e + e.apps[g] * kEmbD + threadIdx.x;
+    if constexpr (ADAM)
+      adam_update(p, i, x, p.st->c1, p.st->c2);
+    else
+      p.g[i] = x;
+  }
+}
+
+// gS of 1024 elements (setting, dimension): applications in order
+template <bool ADAM>
+__device__ __forceinline__ void setting_embeddings(const WgradStep &p, int q) {
+  const WgradEmb &e = p.emb;
+  const int64_t t = (int64_t)q * kWgThreads + threadIdx.x;
+  if (t >= (int64_t)e.n * kEmbD) return;
+  const float *src = e.dX + t / kEmbD * 2 * kEmbD + kEmbD + t % kEmbD;
+  float x = 0.f;
+#pragma unroll 8
+  for (int g = 0; g < e.G; ++g) x += src[(int64_t)g * e.n * 2 * kEmbD];
+  if constexpr (ADAM)
+    adam_update(p, e.s + t, x, p.st->c1, p.st->c2);
+  else
+    p.g[e.s + t] = x;
+}
+
+// 1024 elements of E: the applications outside the batch have zero gradient (Adam still moves
+// them by their moments)
+template <bool ADAM>
+__device__ __forceinline__ void other_embeddings(const WgradStep &p, int q) {
+  const WgradEmb &e = p.emb;
+  const int64_t t = (int64_t)q * kWgThreads + threadIdx.x;
+  if (t >= e.m * kEmbD || e.mark[t / kEmbD] == p.st->tag) return;
+  if constexpr (ADAM)
+    adam_update(p, e.e + t, 0.f, p.st->c1, p.st->c2);
+  else
+    p.g[e.e + t] = 0.f;
+}
+
 // the batch loss, and the step state's counters (read by no other block of this launch)
 template <bool ADAM>
 __device__ __forceinline__ void loss_and_state(const WgradStep &p, double *red) {
@@ -247,8 +308,18 @@ __device__ __forceinline__ void loss_and_state(const WgradStep &p, double *red) 
 template <bool ADAM>
 __global__ __launch_bounds__(kWgThreads) void k_wgrad_step(WgradStep p) {
   __shared__ __attribute__((aligned(16))) float buf[kWgLdsFloats];
-  // the bias sums and the loss first: they are the longest chains
+  // the longest chains first: the embedding and bias sums, the loss
   int q = blockIdx.x;
+  if (p.emb.G > 0) {
+    const int ns = (int)(((int64_t)p.emb.n * kEmbD + kWgThreads - 1) / kWgThreads);
+    const int no = (int)((p.emb.m * kEmbD + kWgThreads - 1) / kWgThreads);
+    if (q < p.emb.G) return app_embedding<ADAM>(p, q, buf);
+    q -= p.emb.G;
+    if (q < ns) return setting_embeddings<ADAM>(p, q);
+    q -= ns;
+    if (q < no) return other_embeddings<ADAM>(p, q);
+    q -= no;
+  }
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const int nb = (p.l[i].M + kWgBias - 1) / kWgBias;
@@ -270,6 +341,9 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad_step(WgradStep p) {
 
 open_status wgrad_step(open_ctx *ctx, const char *name, WgradStep p, bool adam) {
   unsigned blocks = 1;
+  if (p.emb.G > 0)
+    blocks += (unsigned)(p.emb.G + ((int64_t)p.emb.n * kEmbD + kWgThreads - 1) / kWgThreads +
+                         (p.emb.m * kEmbD + kWgThreads - 1) / kWgThreads);
   for (WgradLayer &l : p.l) {
     l.S = wgrad_slices(p.B, l.M, l.N, &l.kc);
     wgrad_shape(l);

@@ -1,4 +1,4 @@
-"""The two-launch training step at the edges of its tiles and rules: batches around a tile of 16
+"""The two-launch training steps at the edges of its tiles and rules: batches around a tile of 16
 or 32 rows and around the switch between them, batch slices with a remainder, few slices with
 several output tiles per block (wide inputs, large batches), many short slices (narrow output
 layers), inputs that are no multiple of a tile, rows of more than 64 entries.
@@ -74,3 +74,59 @@ def test_gradients_at_tile_edges(ctx, B, n, k, longest):
     assert np.array_equal(g1, g2)
     net.close()
     fresh.close()
+
+
+
+def bf16(x):
+    return torch.from_numpy(np.ascontiguousarray(x, np.float32)).to(torch.bfloat16).double().numpy()
+
+
+def ncf_rounded_gradients(E, S, p, apps, R):
+    """The batch's loss and gradients in float64 with every product's operands rounded to
+    bfloat16 where the kernels round them.  (Against unrounded products a gradient of a small
+    batch is off by the share of pre-activations that the rounding moves across SELU's kink.)"""
+    from oracle.ncf import selu, selu_grad
+    G, n = len(apps), S.shape[0]
+    X = bf16(np.concatenate([np.repeat(E[apps], n, 0), np.tile(S, (G, 1))], 1))
+    W1, W2, w3 = bf16(p["W1"]), bf16(p["W2"]), bf16(p["w3"])
+    z1 = X @ W1.T + p["b1"]
+    h1 = bf16(selu(z1))
+    z2 = h1 @ W2.T + p["b2"]
+    h2 = bf16(selu(z2))
+    d = h2 @ w3 + p["b3"] - R[apps].reshape(-1).astype(np.float64)
+    dy = 2.0 * d / d.size
+    d2 = bf16(dy)[:, None] * w3 * selu_grad(z2)
+    d1 = (bf16(d2) @ W2) * selu_grad(z1)
+    dX = (bf16(d1) @ W1).reshape(G, n, 64)
+    gE = np.zeros(E.shape)
+    gE[apps] = dX[:, :, :32].sum(1)
+    g = dict(E=gE, S=dX[:, :, 32:].sum(0), W1=bf16(d1).T @ X, b1=d1.sum(0), W2=bf16(d2).T @ h1, b2=d2.sum(0),
+             w3=bf16(dy) @ h2, b3=np.array([dy.sum()]))
+    return float(np.mean(d * d)), g
+
+
+# NCF: batches of G applications x n settings around a tile of 16 or 32 rows and the switch
+# between them, more settings than one pass of the embedding sums holds (1024), one
+# application.  Tolerance: float32 accumulation moves a value by about 64 2^-24 relative, which
+# carries about one value in a thousand across a bfloat16 rounding boundary (2^-8 relative):
+# 1e-4 in a tensor's Frobenius norm; 1e-3 leaves room for small tensors.
+@pytest.mark.parametrize("m_off,n,G", [(1, 1, 1), (5, 33, 3), (40, 31, 1), (16, 256, 16), (9, 480, 9), (3, 1025, 2),
+                                       (2, 2100, 2)])
+def test_ncf_gradients_at_tile_edges(ctx, m_off, n, G):
+    r = np.random.default_rng([m_off, n, G])
+    R = (3.0 + r.random((m_off, n))).astype(np.float32)
+    p = synth.ncf_params(3, n, seed=2)
+    S = p.pop("S")
+    E = (0.3 * r.standard_normal((m_off, 32))).astype(np.float32)
+    flat = dev(native.ncf_pack(E, S, p))
+    apps = r.permutation(m_off)[:G].astype(np.int64)
+    loss, g = native.open_ncf_loss_grad(ctx, dev(R), flat, dev(apps))
+    Lr, gr = ncf_rounded_gradients(E, S, p, apps, R)
+    gE, gS, gnet = native.ncf_unpack(g, m_off, n)
+    errs = {"E": fro(gE, gr["E"]), "S": fro(gS, gr["S"])}
+    errs.update({k: fro(v, gr[k]) for k, v in gnet.items()})
+    print("NCF %d x %d, batch %d: loss %.6g vs %.6g, gradients %s"
+          % (m_off, n, G, loss, Lr, {k: "%.1e" % v for k, v in errs.items()}))
+    assert abs(loss - Lr) <= 1e-3 * Lr
+    assert max(errs.values()) <= 1e-3
+    assert not gE[np.setdiff1d(np.arange(m_off), apps)].any()
