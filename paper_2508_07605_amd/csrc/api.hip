@@ -251,21 +251,25 @@ open_status open_sync(open_ctx *ctx) {
   return OPEN_OK;
 }
 
-// Shared front half of open_foldin and open_autotune: validation and bucketing.  Rows can
-// reach the split-K length only when F has at least kSplitMin rows (column indices are
-// unique within a row); then the total entry count is read back to size its work.
-static open_status foldin_prepare(open_ctx *ctx, const float *F, int32_t n, int32_t k, int64_t m,
-                                  const int64_t *row_ptr, const int32_t *col, const float *val, float lambda,
-                                  float *U_out, RowRef **list, int64_t **cls, int64_t *nnz_split) {
-  *nnz_split = -1;
+static open_status foldin_check(open_ctx *ctx, const float *F, int32_t n, int32_t k, int64_t m,
+                                const int64_t *row_ptr, const int32_t *col, const float *val, float lambda,
+                                float *U_out) {
   if (!rank_ok(k)) return fail(ctx, OPEN_E_UNSUPPORTED, "rank must be 8, 16, 32 or 64");
   if (n <= 0 || !F) return fail(ctx, OPEN_E_INVALID, "factor matrix must be non-empty");
   if (!(lambda >= 0.0f) || !isfinite(lambda)) return fail(ctx, OPEN_E_INVALID, "lambda must be finite and >= 0");
   open_status st = check_csr(ctx, m, row_ptr, col, val);
   if (st) return st;
   if (m > 0 && !U_out) return fail(ctx, OPEN_E_INVALID, "output must not be NULL");
-  if (m == 0) return OPEN_OK;
-  OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
+  return OPEN_OK;
+}
+
+// Bucketing of open_foldin and open_autotune.  Rows can reach the split-K length only when F has
+// at least kSplitMin rows (column indices are unique within a row); then the total entry count is
+// read back to size its work.
+static open_status foldin_prepare(open_ctx *ctx, int32_t n, int32_t k, int64_t m, const int64_t *row_ptr,
+                                  RowRef **list, int64_t **cls, int64_t *nnz_split) {
+  *nnz_split = -1;
+  open_status st;
   if (n >= kSplitMin) {
     int64_t *h;
     if ((st = pinned_get(ctx, sizeof(int64_t), (void **)&h))) return st;
@@ -283,8 +287,12 @@ open_status open_foldin(open_ctx *ctx, const float *F, int32_t n, int32_t k, int
   if (!ctx) return OPEN_E_INVALID;
   RowRef *list = nullptr;
   int64_t *cls = nullptr, nnz = -1;
-  open_status st = foldin_prepare(ctx, F, n, k, m, row_ptr, col, val, lambda, U_out, &list, &cls, &nnz);
+  open_status st = foldin_check(ctx, F, n, k, m, row_ptr, col, val, lambda, U_out);
   if (st || m == 0) return st;
+  OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
+  if (small_batch(ctx, n, k, m))
+    return small_batch_launch(ctx, F, n, k, row_ptr, col, val, nullptr, lambda, weighted, U_out, row_status, m);
+  if ((st = foldin_prepare(ctx, n, k, m, row_ptr, &list, &cls, &nnz))) return st;
   if ((st = rowsolve_launch(ctx, F, n, k, row_ptr, col, val, lambda, weighted, list, cls, U_out, row_status, m)))
     return st;
   if (nnz >= 0) return splitk_launch(ctx, F, n, k, col, val, lambda, weighted, list, cls, U_out, row_status, m, nnz);
@@ -360,6 +368,8 @@ open_status open_foldin_noalloc(open_ctx *ctx, const float *F, int32_t n, int32_
     return fail(ctx, OPEN_E_INVALID, "row count exceeds the scratch layout");
   if (m == 0) return OPEN_OK;
   OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
+  if (small_batch(ctx, n, k, m))
+    return small_batch_launch(ctx, F, n, k, row_ptr, col, val, nullptr, lambda, weighted, U_out, row_status, m);
   unsigned char *base = (unsigned char *)ctx->scratch;
   RowRef *list = (RowRef *)(base + kScrList);
   int32_t *hist = (int32_t *)(base + kScrHist);
@@ -409,8 +419,10 @@ open_status open_autotune(open_ctx *ctx, const float *F, int32_t n, int32_t k, i
   if (reps < 1) return fail(ctx, OPEN_E_INVALID, "reps must be >= 1");
   RowRef *list = nullptr;
   int64_t *cls = nullptr, nnz = -1;
-  open_status st = foldin_prepare(ctx, F, n, k, m, row_ptr, col, val, lambda, U_out, &list, &cls, &nnz);
+  open_status st = foldin_check(ctx, F, n, k, m, row_ptr, col, val, lambda, U_out);
   if (st || m == 0) return st;
+  OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
+  if ((st = foldin_prepare(ctx, n, k, m, row_ptr, &list, &cls, &nnz))) return st;
   if ((st = rowsolve_autotune(ctx, F, n, k, row_ptr, col, val, lambda, weighted, list, cls, U_out, row_status, m,
                               reps, ms_out)))
     return st;

@@ -224,6 +224,8 @@ open_status bucket_rows(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int k,
 open_status bucket_rows_into(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int k, int32_t *hist, RowRef *list,
                              int64_t *cls, int64_t split_min, const uint8_t *mask = nullptr);
 int64_t bucket_hist_ints(int64_t m);
+// rows per block of the one-launch fold-in of small batches
+constexpr int kSmallRows = 128;
 // rows per block of the bucketing kernels (the per-block class counts are kNumClasses ints)
 constexpr int kBucketRowsPerBlock = 2048;
 // Column view on the device (stable counting sort); entries with a column outside [0, n) are dropped.
@@ -233,6 +235,12 @@ open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, const int64_t *row_p
 open_status rowsolve_launch(open_ctx *ctx, const float *F, int n, int k, const int64_t *row_ptr, const int32_t *col,
                             const float *val, float lambda, int weighted, const RowRef *list, const int64_t *cls,
                             float *X, int32_t *status, int64_t m);
+// Whether a fold-in of m rows goes through the one-launch path (bucketing included, no
+// workspace), and that launch; mask (nullable): rows with mask[i] == 0 are left alone.
+bool small_batch(const open_ctx *ctx, int n, int k, int64_t m);
+open_status small_batch_launch(open_ctx *ctx, const float *F, int n, int k, const int64_t *row_ptr,
+                               const int32_t *col, const float *val, const uint8_t *mask, float lambda, int weighted,
+                               float *X, int32_t *status, int64_t m);
 // Split-K solve of the rows of class kSplitClass (F has nF rows, nnz bounds the work).
 open_status splitk_launch(open_ctx *ctx, const float *F, int nF, int k, const int32_t *idx, const float *val,
                           float lambda, int weighted, const RowRef *list, const int64_t *cls, float *X,

@@ -899,9 +899,14 @@ open_status open_mlp_foldin(open_mlp *p, const float *F, int64_t m, const int64_
   // re-solve the flagged rows with the ridge fold-in (only they are bucketed)
   RowRef *list;
   int64_t *cls;
-  if ((st = bucket_rows(ctx, m, row_ptr, p->k, &list, &cls, INT64_MAX, f))) return st;
-  if ((st = rowsolve_launch(ctx, F, p->n, p->k, row_ptr, col, val, lambda, weighted, list, cls, U_out, nullptr, m)))
+  if (small_batch(ctx, p->n, p->k, m)) {
+    if ((st = small_batch_launch(ctx, F, p->n, p->k, row_ptr, col, val, f, lambda, weighted, U_out, nullptr, m)))
+      return st;
+  } else if ((st = bucket_rows(ctx, m, row_ptr, p->k, &list, &cls, INT64_MAX, f)) ||
+             (st = rowsolve_launch(ctx, F, p->n, p->k, row_ptr, col, val, lambda, weighted, list, cls, U_out, nullptr,
+                                   m))) {
     return st;
+  }
   if (n_fallback) {
     OPEN_LAUNCH(ctx, "mlp_count_fallback", k_count_u8, dim3(256), dim3(256), 0, m, f, p->cnt);
     int64_t *h;

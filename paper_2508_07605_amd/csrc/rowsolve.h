@@ -498,7 +498,9 @@ __device__ __forceinline__ void solve_group(const FRows<K, LDSF> &Fr, int n, con
     sfor<0, M>([&](auto m) { xv[m] = 0.f; });
     sfor_down<0, D>([&](auto Pp) {
       constexpr int p = decltype(Pp)::value, mp = p / 4, pp = p % 4;
-      float part = st[mp][p] * xv[mp];
+      // an fma also for the first term: a product would be contracted into the quad sum when it is
+      // the only one, and the bits of x would depend on the padded dimension
+      float part = __builtin_fmaf(st[mp][p], xv[mp], 0.f);
       sfor<mp + 1, M>([&](auto Ii) {
         constexpr int I = decltype(Ii)::value;
         part = __builtin_fmaf(st[I][p], xv[I], part);
@@ -573,6 +575,25 @@ __host__ __device__ constexpr int factor_lds_bytes() { return ((kFactorLdsRows +
 template <int K, int P, int D>
 __host__ __device__ constexpr int wave_bytes() { return wave_lds_floats(P, D) * 4; }
 
+// Stage the factor matrix in LDS at `fl`: [zero row][n rows at pitch K + 4][tail], by direct
+// global -> LDS copies, one 16-byte slot per lane and 1 KB per wave instruction; a row's pad slot
+// copies its chunk 0, and the lanes of the last instruction past the end copy the last chunk into
+// the tail.  Returns row 0; the copies have landed after s_waitcnt and a barrier.
+template <int K, int W>
+__device__ __forceinline__ const float *stage_factors(const float *__restrict__ F, int n, float *fl) {
+  constexpr int PS = K + 4, CH = K / 4, SL = CH + 1;
+  const int slots = n * SL;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int base = w * 64; base < slots; base += W * 64) {
+    const int e = base + lane < slots ? base + lane : slots - 2;  // slots - 2: last data chunk
+    const int jj = e / SL, cc = e % SL;
+    __builtin_amdgcn_global_load_lds(F + (int64_t)jj * K + 4 * (cc < CH ? cc : 0),
+                                     (__attribute__((address_space(3))) void *)(fl + PS + 4 * base), 16, 0, 0);
+  }
+  if (threadIdx.x < PS) fl[threadIdx.x] = 0.f;
+  return fl + PS;
+}
+
 // Persistent kernel over the rows of classes c_lo..c_hi (contiguous in the bucketed list),
 // all solved at padded dimension D (dual) or k (primal).
 template <int K, int P, int D, bool DUAL, bool LDSF, int W, int OCC, bool BLK>
@@ -594,23 +615,9 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   if ((int64_t)blockIdx.x * W * SYS >= count) return;  // block has no work (uniform)
   FRows<K, LDSF> Fr;
   if constexpr (LDSF) {
-    // [zero row][n rows at pitch PS][tail]: direct global -> LDS copies, one 16-byte slot
-    // per lane and 1 KB per wave instruction; a row's pad slot copies its chunk 0, and the
-    // lanes of the last instruction past the end copy the last chunk into the tail
-    constexpr int PS = K + 4, CH = K / 4, SL = CH + 1;
-    float *fl = lds_all + W * WL;
-    const int slots = n * SL;
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int base = w * 64; base < slots; base += W * 64) {
-      const int e = base + lane < slots ? base + lane : slots - 2;  // slots - 2: last data chunk
-      const int jj = e / SL, cc = e % SL;
-      __builtin_amdgcn_global_load_lds(F + (int64_t)jj * K + 4 * (cc < CH ? cc : 0),
-                                       (__attribute__((address_space(3))) void *)(fl + PS + 4 * base), 16, 0, 0);
-    }
-    if (threadIdx.x < PS) fl[threadIdx.x] = 0.f;
+    Fr.lds = stage_factors<K, W>(F, n, lds_all + W * WL);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    Fr.lds = fl + PS;
   } else {
     Fr.rs = make_rsrc(F, (uint64_t)n * K * sizeof(float));
   }
@@ -677,20 +684,9 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   if ((int64_t)blockIdx.x * W >= total) return;  // block has no work (uniform)
   FRows<K, LDSF> Fr;
   if constexpr (LDSF) {
-    constexpr int PS = K + 4, CH = K / 4, SL = CH + 1;
-    float *fl = lds_all + W * WL;
-    const int slots = n * SL;
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int base = w * 64; base < slots; base += W * 64) {
-      const int e = base + lane < slots ? base + lane : slots - 2;  // slots - 2: last data chunk
-      const int jj = e / SL, cc2 = e % SL;
-      __builtin_amdgcn_global_load_lds(F + (int64_t)jj * K + 4 * (cc2 < CH ? cc2 : 0),
-                                       (__attribute__((address_space(3))) void *)(fl + PS + 4 * base), 16, 0, 0);
-    }
-    if (threadIdx.x < PS) fl[threadIdx.x] = 0.f;
+    Fr.lds = stage_factors<K, W>(F, n, lds_all + W * WL);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    Fr.lds = fl + PS;
   } else {
     Fr.rs = make_rsrc(F, (uint64_t)n * K * sizeof(float));
   }
@@ -825,6 +821,15 @@ const ClassGroup *class_groups(int k, int *count);
 // The rank-32 pass in three merged launches, selected by the launch-mode entry of the rank's
 // tuning table (0: merged, 1: one launch per class group).
 open_status rowsolve_k32_merged(OPEN_TIER_ARGS);
+// Batches of few rows in one launch, bucketing included (foldin_small.h); mask (nullable): rows
+// with mask[i] == 0 are left alone.
+#define OPEN_SMALL_ARGS                                                                                          \
+  open_ctx *ctx, const float *F, int n, const int64_t *ptr, const int32_t *idx, const float *val,                 \
+      const uint8_t *mask, float lambda, int weighted, float *X, int32_t *status, int64_t m
+#define OPEN_SMALL_PASS F, n, ptr, idx, val, mask, lambda, weighted, X, status, m
+open_status foldin_small_k8(OPEN_SMALL_ARGS);
+open_status foldin_small_k16(OPEN_SMALL_ARGS);
+open_status foldin_small_k32(OPEN_SMALL_ARGS);
 OPEN_GROUP(g_k8_d4);
 OPEN_GROUP(g_k8_d8);
 OPEN_GROUP(g_k8_primal);

@@ -62,6 +62,34 @@ static int launch_mode(const open_ctx *ctx, int k, const ClassGroup *g, int ng) 
   return (k == 32 && ng > 0 && !g[ng - 1].fn) ? ctx->tune[rank_index(k)][ng - 1] : 1;
 }
 
+// A small batch is bound by launches and by one group's latency, not by throughput: one launch
+// with the bucketing in LDS replaces the two bucketing launches and one per class group.
+// Beyond one block of kSmallRows rows per compute unit the class-major list pays: it fills every
+// group and spreads the costly classes over the chip, where a block holds whatever its rows
+// are.  One launch against the bucketed path, us (counts 4..24 / long-tailed, 480 settings; rank 8: 120):
+//     rows    rank 8          rank 16         rank 32
+//    32,700   10/50  24/81    12/87 103/279   17/43 161/274
+//    65,000   16/56  47/90    23/95 203/283   32/52 317/276
+//   130,000   31/63  92/95    46/97 399/285   61/64 624/317
+// so ranks 8 and 16 take it up to two blocks per unit, rank 32 up to one.  A tuned rank keeps the
+// kernels that its table names, and rows of split-K length their own path.
+bool small_batch(const open_ctx *ctx, int n, int k, int64_t m) {
+  if (k == 64 || n >= kSplitMin || m > (int64_t)kSmallRows * (k == 32 ? 1 : 2) * ctx->num_cu) return false;
+  for (int8_t v : ctx->tune[rank_index(k)])
+    if (v) return false;
+  return true;
+}
+
+open_status small_batch_launch(open_ctx *ctx, const float *F, int n, int k, const int64_t *ptr, const int32_t *idx,
+                               const float *val, const uint8_t *mask, float lambda, int weighted, float *X,
+                               int32_t *status, int64_t m) {
+  switch (k) {
+    case 8: return foldin_small_k8(ctx, OPEN_SMALL_PASS);
+    case 16: return foldin_small_k16(ctx, OPEN_SMALL_PASS);
+    default: return foldin_small_k32(ctx, OPEN_SMALL_PASS);
+  }
+}
+
 open_status rowsolve_launch(open_ctx *ctx, const float *F, int n, int k, const int64_t *ptr, const int32_t *idx,
                             const float *val, float lambda, int weighted, const RowRef *list, const int64_t *cls,
                             float *X, int32_t *status, int64_t m) {
