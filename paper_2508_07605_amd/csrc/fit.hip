@@ -1,13 +1,5 @@
 // ALS-WR fit support: column view of the CSR (exact stable counting sort), the objective
 // reduced in float64 in a fixed order, the observed-entry residual, and the sweep driver.
-//
-// Column view.  Rows are cut into chunks of kChunkRows rows; one wavefront owns a chunk.
-//   pass 1  per-chunk column histogram (LDS counters, exact)
-//   scan    exclusive scan of the column-major histogram (column j, then chunk) gives, for
-//           every (j, chunk), the position of the chunk's first entry of column j
-//   pass 2  the wavefront walks its rows in order; the entries of one row have distinct
-//           columns, so its lanes place them without conflicts.  Entries land ordered by
-//           column and, within a column, by row.
 #include <math.h>
 #include <string.h>
 
@@ -15,110 +7,173 @@
 
 namespace openk {
 
-constexpr int kChunkRows = 256;
-constexpr int kCscWaves = 4;  // wavefronts per block
+// Column view on the device: an exact stable counting sort of the entries by column.
+//
+// Rows are cut into chunks of kCscRows; a block owns a chunk and keeps, per column, one bit per
+// row of the chunk that has an entry there.  The rank of an entry among the chunk's entries of
+// its column is then a bit count, so all entries of a chunk are placed at once, ordered by
+// column and, within a column, by row.
+//   count   entries per (chunk, column), chunk-major
+//   scan    per column: exclusive over the chunks of a segment, in place; then over the segments
+//           and the columns (one block), which also gives col_ptr
+//   place   position = segment base + chunk offset + rank
+// Bound by the scattered 4-byte stores of the place kernel (runs of a few entries per column and
+// chunk); consecutive chunks, which write next to each other, are dealt to one XCD's L2.
+// 12.7M entries, 200,003 x 480: count 28, scan 13, place 414 us; with chunks of 256 rows per
+// wavefront that walked its rows one by one (three quarters of the SIMDs busy, one row's loads
+// at a time) 109, 15 and 860.
+constexpr int kCscRows = 128;          // rows of a chunk: two 64-bit masks per column
+constexpr int kCscThreads = 512;
+constexpr int kCscSeg = 64;            // chunks of a scan segment
 constexpr int kMaxCols = 4096;
 
-__global__ __launch_bounds__(kCscWaves * 64) void k_csc_count(int64_t m, int n, const int64_t *__restrict__ ptr,
-                                                              const int32_t *__restrict__ col, int nchunk,
-                                                              int32_t *__restrict__ hist) {
-  extern __shared__ int cnt_s[];  // [kCscWaves][n]
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int *cnt = cnt_s + w * n;
-  const int64_t chunk = (int64_t)blockIdx.x * kCscWaves + w;
-  for (int j = lane; j < n; j += 64) cnt[j] = 0;
+// the chunk of a block: blocks are dealt to the 8 XCDs round-robin, so XCD x walks the x-th
+// eighth of the chunks
+__device__ __forceinline__ int csc_chunk(int nchunk) {
+  const int per = (nchunk + 7) / 8;
+  const int c = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  return (int)(blockIdx.x >> 3) < per && c < nchunk ? c : -1;
+}
+
+// the chunk's row pointers relative to its first entry, and the column masks
+struct CscChunk {
+  int64_t r0, e0;
+  int rows, len;
+};
+__device__ __forceinline__ CscChunk csc_begin(int64_t m, int n, const int64_t *__restrict__ ptr, int chunk,
+                                              int *rp, unsigned long long *mask) {
+  CscChunk c;
+  c.r0 = (int64_t)chunk * kCscRows;
+  c.rows = (int)(m - c.r0 < kCscRows ? m - c.r0 : kCscRows);
+  c.e0 = ptr[c.r0];
+  for (int i = threadIdx.x; i <= kCscRows; i += kCscThreads)
+    rp[i] = (int)(ptr[c.r0 + (i < c.rows ? i : c.rows)] - c.e0);
+  for (int j = threadIdx.x; j < 2 * n; j += kCscThreads) mask[j] = 0ull;
   __syncthreads();
-  if (chunk < nchunk) {
-    const int64_t r0 = chunk * kChunkRows;
-    const int64_t r1 = r0 + kChunkRows < m ? r0 + kChunkRows : m;
-    for (int64_t t = ptr[r0] + lane; t < ptr[r1]; t += 64) {
-      const int j = col[t];
-      if (j >= 0 && j < n) atomicAdd(&cnt[j], 1);
+  c.len = rp[kCscRows];
+  return c;
+}
+// row (of the chunk) of its entry t: the last one that starts at or before t
+__device__ __forceinline__ int csc_row(const int *rp, int t) {
+  int r = 0;
+#pragma unroll
+  for (int s = kCscRows / 2; s > 0; s >>= 1) r += rp[r + s] <= t ? s : 0;
+  return r;
+}
+__device__ __forceinline__ void csc_masks(const CscChunk &c, int n, const int32_t *__restrict__ col, const int *rp,
+                                          unsigned long long *mask) {
+  for (int t = threadIdx.x; t < c.len; t += kCscThreads) {
+    const int j = col[c.e0 + t];
+    if (j < 0 || j >= n) continue;  // rejected by the index check
+    const int r = csc_row(rp, t);
+    atomicOr(&mask[2 * j + (r >> 6)], 1ull << (r & 63));
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kCscThreads) void k_csc_count(int64_t m, int n, const int64_t *__restrict__ ptr,
+                                                           const int32_t *__restrict__ col, int nchunk,
+                                                           int32_t *__restrict__ hist) {
+  extern __shared__ unsigned long long mask_s[];  // [n][2]
+  __shared__ int rp[kCscRows + 1];
+  const int chunk = csc_chunk(nchunk);
+  if (chunk < 0) return;
+  const CscChunk c = csc_begin(m, n, ptr, chunk, rp, mask_s);
+  csc_masks(c, n, col, rp, mask_s);
+  for (int j = threadIdx.x; j < n; j += kCscThreads)
+    hist[(int64_t)chunk * n + j] = __popcll(mask_s[2 * j]) + __popcll(mask_s[2 * j + 1]);
+}
+
+// hist[c][j] -> entries of column j in the chunks of c's segment before c; seg[s][j] = its total
+__global__ __launch_bounds__(256) void k_csc_segments(int n, int nchunk, int32_t *__restrict__ hist,
+                                                      int64_t *__restrict__ seg) {
+  const int j = blockIdx.x * 256 + threadIdx.x, c0 = blockIdx.y * kCscSeg;
+  if (j >= n) return;
+  int run = 0;
+  for (int b = 0; b < kCscSeg; b += 16) {
+    int v[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = c0 + b + e < nchunk ? hist[(int64_t)(c0 + b + e) * n + j] : 0;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      if (c0 + b + e < nchunk) hist[(int64_t)(c0 + b + e) * n + j] = run;
+      run += v[e];
     }
   }
-  __syncthreads();
-  if (chunk < nchunk)
-    for (int j = lane; j < n; j += 64) hist[(int64_t)j * nchunk + chunk] = cnt[j];
+  seg[(int64_t)blockIdx.y * n + j] = run;
 }
 
-__global__ __launch_bounds__(kCscWaves * 64) void k_csc_place(int64_t m, int n, const int64_t *__restrict__ ptr,
-                                                              const int32_t *__restrict__ col,
-                                                              const float *__restrict__ val, int nchunk,
-                                                              const int64_t *__restrict__ base,
-                                                              int32_t *__restrict__ row_idx,
-                                                              float *__restrict__ cval) {
-  extern __shared__ int64_t pos_s[];  // [kCscWaves][n]
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int64_t *pos = pos_s + (int64_t)w * n;
-  const int64_t chunk = (int64_t)blockIdx.x * kCscWaves + w;
-  if (chunk >= nchunk) return;
-  for (int j = lane; j < n; j += 64) pos[j] = base[(int64_t)j * nchunk + chunk];
-  const int64_t r0 = chunk * kChunkRows;
-  const int64_t r1 = r0 + kChunkRows < m ? r0 + kChunkRows : m;
-  for (int64_t i = r0; i < r1; ++i) {
-    for (int64_t t = ptr[i] + lane; t < ptr[i + 1]; t += 64) {
-      const int j = col[t];
-      if (j < 0 || j >= n) continue;  // rejected by the index check
-      const int64_t p = pos[j]++;     // columns are distinct within a row
-      row_idx[p] = (int32_t)i;
-      cval[p] = val[t];
+// seg[s][j] -> position of segment s's first entry of column j; col_ptr.  One block; thread t owns
+// columns t, t + 1024, ...
+__global__ __launch_bounds__(1024) void k_csc_bases(int n, int nseg, int64_t *__restrict__ seg,
+                                                    int64_t *__restrict__ col_ptr) {
+  __shared__ int64_t scan[1024];
+  int64_t before = 0;  // entries of the columns before this round's
+  for (int j0 = 0; j0 < n; j0 += 1024) {
+    const int j = j0 + (int)threadIdx.x;
+    int64_t tot = 0;
+    if (j < n)
+      for (int s = 0; s < nseg; s += 8) {
+        int64_t v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = s + e < nseg ? seg[(int64_t)(s + e) * n + j] : 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) tot += v[e];
+      }
+    scan[threadIdx.x] = tot;
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {
+      const int64_t v = threadIdx.x >= (unsigned)off ? scan[threadIdx.x - off] : 0;
+      __syncthreads();
+      scan[threadIdx.x] += v;
+      __syncthreads();
     }
-  }
-}
-
-// Exclusive scan of int32 counts into int64 offsets, three phases over blocks of 1024.
-__global__ __launch_bounds__(1024) void k_scan_blocks(const int32_t *__restrict__ in, int64_t len,
-                                                      int64_t *__restrict__ out, int64_t *__restrict__ block_sum) {
-  __shared__ int64_t s[1024];
-  const int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-  s[threadIdx.x] = i < len ? in[i] : 0;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int64_t v = threadIdx.x >= (unsigned)off ? s[threadIdx.x - off] : 0;
-    __syncthreads();
-    s[threadIdx.x] += v;
-    __syncthreads();
-  }
-  if (i < len) out[i] = s[threadIdx.x] - (i < len ? in[i] : 0);
-  if (threadIdx.x == 1023) block_sum[blockIdx.x] = s[1023];
-}
-
-__global__ __launch_bounds__(1024) void k_scan_sums(int64_t *__restrict__ block_sum, int64_t nb) {
-  // single block: exclusive scan of nb block sums, sequential chunks per thread
-  __shared__ int64_t part[1024];
-  const int64_t per = (nb + 1023) / 1024;
-  const int64_t b0 = threadIdx.x * per;
-  const int64_t b1 = b0 + per < nb ? b0 + per : nb;
-  int64_t acc = 0;
-  for (int64_t i = b0; i < b1; ++i) acc += block_sum[i];
-  part[threadIdx.x] = acc;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int64_t v = threadIdx.x >= (unsigned)off ? part[threadIdx.x - off] : 0;
-    __syncthreads();
-    part[threadIdx.x] += v;
+    int64_t run = before + scan[threadIdx.x] - tot;
+    before += scan[1023];
+    if (j < n) {
+      col_ptr[j] = run;
+      for (int s = 0; s < nseg; s += 8) {
+        int64_t v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = s + e < nseg ? seg[(int64_t)(s + e) * n + j] : 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (s + e < nseg) seg[(int64_t)(s + e) * n + j] = run;
+          run += v[e];
+        }
+      }
+    }
     __syncthreads();
   }
-  int64_t run = threadIdx.x ? part[threadIdx.x - 1] : 0;
-  for (int64_t i = b0; i < b1; ++i) {
-    const int64_t v = block_sum[i];
-    block_sum[i] = run;
-    run += v;
+  if (threadIdx.x == 0) col_ptr[n] = before;
+}
+
+__global__ __launch_bounds__(kCscThreads) void k_csc_place(int64_t m, int n, const int64_t *__restrict__ ptr,
+                                                           const int32_t *__restrict__ col,
+                                                           const float *__restrict__ val, int nchunk,
+                                                           const int32_t *__restrict__ hist,
+                                                           const int64_t *__restrict__ seg,
+                                                           int32_t *__restrict__ row_idx, float *__restrict__ cval) {
+  extern __shared__ unsigned long long mask_s[];  // [n][2] masks, then [n] positions
+  __shared__ int rp[kCscRows + 1];
+  int64_t *pos = reinterpret_cast<int64_t *>(mask_s + 2 * n);
+  const int chunk = csc_chunk(nchunk);
+  if (chunk < 0) return;
+  for (int j = threadIdx.x; j < n; j += kCscThreads)
+    pos[j] = seg[(int64_t)(chunk / kCscSeg) * n + j] + hist[(int64_t)chunk * n + j];
+  const CscChunk c = csc_begin(m, n, ptr, chunk, rp, mask_s);
+  csc_masks(c, n, col, rp, mask_s);
+  for (int t = threadIdx.x; t < c.len; t += kCscThreads) {
+    const int j = col[c.e0 + t];
+    if (j < 0 || j >= n) continue;
+    const int r = csc_row(rp, t);
+    const unsigned long long lo = mask_s[2 * j], hi = mask_s[2 * j + 1];
+    const unsigned long long below = (1ull << (r & 63)) - 1ull;
+    const int rank = r < 64 ? __popcll(lo & below) : __popcll(lo) + __popcll(hi & below);
+    const int64_t p = pos[j] + rank;
+    row_idx[p] = (int32_t)(c.r0 + r);
+    cval[p] = val[c.e0 + t];
   }
-}
-
-__global__ void k_scan_add(int64_t *__restrict__ out, int64_t len, const int64_t *__restrict__ block_sum) {
-  const int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-  if (i < len) out[i] += block_sum[blockIdx.x];
-}
-
-// col_ptr[j] = base[j * nchunk] (first chunk of column j), col_ptr[n] = number of entries
-__global__ void k_colptr(const int64_t *__restrict__ base, const int32_t *__restrict__ hist, int n, int nchunk,
-                         int64_t *__restrict__ col_ptr) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t len = (int64_t)n * nchunk;
-  if (j < n) col_ptr[j] = nchunk > 0 ? base[(int64_t)j * nchunk] : 0;
-  if (j == n) col_ptr[n] = len > 0 ? base[len - 1] + hist[len - 1] : 0;
 }
 
 // flag[0] |= 1 if some column index lies outside [0, n)
@@ -149,29 +204,25 @@ static open_status check_cols(open_ctx *ctx, int64_t nnz, const int32_t *col, in
 
 open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, const int64_t *row_ptr, const int32_t *col,
                                    const float *val, int64_t *col_ptr, int32_t *row_idx, float *cval) {
-  const int nchunk = (int)((m + kChunkRows - 1) / kChunkRows);
-  const int64_t len = (int64_t)n * nchunk;
-  const int64_t nb = (len + 1023) / 1024;
-  void *hist, *base, *bsum;
+  const int nchunk = (int)((m + kCscRows - 1) / kCscRows);
+  const int nseg = (nchunk + kCscSeg - 1) / kCscSeg;
+  void *hist, *seg;
   open_status st;
-  if ((st = ws_get(ctx, open_ctx::WS_HIST, sizeof(int32_t) * (size_t)(len > 0 ? len : 1), &hist))) return st;
-  if ((st = ws_get(ctx, open_ctx::WS_SPLIT, sizeof(int64_t) * (size_t)(len > 0 ? len : 1), &base))) return st;
-  if ((st = ws_get(ctx, open_ctx::WS_RED, sizeof(int64_t) * (size_t)(nb > 0 ? nb : 1), &bsum))) return st;
-  const int blocks = (nchunk + kCscWaves - 1) / kCscWaves;
+  if ((st = ws_get(ctx, open_ctx::WS_HIST, sizeof(int32_t) * (size_t)n * (size_t)(nchunk > 0 ? nchunk : 1), &hist)))
+    return st;
+  if ((st = ws_get(ctx, open_ctx::WS_SPLIT, sizeof(int64_t) * (size_t)n * (size_t)(nseg > 0 ? nseg : 1), &seg)))
+    return st;
+  const dim3 blocks(8 * (unsigned)((nchunk + 7) / 8)), threads(kCscThreads);
+  const size_t lds = sizeof(unsigned long long) * 2 * (size_t)n;
   if (nchunk > 0) {
-    OPEN_LAUNCH(ctx, "csc_count", k_csc_count, dim3(blocks), dim3(kCscWaves * 64), sizeof(int) * kCscWaves * n, m, n,
-                row_ptr, col, nchunk, (int32_t *)hist);
-    OPEN_LAUNCH(ctx, "scan_blocks", k_scan_blocks, dim3((unsigned)nb), dim3(1024), 0, (const int32_t *)hist, len,
-                (int64_t *)base, (int64_t *)bsum);
-    OPEN_LAUNCH(ctx, "scan_sums", k_scan_sums, dim3(1), dim3(1024), 0, (int64_t *)bsum, nb);
-    OPEN_LAUNCH(ctx, "scan_add", k_scan_add, dim3((unsigned)nb), dim3(1024), 0, (int64_t *)base, len,
-                (const int64_t *)bsum);
+    OPEN_LAUNCH(ctx, "csc_count", k_csc_count, blocks, threads, lds, m, n, row_ptr, col, nchunk, (int32_t *)hist);
+    OPEN_LAUNCH(ctx, "csc_segments", k_csc_segments, dim3((unsigned)((n + 255) / 256), (unsigned)nseg), dim3(256), 0, n,
+                nchunk, (int32_t *)hist, (int64_t *)seg);
   }
-  OPEN_LAUNCH(ctx, "csc_colptr", k_colptr, dim3((n + 1 + 255) / 256), dim3(256), 0, (const int64_t *)base,
-              (const int32_t *)hist, n, nchunk, col_ptr);
+  OPEN_LAUNCH(ctx, "csc_bases", k_csc_bases, dim3(1), dim3(1024), 0, n, nseg, (int64_t *)seg, col_ptr);
   if (nchunk > 0) {
-    OPEN_LAUNCH(ctx, "csc_place", k_csc_place, dim3(blocks), dim3(kCscWaves * 64), sizeof(int64_t) * kCscWaves * n, m,
-                n, row_ptr, col, val, nchunk, (const int64_t *)base, row_idx, cval);
+    OPEN_LAUNCH(ctx, "csc_place", k_csc_place, blocks, threads, lds + sizeof(int64_t) * (size_t)n, m, n, row_ptr, col,
+                val, nchunk, (const int32_t *)hist, (const int64_t *)seg, row_idx, cval);
   }
   return OPEN_OK;
 }

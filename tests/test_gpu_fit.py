@@ -198,3 +198,27 @@ def test_large_config_fit_sampled(ctx):
     print("large column half-sweep (64 columns, %d-%d entries): max %.3e median %.3e"
           % (np.diff(rcp)[scols].min(), np.diff(rcp)[scols].max(), ec.max(), np.median(ec)), flush=True)
     assert ec.max() <= 1e-4
+
+
+@pytest.mark.parametrize("m,n", [(1, 1), (127, 7), (128, 1), (129, 4096), (1000, 480), (8 * 128 + 1, 33), (8300, 1025)])
+def test_csc_chunk_edges(ctx, m, n):
+    # chunks of 128 rows (two masks of 64), scan segments of 64 chunks, rounds of 1024 columns;
+    # empty and full rows and columns
+    r = np.random.default_rng([m, n])
+    counts = np.minimum(r.integers(0, 9, size=m), n)
+    counts[r.integers(0, m)] = n
+    counts[m // 2] = 0
+    rp = np.zeros(m + 1, np.int64)
+    rp[1:] = np.cumsum(counts)
+    col = np.concatenate([np.sort(r.choice(n, size=c, replace=False)) for c in counts]).astype(np.int32)
+    val = r.uniform(size=len(col)).astype(np.float32)
+    if len(col) == 0:
+        col, val = np.zeros(1, np.int32), np.zeros(1, np.float32)
+    cp, ri, cv = native.open_csr_to_csc(ctx, dev(rp), dev(col), dev(val), n)
+    torch.cuda.synchronize()
+    nnz = int(rp[-1])
+    rows = np.repeat(np.arange(m), counts)
+    order = np.lexsort((rows, col[:nnz]))
+    assert np.array_equal(cp.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(col[:nnz], minlength=n))]))
+    assert np.array_equal(ri.cpu().numpy()[:nnz], rows[order])
+    assert np.array_equal(cv.cpu().numpy()[:nnz], val[:nnz][order])
