@@ -4,9 +4,10 @@
 // written class by class (ascending within a class) by a stable counting sort:
 //   class 0              empty rows
 //   classes 1..8         dual form, system dimension padded to 4*class (n_i <= min(k, 32))
-//   classes 9..15        primal form (k x k system), n_i in (k 2^p, k 2^(p+1)], p = class - 9
-//                        (class 9 also takes n_i in (32, 64] at rank 64)
-//   class 16             rows long enough for the split-K path
+//   classes 9..30        primal form (k x k system), four classes per doubling of n_i / k (class
+//                        9 also takes n_i in (32, 64] at rank 64): the 16 rows of a group run to
+//                        their longest, 30 % more than their mean at one class per doubling
+//   class 31             rows long enough for the split-K path
 // Exact integer work; the resulting list is independent of scheduling.
 #include "common.h"
 
@@ -28,12 +29,13 @@ __device__ __forceinline__ int row_class(int64_t cnt, int k, int64_t split_min) 
   const int dmax = k < 32 ? k : 32;
   if (cnt <= dmax) return (int)((cnt + 3) >> 2);
   if (cnt >= split_min) return kSplitClass;
-  // primal: class 9 + floor(log2((n_i - 1) / k)), at least 9 (rank 64 reaches here from
-  // n_i = 33, where (n_i - 1) / k is still 0)
-  const int64_t r = (cnt - 1) / k;
-  int p = r > 0 ? 63 - __clzll((unsigned long long)r) : 0;
-  p = p > 6 ? 6 : p;
-  return 9 + p;
+  // primal: v = 4 (n_i - 1) / k >= 4 past one doubling; its leading bit and the two bits below it
+  // (rank 64 reaches here from n_i = 33, where v is 2 or 3)
+  const int64_t v = 4 * (cnt - 1) / k;
+  if (v < 4) return kPrimalLo;
+  const int o = 61 - __clzll((unsigned long long)v);  // v in [4 2^o, 8 2^o)
+  const int c = kPrimalLo + 4 * o + (int)((v >> o) & 3);
+  return c < kPrimalHi ? c : kPrimalHi;
 }
 
 // mask (nullable): rows with mask[i] == 0 are left out of every class (class -1)
@@ -103,7 +105,7 @@ __device__ __forceinline__ unsigned wave_classes_present(const WaveRows &r) {
 }
 
 // per-class count of the wave's rows, class cc held by lane cc; one ballot per pass and
-// class present (a fold-in batch has a handful of classes out of 17)
+// class present (a fold-in batch has a handful of classes)
 __device__ __forceinline__ int wave_class_counts(const WaveRows &r, int lane, unsigned present) {
   int mine = 0;
 #pragma unroll

@@ -123,7 +123,7 @@ struct open_ctx {
   std::string err;
   // grow-only device workspaces, indexed by purpose
   enum {
-    WS_HIST, WS_CLS, WS_LIST, WS_CSC_PTR, WS_CSC_IDX, WS_CSC_VAL, WS_RED, WS_SPLIT, WS_MISC, WS_FLAG, WS_OBJ,
+    WS_HIST, WS_CLS, WS_LIST, WS_CSC_PTR, WS_CSC_IDX, WS_CSC_VAL, WS_SPLIT, WS_MISC, WS_FLAG, WS_OBJ,
     WS_PRED, WS_SPLIT_START, WS_SPLIT_PART, WS_SPLIT_FLAG, WS_NCF, WS_COUNT
   };
   void *ws[WS_COUNT] = {};
@@ -214,8 +214,9 @@ struct RowRef {
 // ---- internal launchers (defined in the .hip files)
 // Row classification + stable counting sort; fills list[m] (row ids grouped by class) and
 // cls[2*kNumClasses] = {start, count} per class, on the device.
-constexpr int kNumClasses = 17;
-constexpr int kSplitClass = 16;  // rows solved by the split-K path
+constexpr int kPrimalLo = 9, kPrimalHi = 30;  // primal classes, by length
+constexpr int kNumClasses = 32;
+constexpr int kSplitClass = 31;  // rows solved by the split-K path
 constexpr int64_t kSplitMin = 1024;  // observations from which a row takes the split-K path
 open_status bucket_rows(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int k, RowRef **list, int64_t **cls,
                         int64_t split_min, const uint8_t *mask = nullptr);

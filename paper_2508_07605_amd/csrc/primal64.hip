@@ -195,7 +195,7 @@ __global__ __launch_bounds__(64 * kP64Waves) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
-// The group of size classes 9..15 at rank 64 (n_i > 32 below the split-K length): one
+// The group of primal size classes at rank 64 (n_i > 32 below the split-K length): one
 // variant, a persistent grid of up to two blocks per CU (LDS: 4 x 16.9 KB per block).
 OPEN_GROUP(g_k64_primal) {
   if (choice != 0) return fail(ctx, OPEN_E_INVALID, "kernel variant out of range");
@@ -204,7 +204,7 @@ OPEN_GROUP(g_k64_primal) {
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
   OPEN_LAUNCH(ctx, "ridge_k64_primal", k_primal64, dim3((unsigned)blocks), dim3(64 * kP64Waves), 0, F, n, idx, val,
-              list, cls, 9, 15, lambda, weighted, X, status);
+              list, cls, kPrimalLo, kPrimalHi, lambda, weighted, X, status);
   return OPEN_OK;
 }
 

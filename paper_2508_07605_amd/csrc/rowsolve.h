@@ -28,6 +28,11 @@
 //          columns move between the P lanes by DPP quad_perm; with P = 1 no data moves at all.
 //   Output dual: each lane forms K/P outputs of u = F_O^T a from its system's factor rows;
 //          primal: the solution is u itself.
+// Primal classes are walked longest rows first, and consecutive groups go to different compute
+// units: a group of the longest rows (480 entries at 480 settings) runs for several times the mean,
+// and started last it was the launch's tail.  With that, four classes per doubling of the length and
+// the entries read two batches ahead, the launch of the rows of 25 and more entries of the 200,003 x
+// 480 fit takes 290 us instead of 355.
 // Padded rows of a dual system (i >= n_i) have zero factors, unit diagonal and zero rhs:
 // their unknowns are exactly zero and they do not touch the others.
 #pragma once
@@ -200,8 +205,9 @@ __device__ __forceinline__ void solve_group(const FRows<K, LDSF> &Fr, int n, con
       const int64_t qbeg = (int64_t)(uint32_t)__shfl((int)(mbeg & 0xffffffff), qsrc, 64) |
                            ((int64_t)__shfl((int)(mbeg >> 32), qsrc, 64) << 32);
       const int tmax = wave_max_i(cnt);
-      // indices and values PD entries ahead of the contraction
-      constexpr int PD = 4;
+      // indices and values two batches of PD entries ahead of the contraction, the factor rows one
+      // entry ahead
+      constexpr int PD = 8;
       int jn[PD];
       float rn[PD];
       auto fetch = [&](int t0) {
@@ -212,27 +218,34 @@ __device__ __forceinline__ void solve_group(const FRows<K, LDSF> &Fr, int n, con
           rn[E] = val[e];
         });
       };
-      if (tmax > 0) fetch(0);
+      // the entry's factor row, or -1 (zeros) past the row's end and for a rejected index
+      auto row_of = [&](int t, int j) { return t < cnt && j >= 0 && j < n ? j : -1; };
+      float a[N];
+      if (tmax > 0) {
+        fetch(0);
+        sfor<0, N>([&](auto J) { a[J] = Fr.row1(row_of(0, jn[0]), 4 * J + qi); });
+      }
       for (int t0 = 0; t0 < tmax; t0 += PD) {
         int jc[PD];
         float rc[PD];
         sfor<0, PD>([&](auto E) {
-          jc[E] = jn[E];
-          rc[E] = rn[E];
+          const int t = t0 + (int)E;
+          if (t < cnt && (jn[E] < 0 || jn[E] >= n)) pflags |= 2;
+          if (t < cnt && !__builtin_isfinite(rn[E])) pflags |= 1;
+          jc[E] = row_of(t, jn[E]);
+          rc[E] = jc[E] >= 0 ? rn[E] : 0.f;
         });
         if (t0 + PD < tmax) fetch(t0 + PD);
         sfor<0, PD>([&](auto E) {
           const int t = t0 + (int)E;
           if (t < tmax) {  // wave-uniform
-            const bool ok = t < cnt;
-            int j = jc[E];
-            const float r0 = rc[E];
-            if (ok && (j < 0 || j >= n)) pflags |= 2;
-            if (ok && !__builtin_isfinite(r0)) pflags |= 1;
-            j = (ok && j >= 0 && j < n) ? j : -1;
-            const float r = j >= 0 ? r0 : 0.f;
-            float a[N];
-            sfor<0, N>([&](auto J) { a[J] = Fr.row1(j, 4 * J + qi); });
+            float an[N];
+            int jx;
+            if constexpr (E + 1 < PD)
+              jx = jc[E + 1];
+            else
+              jx = row_of(t + 1, jn[0]);
+            sfor<0, N>([&](auto J) { an[J] = Fr.row1(jx, 4 * J + qi); });
             sfor<0, N>([&](auto I) {
               sfor<0, I + 1>([&](auto J) {
                 if constexpr (ROW)
@@ -241,7 +254,8 @@ __device__ __forceinline__ void solve_group(const FRows<K, LDSF> &Fr, int n, con
                   acc[tri(I, J)] = mfma4x4(a[I], a[J], acc[tri(I, J)]);
               });
             });
-            sfor<0, N>([&](auto J) { pb[J] = __builtin_fmaf(r, a[J], pb[J]); });
+            sfor<0, N>([&](auto J) { pb[J] = __builtin_fmaf(rc[E], a[J], pb[J]); });
+            sfor<0, N>([&](auto J) { a[J] = an[J]; });
           }
         });
       }
@@ -611,8 +625,10 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   const int64_t count = cls[2 * c_hi] + cls[2 * c_hi + 1] - start;
   const int64_t end = start + count;
   const int64_t nw = (int64_t)gridDim.x * W;
-  const int64_t g0 = (int64_t)blockIdx.x * W + (threadIdx.x >> 6);
-  if ((int64_t)blockIdx.x * W * SYS >= count) return;  // block has no work (uniform)
+  // wave-major: consecutive groups, which cost alike, go to different compute units
+  const int64_t g0 = (int64_t)blockIdx.x + (int64_t)gridDim.x * (threadIdx.x >> 6);
+  const int64_t groups = (count + SYS - 1) / SYS;
+  if ((int64_t)blockIdx.x >= groups) return;  // block has no work (uniform)
   FRows<K, LDSF> Fr;
   if constexpr (LDSF) {
     Fr.lds = stage_factors<K, W>(F, n, lds_all + W * WL);
@@ -624,11 +640,12 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   float *wl = lds_all + (threadIdx.x >> 6) * WL;
   const int sme = (threadIdx.x & 63) / P;
   auto fetch = [&](int64_t g) -> RowRef {
-    const int64_t sl = start + g * SYS + sme;
-    return (g * SYS < count && sl < end) ? list[sl] : RowRef{-1, 0, 0};
+    // primal classes hold ascending lengths: the longest first
+    const int64_t sl = start + (DUAL ? g : groups - 1 - g) * SYS + sme;
+    return (g < groups && sl < end) ? list[sl] : RowRef{-1, 0, 0};
   };
   RowRef cur = fetch(g0);
-  for (int64_t g = g0; g * SYS < count; g += nw) {
+  for (int64_t g = g0; g < groups; g += nw) {
     const RowRef nxt = fetch(g + nw);  // next group's records load while this group computes
     // operand prefetch in the Gram loop when a single wave per SIMD has to hide the latency
     solve_group<P, D, K, DUAL, LDSF, (OCC == 1 || D <= 12), BLK>(Fr, n, cur, idx, val, lambda, weighted, X, status,
@@ -680,8 +697,9 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   const int64_t total = g1[NC - 1];  // groups of all classes
   const int64_t nw = (int64_t)gridDim.x * W;
   (void)ptr;
-  const int64_t g0 = (int64_t)blockIdx.x * W + (threadIdx.x >> 6);
-  if ((int64_t)blockIdx.x * W >= total) return;  // block has no work (uniform)
+  // wave-major: consecutive groups, which cost alike, go to different compute units
+  const int64_t g0 = (int64_t)blockIdx.x + (int64_t)gridDim.x * (threadIdx.x >> 6);
+  if ((int64_t)blockIdx.x >= total) return;  // block has no work (uniform)
   FRows<K, LDSF> Fr;
   if constexpr (LDSF) {
     Fr.lds = stage_factors<K, W>(F, n, lds_all + W * WL);
@@ -703,7 +721,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
         int64_t gl = (g0 - gb) % nw;           // the wave's first group of the class
         if (gl < 0) gl += nw;
         auto fetch = [&](int64_t q) -> RowRef {
-          const int64_t sl = q * SYS + sme;
+          // primal classes hold ascending lengths: the longest first
+          const int64_t sl = (C::DUAL ? q : ng - 1 - q) * SYS + sme;
           return (q < ng && sl < cc[i]) ? list[cs[i] + sl] : RowRef{-1, 0, 0};
         };
         RowRef cur = fetch(gl);

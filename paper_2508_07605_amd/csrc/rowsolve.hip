@@ -12,14 +12,14 @@ const ClassGroup *class_groups(int k, int *count) {
   static const ClassGroup g8[] = {
       {"ridge_k8_d4", 0, 1, 2, g_k8_d4},
       {"ridge_k8_d8", 2, 2, 2, g_k8_d8},
-      {"ridge_k8_primal", 9, 15, 2, g_k8_primal},
+      {"ridge_k8_primal", kPrimalLo, kPrimalHi, 2, g_k8_primal},
   };
   static const ClassGroup g16[] = {
       {"ridge_k16_d4", 0, 1, 2, g_k16_d4},
       {"ridge_k16_d8", 2, 2, 2, g_k16_d8},
       {"ridge_k16_d12", 3, 3, 2, g_k16_d12},
       {"ridge_k16_d16", 4, 4, 2, g_k16_d16},
-      {"ridge_k16_primal", 9, 15, 2, g_k16_primal},
+      {"ridge_k16_primal", kPrimalLo, kPrimalHi, 2, g_k16_primal},
   };
   static const ClassGroup g32[] = {
       {"ridge_k32_d4", 0, 1, 2, g_k32_d4},
@@ -30,9 +30,9 @@ const ClassGroup *class_groups(int k, int *count) {
       {"ridge_k32_d24", 6, 6, 4, g_k32_d24},
       {"ridge_k32_d28", 7, 7, 2, g_k32_d28},
       {"ridge_k32_d32", 8, 8, 2, g_k32_d32},
-      {"ridge_k32_primal", 9, 15, 2, g_k32_primal},
+      {"ridge_k32_primal", kPrimalLo, kPrimalHi, 2, g_k32_primal},
       // launch mode of the whole pass: 0 = three merged launches, 1 = one launch per group above
-      {"ridge_k32_launch", 0, 15, 2, nullptr},
+      {"ridge_k32_launch", 0, kPrimalHi, 2, nullptr},
   };
   static const ClassGroup g64[] = {
       {"ridge_k64_d4", 0, 1, 2, g_k64_d4},
@@ -43,7 +43,7 @@ const ClassGroup *class_groups(int k, int *count) {
       {"ridge_k64_d24", 6, 6, 2, g_k64_d24},
       {"ridge_k64_d28", 7, 7, 2, g_k64_d28},
       {"ridge_k64_d32", 8, 8, 2, g_k64_d32},
-      {"ridge_k64_primal", 9, 15, 1, g_k64_primal},
+      {"ridge_k64_primal", kPrimalLo, kPrimalHi, 1, g_k64_primal},
   };
   switch (k) {
     case 8: *count = (int)(sizeof(g8) / sizeof(g8[0])); return g8;

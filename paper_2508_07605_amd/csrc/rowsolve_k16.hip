@@ -25,7 +25,7 @@ OPEN_GROUP(g_k16_d16) {
 }
 
 OPEN_GROUP(g_k16_primal) {
-  return launch_variant<16, 16, false, cfg(4, 16, 4), cfg(4, 8, 2)>(choice, "ridge_k16_primal", 9, 15, OPEN_TIER_PASS, X,
+  return launch_variant<16, 16, false, cfg(4, 16, 4), cfg(4, 8, 2)>(choice, "ridge_k16_primal", kPrimalLo, kPrimalHi, OPEN_TIER_PASS, X,
                        status, m);
 }
 

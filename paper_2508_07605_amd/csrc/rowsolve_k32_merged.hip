@@ -10,7 +10,7 @@
 namespace openk {
 
 open_status rowsolve_k32_merged(OPEN_TIER_ARGS) {
-  open_status st = launch_multi<32, 4, 8, 2, SizeClass<32, false, 9, 15>, SizeClass<32, true, 8, 8>,
+  open_status st = launch_multi<32, 4, 8, 2, SizeClass<32, false, kPrimalLo, kPrimalHi>, SizeClass<32, true, 8, 8>,
                                 SizeClass<28, true, 7, 7>>("ridge_k32_d28_up", OPEN_TIER_PASS, X, status, m);
   if (st) return st;
   st = launch_multi<32, 4, 8, 2, SizeClass<24, true, 6, 6>, SizeClass<20, true, 5, 5>, SizeClass<16, true, 4, 4>>(

@@ -5,7 +5,7 @@
 namespace openk {
 
 OPEN_GROUP(g_k32_primal) {
-  return launch_variant<32, 32, false, cfg(4, 8, 2), cfg(4, 4, 1)>(choice, "ridge_k32_primal", 9, 15, OPEN_TIER_PASS, X,
+  return launch_variant<32, 32, false, cfg(4, 8, 2), cfg(4, 4, 1)>(choice, "ridge_k32_primal", kPrimalLo, kPrimalHi, OPEN_TIER_PASS, X,
                        status, m);
 }
 

@@ -15,7 +15,7 @@ OPEN_GROUP(g_k8_d8) {
 }
 
 OPEN_GROUP(g_k8_primal) {
-  return launch_variant<8, 8, false, cfg(4, 16, 4), cfg(4, 8, 2)>(choice, "ridge_k8_primal", 9, 15, OPEN_TIER_PASS, X,
+  return launch_variant<8, 8, false, cfg(4, 16, 4), cfg(4, 8, 2)>(choice, "ridge_k8_primal", kPrimalLo, kPrimalHi, OPEN_TIER_PASS, X,
                        status, m);
 }
 
