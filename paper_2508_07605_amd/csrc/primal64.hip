@@ -2,204 +2,271 @@
 // fold-in and of the ALS row half-sweep, Section III-B.2, with the ALS-WR weighting of the
 // paper's CF reference):
 //     (sum_{j in O_i} f_j f_j^T + lambda w_i I_64) u_i = sum_{j in O_i} r_ij f_j.
-// The 64 x 64 system of a row does not fit the register layouts of the other size classes, so
-// each row gets one wavefront:
-//   Gram   the row's entries are staged in LDS (1024 per chunk); the factor rows are gathered
-//          through a bounds-checked buffer resource (index -1 of padding reads zero), two
-//          observations per v_mfma_f32_32x32x2f32 step, three 32x32 blocks (A11, A21, A22) in
-//          float32 accumulators; the right-hand side accumulates beside them.
-//   Layout the blocks go to LDS as the full symmetric matrix (pitch 65, conflict-free columns)
-//          with the ridge on the diagonal; lane c then holds column c in 64 registers.
-//   Solve  right-looking LDL^T without pivoting (SPD): at pivot p every lane writes its entry
-//          of row p of the (symmetric) trailing matrix to LDS, and every lane reads the row
-//          back as 16-byte broadcasts, which is column p below the pivot; lane c applies the
-//          multiplier A[p][c] / d_p to its rows r > p and to its right-hand side (forward
-//          substitution fused in).  After the elimination lane r still holds d_r L[p][r] in
-//          register p > r, so the back substitution is column-oriented: x_p is broadcast
-//          with a lane read and lanes r < p subtract d_r L[p][r] x_p.
-//   Output lane c writes u_c (one 256-byte row per wavefront).
+// The 64 x 64 system of a row does not fit the register layouts of the other size classes.  A
+// wavefront takes four rows:
+//   Gram   row by row on v_mfma_f32_16x16x4f32, four observations a step.  Lane (i, o), i = lane % 16,
+//          o = lane / 16, loads the dimensions 4 i .. 4 i + 3 of observation o (16 bytes); block b
+//          of 16 dimensions is {4 i + b}, and the ten blocks of the lower triangle are formed
+//          transposed: register e of lane (i, o) is row 16 b + i, column 16 c + 4 o + e.  Indices
+//          and values are staged in LDS 256 at a time, the next ones (of the next row too) loading
+//          meanwhile.  All four rows stay in registers, 160 of them.
+//   Layout the four lanes i, 16 + i, 32 + i, 48 + i exchange their pieces of the four systems
+//          (lane-row swaps, no LDS): then lane row q holds system q, lane i its rows 16 b + i.
+//   Solve  right-looking LDL^T without pivoting (SPD) of the four systems at once, 16 lanes each,
+//          with the forward substitution fused in: pivot entries move by DPP row broadcast.  The
+//          back substitution is a sum per lane and a reduction over the 16 lanes per unknown.
+//   Output lane i writes the dimensions 4 i .. 4 i + 3 of its system (16 bytes).
+// One wavefront's matrix instructions run under the other's solve (two per SIMD).
 #include "rowsolve.h"
 
 namespace openk {
 
-constexpr int kP64Waves = 4;                 // wavefronts per block
-constexpr int kP64Pitch = 65;                // LDS pitch of the 64 x 64 matrix
-constexpr int kP64Mat = 64 * kP64Pitch;      // matrix floats per wavefront
-constexpr int kP64Chunk = 1024;              // entries staged per chunk (indices + values)
-constexpr int kP64Unr = 8;                   // MFMA steps (2 observations each) per batch
-static_assert(2 * kP64Chunk <= kP64Mat, "entry staging aliases the matrix area");
+constexpr int kP64Waves = 4;    // wavefronts per block
+constexpr int kP64Rows = 4;     // rows of a wavefront
+constexpr int kP64Stage = 256;  // entries staged per wavefront, twice
+constexpr int kP64Steps = 4;    // MFMA steps (four observations each) whose rows load together
 
-typedef float f16v __attribute__((ext_vector_type(16)));
+// value of lane SRC of the lane's row of 16 (DPP row broadcast)
+template <int SRC>
+__device__ __forceinline__ float row16_bcast(float x) {
+  return __builtin_bit_cast(float,
+                            __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x150 + SRC, 0xf, 0xf, true));
+}
+// sum over the lane's row of 16
+__device__ __forceinline__ float row16_sum(float x) {
+  x += quad_xor1(x);
+  x += quad_xor2(x);
+  x += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x141, 0xf, 0xf, true));  // half mirror
+  x += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x140, 0xf, 0xf, true));  // mirror
+  return x;
+}
+// x[q], q = 0..3, of lane row o -> x[o] of lane row q (a 4 x 4 transposition over the lane rows)
+__device__ __forceinline__ void swap_lane_rows(float &x0, float &x1, float &x2, float &x3) {
+  auto half = [](float &a, float &b) {  // upper half of a <-> lower half of b
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
+                                                    false, false);
+    const unsigned ra = r[0], rb = r[1];  // (a bit cast of the vector element itself reads element 0)
+    a = __builtin_bit_cast(float, ra);
+    b = __builtin_bit_cast(float, rb);
+  };
+  auto quarter = [](float &a, float &b) {  // odd rows of a <-> even rows of b
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
+                                                    false, false);
+    const unsigned ra = r[0], rb = r[1];  // (a bit cast of the vector element itself reads element 0)
+    a = __builtin_bit_cast(float, ra);
+    b = __builtin_bit_cast(float, rb);
+  };
+  half(x0, x2);
+  half(x1, x3);
+  quarter(x0, x1);
+  quarter(x2, x3);
+}
 
-__global__ __launch_bounds__(64 * kP64Waves) __attribute__((amdgpu_waves_per_eu(2))) void k_primal64(const float *__restrict__ F, int n,
-                                                             const int32_t *__restrict__ idx,
-                                                             const float *__restrict__ val,
-                                                             const RowRef *__restrict__ list,
-                                                             const int64_t *__restrict__ cls, int c_lo, int c_hi,
-                                                             float lambda, int weighted, float *__restrict__ X,
-                                                             int32_t *__restrict__ status) {
-  __shared__ __attribute__((aligned(16))) float lds[kP64Waves][kP64Mat + 64];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float *mat = lds[w];
-  float *colb = lds[w] + kP64Mat;  // pivot column broadcast buffer
-  int *jl = reinterpret_cast<int *>(mat);
-  float *rl = mat + kP64Chunk;
-  const int64_t start = cls[2 * c_lo];
-  const int64_t count = cls[2 * c_hi] + cls[2 * c_hi + 1] - start;
+__global__ __launch_bounds__(64 * kP64Waves) __attribute__((amdgpu_waves_per_eu(2))) void k_primal64(
+    const float *__restrict__ F, int n, const int32_t *__restrict__ idx, const float *__restrict__ val,
+    const RowRef *__restrict__ list, const int64_t *__restrict__ cls, int c_lo, int c_hi, float lambda, int weighted,
+    float *__restrict__ X, int32_t *__restrict__ status) {
+  __shared__ int jl_all[kP64Waves][2][kP64Stage];
+  __shared__ float rl_all[kP64Waves][2][kP64Stage];
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int i16 = lane & 15, o = lane >> 4;
+  const int64_t first = cls[2 * c_lo];
+  const int64_t count = cls[2 * c_hi] + cls[2 * c_hi + 1] - first;
+  const int64_t units = (count + kP64Rows - 1) / kP64Rows;
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(F, (uint64_t)n * 64 * sizeof(float));
-  const int d = lane & 31, o = lane >> 5;  // dimension and observation slot in an MFMA step
   const int64_t nw = (int64_t)gridDim.x * kP64Waves;
-  for (int64_t g = (int64_t)blockIdx.x * kP64Waves + w; g < count; g += nw) {
-    const RowRef rr = list[start + g];
-    f16v a11 = f16v{}, a21 = f16v{}, a22 = f16v{};
-    float bl = 0.f, bh = 0.f;
-    int flags = 0;  // 1: non-finite value, 2: column index outside [0, n)
-    for (int c0 = 0; c0 < rr.cnt; c0 += kP64Chunk) {
-      const int len = rr.cnt - c0 < kP64Chunk ? rr.cnt - c0 : kP64Chunk;
-      const int lenp = (len + 2 * kP64Unr - 1) & ~(2 * kP64Unr - 1);  // <= kP64Chunk
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();  // the previous chunk's (or row's) LDS reads are done
-      for (int t = lane; t < lenp; t += 64) {
-        const bool in = t < len;
-        const int j = in ? idx[rr.beg + c0 + t] : -1;
-        const float r = in ? val[rr.beg + c0 + t] : 0.f;
-        const bool jok = j >= 0 && j < n;
-        if (in && !jok) flags |= 2;
-        if (in && !__builtin_isfinite(r)) flags |= 1;
-        jl[t] = jok ? j : -1;
-        rl[t] = r;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      float ul[kP64Unr], uh[kP64Unr], rv[kP64Unr];
-      auto load = [&](int t0) {
+  // wave-major and the longest rows first: units that cost alike go to different compute units
+  const int64_t u0 = (int64_t)blockIdx.x + (int64_t)gridDim.x * w;
+  // the unit's records, row q in lane q
+  auto records = [&](int64_t u) -> RowRef {
+    const int64_t sl = (units - 1 - u) * kP64Rows + lane;
+    return u < units && lane < kP64Rows && sl < count ? list[first + sl] : RowRef{-1, 0, 0};
+  };
+  RowRef rec = records(u0);
+  int jn[kP64Stage / 64];
+  float rn[kP64Stage / 64];
+  auto fetch = [&](int64_t beg, int len, int t0) {
 #pragma unroll
-        for (int u = 0; u < kP64Unr; ++u) {
-          const int t = t0 + 2 * u + o;
-          const int j = jl[t];
-          rv[u] = rl[t];
-          const uint32_t off = (uint32_t)(j * 64 + d) * 4u;  // j = -1 wraps out of range: zero
-          ul[u] = bload_f32(rs, (int)off);
-          uh[u] = bload_f32(rs, (int)(off + 128u));
+    for (int e = 0; e < kP64Stage / 64; ++e) {
+      const int t = t0 + 64 * e + lane;
+      jn[e] = t < len ? idx[beg + t] : -1;
+      rn[e] = t < len ? val[beg + t] : 0.f;
+    }
+  };
+  int stg = 0;  // staging buffer in use
+  if (u0 < units) fetch(readlane_i64(rec.beg, 0), __builtin_amdgcn_readlane(rec.cnt, 0), 0);
+  for (int64_t u = u0; u < units; u += nw) {
+    const RowRef nxt = records(u + nw);
+    float g[kP64Rows][40];  // the four lower block triangles, block (b, c <= b), register e: [4 tri(b, c) + e]
+    float rhs[4] = {0.f, 0.f, 0.f, 0.f};
+    int flags = 0;          // of the lane row's system: 1 non-finite value, 2 index outside [0, n)
+    sfor<0, kP64Rows>([&](auto Q) {
+      constexpr int q = decltype(Q)::value;
+      const int len = __builtin_amdgcn_readlane(rec.cnt, q);
+      const int64_t beg = readlane_i64(rec.beg, q);
+      f4 acc[10];
+#pragma unroll
+      for (int e = 0; e < 10; ++e) acc[e] = f4{0.f, 0.f, 0.f, 0.f};
+      float b[4] = {0.f, 0.f, 0.f, 0.f};
+      int fl = 0;
+      // the staged registers -> LDS, then the following entries (of this row or the next) load
+      auto stage = [&](int t0) {
+        stg ^= 1;
+        int *jl = jl_all[w][stg];
+        float *rl = rl_all[w][stg];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int e = 0; e < kP64Stage / 64; ++e) {
+          const bool in = t0 + 64 * e + lane < len;
+          const bool ok = jn[e] >= 0 && jn[e] < n;
+          if (in && !ok) fl |= 2;
+          if (in && !__builtin_isfinite(rn[e])) fl |= 1;
+          jl[64 * e + lane] = ok ? jn[e] : -1;
+          rl[64 * e + lane] = rn[e];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (t0 + kP64Stage < len)
+          fetch(beg, len, t0 + kP64Stage);
+        else if constexpr (q + 1 < kP64Rows)
+          fetch(readlane_i64(rec.beg, q + 1), __builtin_amdgcn_readlane(rec.cnt, q + 1), 0);
+        else
+          fetch(readlane_i64(nxt.beg, 0), __builtin_amdgcn_readlane(nxt.cnt, 0), 0);
+      };
+      f4 un[kP64Steps];
+      float vn[kP64Steps];
+      auto gather = [&](int t0) {
+        const int *jl = jl_all[w][stg] + t0 % kP64Stage;
+        const float *rl = rl_all[w][stg] + t0 % kP64Stage;
+#pragma unroll
+        for (int e = 0; e < kP64Steps; ++e) {
+          const int j = jl[4 * e + o];
+          vn[e] = rl[4 * e + o];
+          un[e] = bload_f4(rs, (int)((uint32_t)(j * 64 + 4 * i16) * 4u));  // j = -1 wraps out of range: zeros
         }
       };
-      load(0);
-      for (int t0 = 0; t0 < lenp; t0 += 2 * kP64Unr) {
-        float cl[kP64Unr], ch[kP64Unr], cr[kP64Unr];
+      stage(0);
+      if (len > 0) gather(0);
+      for (int t0 = 0; t0 < len; t0 += 4 * kP64Steps) {
+        f4 f[kP64Steps];
+        float v[kP64Steps];
 #pragma unroll
-        for (int u = 0; u < kP64Unr; ++u) {
-          cl[u] = ul[u];
-          ch[u] = uh[u];
-          cr[u] = rv[u];
+        for (int e = 0; e < kP64Steps; ++e) {
+          f[e] = un[e];
+          v[e] = vn[e];
         }
-        if (t0 + 2 * kP64Unr < lenp) load(t0 + 2 * kP64Unr);
+        const int t1 = t0 + 4 * kP64Steps;
+        if (t1 < len) {  // wave-uniform
+          if (t1 % kP64Stage == 0) stage(t1);
+          gather(t1);
+        }
 #pragma unroll
-        for (int u = 0; u < kP64Unr; ++u) {
-          a11 = __builtin_amdgcn_mfma_f32_32x32x2f32(cl[u], cl[u], a11, 0, 0, 0);
-          a21 = __builtin_amdgcn_mfma_f32_32x32x2f32(ch[u], cl[u], a21, 0, 0, 0);
-          a22 = __builtin_amdgcn_mfma_f32_32x32x2f32(ch[u], ch[u], a22, 0, 0, 0);
-          bl = __builtin_fmaf(cr[u], cl[u], bl);
-          bh = __builtin_fmaf(cr[u], ch[u], bh);
+        for (int e = 0; e < kP64Steps; ++e) {
+          int t = 0;
+#pragma unroll
+          for (int bi = 0; bi < 4; ++bi)
+#pragma unroll
+            for (int bj = 0; bj <= bi; ++bj, ++t)
+              acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[e][bj], f[e][bi], acc[t], 0, 0, 0);
+#pragma unroll
+          for (int bi = 0; bi < 4; ++bi) b[bi] = __builtin_fmaf(v[e], f[e][bi], b[bi]);
         }
       }
-    }
-    // ---- the symmetric matrix to LDS: lane l holds column l % 32 of each block, register v
-    // row 8 (v / 4) + 4 (l / 32) + v % 4 of it; the A21 block is written on both sides
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();  // the staging area is about to be overwritten
+      // ridge on the diagonal: lane (i, o), register e of a diagonal block is row i, column 4 o + e
+      const float reg = lambda * (weighted ? (float)len : 1.0f);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = 8 * (v / 4) + 4 * o + (v % 4);
-      mat[r * kP64Pitch + d] = a11[v];
-      mat[(32 + r) * kP64Pitch + d] = a21[v];
-      mat[d * kP64Pitch + 32 + r] = a21[v];
-      mat[(32 + r) * kP64Pitch + 32 + d] = a22[v];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const float reg = lambda * (weighted ? (float)rr.cnt : 1.0f);
-    float a[64];
+      for (int bi = 0; bi < 4; ++bi)
 #pragma unroll
-    for (int r = 0; r < 64; ++r) a[r] = mat[r * kP64Pitch + lane];
-    // ridge on the diagonal: register `lane` of lane `lane`
-    {
-      int me = lane;
+        for (int e = 0; e < 4; ++e) acc[tri(bi, bi)][e] += i16 == 4 * o + e ? reg : 0.f;
 #pragma unroll
-      for (int r = 0; r < 64; ++r) {
-        asm volatile("" : "+v"(me));
-        a[r] += r == me ? reg : 0.f;
+      for (int t = 0; t < 10; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[q][4 * t + e] = acc[t][e];
+#pragma unroll
+      for (int bi = 0; bi < 4; ++bi) {
+        float s = b[bi];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        rhs[bi] = o == q ? s : rhs[bi];
       }
-    }
-    // right-hand side: lanes l and l ^ 32 hold the two observation slots of dimension l % 32
-    const float bls = bl + __shfl_xor(bl, 32, 64), bhs = bh + __shfl_xor(bh, 32, 64);
-    float b = lane < 32 ? bls : bhs;
-
-    // ---- LDL^T with fused forward substitution
+      const unsigned long long f1 = __ballot(fl & 1), f2 = __ballot(fl & 2);
+      const int all = (f1 ? 1 : 0) | (f2 ? 2 : 0);
+      flags = o == q ? all : flags;
+    });
+    // lane row q, lane i: st[b][c] = row 16 b + i, column c of system q
+    float st[4][64];
+    sfor<0, 4>([&](auto B) {
+      constexpr int b = decltype(B)::value;
+      sfor<0, b + 1>([&](auto C) {
+        constexpr int c = decltype(C)::value;
+        sfor<0, 4>([&](auto E) {
+          constexpr int t = 4 * tri(b, c) + decltype(E)::value;
+          swap_lane_rows(g[0][t], g[1][t], g[2][t], g[3][t]);
+          sfor<0, 4>([&](auto O) { st[b][16 * c + 4 * decltype(O)::value + decltype(E)::value] = g[O][t]; });
+        });
+      });
+    });
+    // ---- LDL^T with fused forward substitution: st[b][p] becomes -L[.][p] below the pivot
     int bad = 0;
-    float dd = 1.f;  // d_lane
-    // The lane tests below go through a value the compiler cannot see through, so each step
-    // compares afresh instead of keeping 64 precomputed lane masks in scalar registers.
-    int me = lane;
     sfor<0, 64>([&](auto Pp) {
-      constexpr int p = decltype(Pp)::value, q0 = p / 4;
-      asm volatile("" : "+v"(me));
-      // row p of the trailing matrix, one entry per lane (register p of lane c is A[p][c]);
-      // by symmetry it is also column p below the pivot
-      colb[lane] = a[p];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      float gcol[64];
-      sfor<q0, 16>([&](auto Q) {
-        constexpr int q = decltype(Q)::value;
-        const f4 x = *reinterpret_cast<const f4 *>(colb + 4 * q);
-        gcol[4 * q] = x[0];
-        gcol[4 * q + 1] = x[1];
-        gcol[4 * q + 2] = x[2];
-        gcol[4 * q + 3] = x[3];
+      constexpr int p = decltype(Pp)::value, bp = p / 16, pp = p % 16;
+      const float d = row16_bcast<pp>(st[bp][p]);
+      bad |= !(d > 0.f);
+      const float s = __builtin_amdgcn_rcpf(d);
+      const float zp = row16_bcast<pp>(rhs[bp]) * s;  // y_p / d_p
+      float gc[4];
+      sfor<bp, 4>([&](auto B) {
+        constexpr int b = decltype(B)::value;
+        float v = st[b][p];
+        if constexpr (b == bp) v = i16 > pp ? v : 0.f;
+        gc[b] = v;
+        rhs[b] = __builtin_fmaf(-v, zp, rhs[b]);
+        st[b][p] = -v * s;
       });
-      const float dp = gcol[p];
-      bad |= !(dp > 0.f);
-      const float inv = __builtin_amdgcn_rcpf(dp);
-      const float lc = me > p ? a[p] * inv : 0.f;  // L[c][p] = A[p][c] / d_p for c > p
-      sfor<p + 1, 64>([&](auto R) {
-        constexpr int r = decltype(R)::value;
-        a[r] = __builtin_fmaf(-gcol[r], lc, a[r]);
+      rhs[bp] = i16 == pp ? zp : rhs[bp];
+      sfor<p + 1, 64>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        const float lj = row16_bcast<j % 16>(st[j / 16][p]);  // -L[j][p]
+        sfor<j / 16, 4>([&](auto B) {
+          constexpr int b = decltype(B)::value;
+          st[b][j] = __builtin_fmaf(lj, gc[b], st[b][j]);
+        });
       });
-      const float bp = readlane_f32(b, p);  // y_p, final at step p
-      b = __builtin_fmaf(-lc, bp, b);
-      dd = me == p ? dp : dd;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();  // the buffer is rewritten at the next pivot
     });
-    // ---- back substitution: x_r = (y_r - sum_{p > r} d_r L[p][r] x_p) / d_r
-    const float rd = __builtin_amdgcn_rcpf(dd);
+    // ---- back substitution: x_p = z_p - sum_{c > p} L[c][p] x_c
+    float xv[4] = {0.f, 0.f, 0.f, 0.f};
     sfor_down<0, 64>([&](auto Pp) {
-      constexpr int p = decltype(Pp)::value;
-      asm volatile("" : "+v"(me));
-      const float xp = readlane_f32(b * rd, p);
-      b = me < p ? __builtin_fmaf(-a[p], xp, b) : b;
+      constexpr int p = decltype(Pp)::value, bp = p / 16, pp = p % 16;
+      float part = __builtin_fmaf(st[bp][p], xv[bp], 0.f);
+      sfor<bp + 1, 4>([&](auto B) { part = __builtin_fmaf(st[B][p], xv[B], part); });
+      part = row16_sum(part);
+      const float xp = row16_bcast<pp>(rhs[bp]) + part;
+      xv[bp] = i16 == pp ? xp : xv[bp];
     });
-    const float x = b * rd;
-    const bool good = !bad && flags == 0 && rr.cnt > 0;
-    X[(int64_t)rr.row * 64 + lane] = good ? x : 0.f;
-    const unsigned long long f1 = __ballot(flags & 1), f2 = __ballot(flags & 2);
-    if (status && lane == 0)
-      status[rr.row] = rr.cnt == 0 ? OPEN_ROW_EMPTY
-                       : f2        ? OPEN_ROW_BADINDEX
-                       : f1        ? OPEN_ROW_NONFINITE
-                       : bad       ? OPEN_ROW_NONPOS_PIVOT
-                                   : OPEN_ROW_OK;
+    // the lane row's record
+    const int my_row = __shfl(rec.row, o, 64), my_cnt = __shfl(rec.cnt, o, 64);
+    if (my_row >= 0) {
+      const bool good = !bad && flags == 0 && my_cnt > 0;
+      // block b of lane i is dimension 4 i + b
+      *reinterpret_cast<f4 *>(X + (int64_t)my_row * 64 + 4 * i16) =
+          good ? f4{xv[0], xv[1], xv[2], xv[3]} : f4{0.f, 0.f, 0.f, 0.f};
+      if (status && i16 == 0)
+        status[my_row] = my_cnt == 0   ? OPEN_ROW_EMPTY
+                         : (flags & 2) ? OPEN_ROW_BADINDEX
+                         : (flags & 1) ? OPEN_ROW_NONFINITE
+                         : bad         ? OPEN_ROW_NONPOS_PIVOT
+                                       : OPEN_ROW_OK;
+    }
+    rec = nxt;
   }
 }
 
-// The group of primal size classes at rank 64 (n_i > 32 below the split-K length): one
-// variant, a persistent grid of up to two blocks per CU (LDS: 4 x 16.9 KB per block).
+// The group of the primal size classes at rank 64 (n_i > 32 below the split-K length): one
+// variant, a persistent grid of up to two blocks per CU.
 OPEN_GROUP(g_k64_primal) {
   if (choice != 0) return fail(ctx, OPEN_E_INVALID, "kernel variant out of range");
-  int64_t blocks = (m + kP64Waves - 1) / kP64Waves;
+  int64_t blocks = (m + kP64Waves * kP64Rows - 1) / (kP64Waves * kP64Rows);
   const int64_t cap = (int64_t)ctx->num_cu * 2;
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;

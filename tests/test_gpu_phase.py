@@ -76,3 +76,22 @@ def test_rejects_bad_arguments(ctx):
         native.open_phase_detect(ctx, P, 60.0, 0)
     with pytest.raises(native.OpenError):
         native.open_phase_detect(ctx, P, float("nan"), 25)
+
+
+@pytest.mark.parametrize("L", [1, 63, 64, 255, 256, 257, 511, 513, 700])
+def test_block_edges(ctx, L):
+    # blocks of four 64-reading steps, skipped when every reading is below the threshold: runs that
+    # start, end or are carried at every step and block edge, traces ending inside a step, windows
+    # longer than a block, thresholds at and below zero (readings past the trace read as zero)
+    r = np.random.default_rng(L)
+    P = np.full((200, L), 10.0, np.float32)
+    for t in range(200):
+        a = int(r.integers(0, L)) if t % 3 else 64 * int(r.integers(0, L // 64 + 1))
+        P[t, a:a + int(r.integers(1, 330))] = 100.0
+        if t % 5 == 0:
+            P[t, r.integers(0, L)] = 59.0
+    for n in (1, 25, 64, 257):
+        assert np.array_equal(run(ctx, P, 60.0, n), [phase.detect(tr, n_window=n) for tr in P])
+    for th in (0.0, -5.0, float("-inf")):
+        Q = np.where(P > 50, np.float32(1.0), np.float32(-3.0)).astype(np.float32)
+        assert np.array_equal(run(ctx, Q, th, 25), [phase.detect(tr, 25, th) for tr in Q])
