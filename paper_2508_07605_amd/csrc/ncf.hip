@@ -19,17 +19,17 @@ namespace openk {
 
 constexpr int kNcfD = 32, kNcfH = 64;
 constexpr int kNcfMaxSteps = 100000;  // bounds a launch's run time
+constexpr int kNcfTwoPairs = 24;     // applications per CU above which a wavefront takes two pairs
 constexpr float kSeluAlpha = 1.6732632423543772f, kSeluLambda = 1.0507009873554805f;
 
+// both sides computed and selected: as branches, the 64 evaluations of a tile run one after the other
 __device__ __forceinline__ void selu_and_grad(float z, float &h, float &dh) {
-  if (z > 0.f) {
-    h = kSeluLambda * z;
-    dh = kSeluLambda;
-  } else {
-    const float ez = __expf(z);
-    h = kSeluLambda * kSeluAlpha * (ez - 1.f);
-    dh = kSeluLambda * kSeluAlpha * ez;
-  }
+  const float ez = __expf(z);
+  const float hn = kSeluLambda * kSeluAlpha * (ez - 1.f), dn = kSeluLambda * kSeluAlpha * ez;
+  const float hp = kSeluLambda * z;
+  const bool pos = z > 0.f;
+  h = pos ? hp : hn;
+  dh = pos ? kSeluLambda : dn;
 }
 
 __device__ __forceinline__ float wave_sum_f(float x) {
@@ -49,13 +49,11 @@ __global__ void k_ncf_table(const float *__restrict__ S, int n, const float *__r
   C[t] = acc;
 }
 
-// Observation tiles on FP32 MFMA (v_mfma_f32_32x32x2f32).  One wavefront per two applications:
-// the 32 MFMA columns hold 16 observations of each (lane j = l % 32 is column j, g = l / 32 the
-// half); the MFMA keeps columns apart, so each column simply carries its own application's
-// embedding.  Every 32 x 32 result holds, in register v of lane (j, g),
-// row 8 (v/4) + 4 g + v%4 of its block; hidden unit U(b, v, g) = 32 b + that row, embedding
-// index K(v, g) = that row.  Each product's contraction index is ordered so that its B operand
-// is a register the lane already holds:
+// Observation tiles on FP32 MFMA (v_mfma_f32_32x32x2f32), 32 columns to a tile; the MFMA keeps
+// columns apart, so each column simply carries its own application's embedding.  Every 32 x 32
+// result holds, in register v of lane (j, g), row 8 (v/4) + 4 g + v%4 of its block; hidden unit
+// U(b, v, g) = 32 b + that row, embedding index K(v, g) = that row.  Each product's contraction
+// index is ordered so that its B operand is a register the lane already holds:
 //   a   = W1e e         (64 x 32):  step s, half g <-> embedding K(s, g)   (e kept as e[K(v, g)])
 //   Z2  = W2 H1         (64 x 64):  step t, half g <-> hidden U(t/16, t%16, g)
 //   dH1 = W2^T dZ2      (64 x 64):  step t, half g <-> layer-2 unit U(t/16, t%16, g)
@@ -63,6 +61,19 @@ __global__ void k_ncf_table(const float *__restrict__ S, int n, const float *__r
 // so activations never move between lanes.  The A operands depend on the lane only and sit in
 // LDS once per block, slot-major so that consecutive lanes read consecutive 16-byte words.
 // DE's columns (observations) are summed across each application's 16 lanes of a half.
+//
+// Columns.  A wavefront takes NP pairs of applications of about the same length.  A pair's tile
+// holds 16 observations of each of its two (lane j = l % 32 is column j, g = l / 32 the half).
+// With NP = 2 a last part of at most 8 observations per application shares one tile among all
+// four: in each half of 16 columns, columns 0..7 belong to the first pair's application and
+// 8..15 to the second's.  a is computed once, in that shared layout, and a pair's tile takes it
+// from column 0 or 8 of each half as it adds it to the table row.
+// Bound by the matrix cores and the vector ALU, which share their time on FP32 products: a
+// 32 x 32 x 2 product next to 16 independent FMAs takes 109 cycles, 66 and 45 alone.  Per step
+// and four applications that is 160 products a tile and 32 for a: 192 up to 8 observations, 352
+// up to 16, 512 up to 24, where two wavefronts of one pair each need 384, 384 and 704; SELU is
+// evaluated once per unit, its derivative kept in the register of its argument.  65,536
+// applications of 4..24 observations, 30 steps: 10.2 -> 7.3 ms, 68 % of the time in products.
 constexpr int kNcfTA = 0, kNcfTF = 8, kNcfTB = 24, kNcfTE = 40, kNcfTW3 = 48, kNcfTB2 = 56, kNcfTSlots = 64;
 
 __device__ __forceinline__ f16 mfma32(float a, float b, f16 c) {
@@ -70,43 +81,64 @@ __device__ __forceinline__ f16 mfma32(float a, float b, f16 c) {
 }
 __device__ __forceinline__ int ncf_row(int v, int g) { return 8 * (v >> 2) + 4 * g + (v & 3); }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_ncf_foldin(int64_t m, const RowRef *__restrict__ list,
-                                                    const int32_t *__restrict__ col, const float *__restrict__ val,
-                                                    int n, const float *__restrict__ C, const float *__restrict__ W1,
-                                                    const float *__restrict__ W2, const float *__restrict__ b2,
-                                                    const float *__restrict__ w3, const float *__restrict__ b3,
-                                                    int steps, float eta, float mu, float *__restrict__ E,
-                                                    float *__restrict__ Lout, int32_t *__restrict__ status) {
+// lane moves within a row of 16 lanes
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;                // quad_perm
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;
+constexpr int kDppRor8 = 0x128, kDppBcast = 0x150;             // + column
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float x) {
+  const int i = __builtin_bit_cast(int, x);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, true));
+}
+// the sum over 8 and over 16 lanes, pairing lanes 1, 2, 4 and 8 apart (the mirrors meet the same
+// partial sums as those, since lanes already summed hold equal values)
+__device__ __forceinline__ float sum8(float x) {
+  x += dpp_mov<kDppXor1>(x);
+  x += dpp_mov<kDppXor2>(x);
+  x += dpp_mov<kDppHalfMirror>(x);
+  return x;
+}
+__device__ __forceinline__ float sum16(float x) {
+  x = sum8(x);
+  x += dpp_mov<kDppMirror>(x);
+  return x;
+}
+
+// `hi` from 8 lanes on, in the banks of four lanes of BANKS, `lo` in the others
+template <int BANKS>
+__device__ __forceinline__ float ror8_into(float lo, float hi) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, lo),
+                                                               __builtin_bit_cast(int, hi), kDppRor8, 0xf, BANKS,
+                                                               false));
+}
+
+template <int NP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_ncf_foldin(
+    int64_t m, const RowRef *__restrict__ list, const int32_t *__restrict__ col, const float *__restrict__ val, int n,
+    const float *__restrict__ C, const float *__restrict__ W1, const float *__restrict__ W2,
+    const float *__restrict__ b2, const float *__restrict__ w3, const float *__restrict__ b3, int steps, float eta,
+    float mu, float *__restrict__ E, float *__restrict__ Lout, int32_t *__restrict__ status) {
   // tab[slot][lane]: per-lane operands, four floats per slot
   __shared__ f4 tab[kNcfTSlots][kWave];
-  if (threadIdx.x < kWave) {
-    const int l = threadIdx.x, j = l & 31, g = l >> 5;
-    float *t = nullptr;
-    // a = W1e e: A[b][s] = W1e[32 b + j][K(s, g)]
-    for (int b = 0; b < 2; ++b)
-      for (int s = 0; s < 16; ++s) {
-        t = reinterpret_cast<float *>(&tab[kNcfTA + (16 * b + s) / 4][l]);
-        t[s & 3] = W1[(32 * b + j) * 2 * kNcfD + ncf_row(s, g)];
+  {
+    const int l = threadIdx.x & 63, j = l & 31, g = l >> 5;
+    auto put = [&](int slot, int q, float x) { reinterpret_cast<float *>(&tab[slot + q / 4][l])[q & 3] = x; };
+    for (int q = threadIdx.x >> 6; q < 32; q += 4) {
+      const int b = q >> 4, u = 32 * b + ncf_row(q & 15, g);
+      // a = W1e e: A[b][s] = W1e[32 b + j][K(s, g)]
+      put(kNcfTA, q, W1[(32 * b + j) * 2 * kNcfD + ncf_row(q & 15, g)]);
+      // Z2 = W2 H1: A[ob][t] = W2[32 ob + j][U(t)], and dH1 = W2^T dZ2: A[b][t] = W2[U(t)][32 b + j]
+#pragma unroll
+      for (int ob = 0; ob < 2; ++ob) {
+        put(kNcfTF, 32 * ob + q, W2[(32 * ob + j) * kNcfH + u]);
+        put(kNcfTB, 32 * ob + q, W2[u * kNcfH + 32 * ob + j]);
       }
-    // Z2 = W2 H1: A[ob][t] = W2[32 ob + j][U(t)], and dH1 = W2^T dZ2: A[b][t] = W2[U(t)][32 b + j]
-    for (int ob = 0; ob < 2; ++ob)
-      for (int q = 0; q < 32; ++q) {
-        const int u = 32 * (q >> 4) + ncf_row(q & 15, g);
-        reinterpret_cast<float *>(&tab[kNcfTF + (32 * ob + q) / 4][l])[q & 3] = W2[(32 * ob + j) * kNcfH + u];
-        reinterpret_cast<float *>(&tab[kNcfTB + (32 * ob + q) / 4][l])[q & 3] = W2[u * kNcfH + 32 * ob + j];
-      }
-    // DE = W1e^T dZ1: A[t] = W1e[U(t)][j]
-    for (int q = 0; q < 32; ++q) {
-      const int u = 32 * (q >> 4) + ncf_row(q & 15, g);
-      reinterpret_cast<float *>(&tab[kNcfTE + q / 4][l])[q & 3] = W1[u * 2 * kNcfD + j];
+      // DE = W1e^T dZ1: A[t] = W1e[U(t)][j]
+      put(kNcfTE, q, W1[u * 2 * kNcfD + j]);
+      // w3 and b2 at this lane's rows
+      put(kNcfTW3, q, w3[u]);
+      put(kNcfTB2, q, b2[u]);
     }
-    // w3 and b2 at this lane's rows
-    for (int b = 0; b < 2; ++b)
-      for (int v = 0; v < 16; ++v) {
-        const int u = 32 * b + ncf_row(v, g);
-        reinterpret_cast<float *>(&tab[kNcfTW3 + (16 * b + v) / 4][l])[v & 3] = w3[u];
-        reinterpret_cast<float *>(&tab[kNcfTB2 + (16 * b + v) / 4][l])[v & 3] = b2[u];
-      }
   }
   __syncthreads();
   const int lane = threadIdx.x & 63, jl = lane & 31, g = lane >> 5;
@@ -119,126 +151,203 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     return reinterpret_cast<const float *>(&tab[0][0])[((slot + q / 4) * kWave + lane + toff) * 4 + (q & 3)];
   };
 
-  // two applications per wavefront: columns 0..15 of every tile belong to the first, 16..31
-  // to the second (observations in tiles of 16 per application)
+  // columns 0..15 of a tile belong to the first application of a pair, 16..31 to the second;
+  // `second`: a column of the second pair in the shared layout
   const int half = jl >> 4, jc = jl & 15;
+  const bool second = NP == 2 && jc >= 8;
   const uint64_t appmask = 0x0000ffff0000ffffull << (16 * half);
-  const int64_t npairs = (m + 1) >> 1;
+  const int64_t ngroups = (m + 2 * NP - 1) / (2 * NP);
   const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-  for (int64_t pr = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); pr < npairs; pr += nw) {
-    const int64_t li = 2 * pr + half;  // this lane's application: entry li of the size-ordered list
-    const bool has = li < m;
-    const RowRef rec = has ? list[li] : RowRef{0, 0, 0};
-    const int64_t i = rec.row, beg = rec.beg, end = rec.beg + rec.cnt;
-    const int q = rec.cnt;
-    int st = q <= 0 ? 1 : 0;
-    {
+  // the last of the list, where the applications with the most tiles are, first
+  for (int64_t gr = ngroups - 1 - ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)); gr >= 0; gr -= nw) {
+    // the application of this lane's columns in each pair's tiles: its entries, cnt = 0 of them
+    // where it is refused
+    int64_t beg[NP];
+    int cnt[NP], st[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int64_t li = 2 * NP * gr + 2 * p + half;  // an entry of the size-ordered list
+      const RowRef rec = li < m ? list[li] : RowRef{0, 0, 0};
+      beg[p] = rec.beg;
+      st[p] = rec.cnt <= 0 ? 1 : 0;
       bool bad_idx = false, bad_val = false;
-      for (int64_t t = beg + jc + 16 * g; st == 0 && t < end; t += 32) {
-        const int j = col[t];
+      for (int t = jc + 16 * g; st[p] == 0 && t < rec.cnt; t += 32) {
+        const int j = col[beg[p] + t];
         bad_idx = bad_idx || j < 0 || j >= n;
-        bad_val = bad_val || !__builtin_isfinite(val[t]);
+        bad_val = bad_val || !__builtin_isfinite(val[beg[p] + t]);
       }
-      if (st == 0 && (__ballot(bad_idx) & appmask)) st = 5;
-      else if (st == 0 && (__ballot(bad_val) & appmask)) st = 3;
+      if (st[p] == 0 && (__ballot(bad_idx) & appmask)) st[p] = 5;
+      else if (st[p] == 0 && (__ballot(bad_val) & appmask)) st[p] = 3;
+      cnt[p] = st[p] == 0 ? rec.cnt : 0;
     }
-    const bool live = has && st == 0;
-    float e[16];  // e[v] = embedding K(v, g) of this lane's application
+    int qm = max(cnt[0], cnt[NP - 1]);
+    qm = __builtin_amdgcn_readfirstlane(max(qm, __shfl_xor(qm, 16, kWave)));
+    // tiles of 16 observations per application in each pair, then the shared one
+    const int shared = NP == 2 && (qm & 15) >= 1 && (qm & 15) <= 8 ? 1 : 0;
+    const int full = (qm >> 4) + ((qm & 15) && !shared ? 1 : 0);
+    const int ntiles = NP * full + shared;
+    const int cnt_own = second ? cnt[NP - 1] : cnt[0];
+    const bool live_own = cnt_own > 0;
+    float e[16];  // e[v] = embedding K(v, g) of this column's application in the shared layout
 #pragma unroll
     for (int v = 0; v < 16; ++v) e[v] = 0.f;
     float lossv = 0.f;
-    const int qt = live ? (q + 15) >> 4 : 0;
-    const int ntiles = max(qt, __shfl_xor(qt, 16, kWave));  // the same in every lane
-    if (ntiles > 0) {
-      const float inv_q = live ? 1.f / (float)q : 0.f;
-      for (int it = 0; it <= steps; ++it) {
-        // a at this lane's hidden units
+    for (int it = 0; ntiles > 0 && it <= steps; ++it) {
+      // a at this lane's hidden units
+      asm volatile("" : "+v"(toff));
+      f16 a[2] = {};
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int s2 = 0; s2 < 16; ++s2) a[b] = mfma32(T(kNcfTA, 16 * b + s2), e[s2], a[b]);
+      // sums of the tiles under way, and those set aside: the first pair's, then, under the shared
+      // tile, both pairs' columns 8..15 (the second's in lanes 0..7)
+      f16 de = {}, aside = {};
+      float sq = 0.f, sq_aside = 0.f;
+      for (int x = 0; x < ntiles; ++x) {
         asm volatile("" : "+v"(toff));
-        f16 a[2] = {};
+        const int part = x < full ? 0 : x < NP * full ? 1 : 2;  // first pair, second pair, shared
+        int64_t t0;
+        int t, q;
+        if (NP == 2 && part == 2) {
+          t0 = second ? beg[NP - 1] : beg[0];
+          t = 16 * full + (jc & 7);
+          q = cnt_own;
+          if (full > 0) {  // the shared columns go on from the pairs' sums
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              const float d1 = de[v];
+              de[v] = ror8_into<0xc>(aside[v], d1);
+              aside[v] = ror8_into<0x3>(aside[v], d1);
+            }
+            const float s1 = sq;
+            sq = ror8_into<0xc>(sq_aside, s1);
+            sq_aside = ror8_into<0x3>(sq_aside, s1);
+          }
+        } else {
+          if (NP == 2 && x == full) {
+            aside = de;
+            sq_aside = sq;
+            de = f16{};
+            sq = 0.f;
+          }
+          t0 = part ? beg[NP - 1] : beg[0];
+          t = 16 * (x - part * full) + jc;
+          q = part ? cnt[NP - 1] : cnt[0];
+        }
+        const bool valid = t < q;
+        const float *crow = C + (int64_t)(valid ? col[t0 + t] : 0) * kNcfH;
+        const float r = valid ? val[t0 + t] : 0.f;
+        // forward: Z2 = b2 + W2 SELU(a + c)
+        f16 z2[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-          for (int s2 = 0; s2 < 16; ++s2) a[b] = mfma32(T(kNcfTA, 16 * b + s2), e[s2], a[b]);
-        f16 de = {};
-        float sq = 0.f;
-        for (int tt = 0; tt < ntiles; ++tt) {
-          asm volatile("" : "+v"(toff));
-          const int64_t t = beg + 16 * tt + jc;
-          const bool valid = live && t < end;
-          const float *crow = C + (int64_t)(valid ? col[t] : 0) * kNcfH;
-          const float r = valid ? val[t] : 0.f;
-          // forward: Z2 = b2 + W2 SELU(a + c)
-          f16 z2[2];
+          for (int v = 0; v < 16; ++v) z2[b][v] = T(kNcfTB2, 16 * b + v);
+        float cz[32];
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
+        for (int q2 = 0; q2 < 32; ++q2) cz[q2] = crow[32 * (q2 >> 4) + ncf_row(q2 & 15, g)];
+        if (NP == 1 || part == 2) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) z2[b][v] = T(kNcfTB2, 16 * b + v);
-          float cz[32];
+          for (int q2 = 0; q2 < 32; ++q2) cz[q2] += a[q2 >> 4][q2 & 15];
+        } else if (part == 0) {
 #pragma unroll
-          for (int q2 = 0; q2 < 32; ++q2) cz[q2] = crow[32 * (q2 >> 4) + ncf_row(q2 & 15, g)];
+          for (int q2 = 0; q2 < 32; ++q2) cz[q2] += dpp_mov<kDppBcast>(a[q2 >> 4][q2 & 15]);
+        } else {
 #pragma unroll
-          for (int q2 = 0; q2 < 32; ++q2) {
-            float h1;
-            selu_and_grad(a[q2 >> 4][q2 & 15] + cz[q2], h1, cz[q2]);  // cz now holds SELU'(z1)
+          for (int q2 = 0; q2 < 32; ++q2) cz[q2] += dpp_mov<kDppBcast + 8>(a[q2 >> 4][q2 & 15]);
+        }
 #pragma unroll
-            for (int ob = 0; ob < 2; ++ob) z2[ob] = mfma32(T(kNcfTF, 32 * ob + q2), h1, z2[ob]);
-          }
-          // output and residual of this column's observation (each half holds half of the sum)
-          float yp = 0.f;
+        for (int q2 = 0; q2 < 32; ++q2) {
+          float h1;
+          selu_and_grad(cz[q2], h1, cz[q2]);  // cz now holds SELU'(z1)
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
+          for (int ob = 0; ob < 2; ++ob) z2[ob] = mfma32(T(kNcfTF, 32 * ob + q2), h1, z2[ob]);
+        }
+        // the derivatives are computed here and not where they are used: that would keep the 64
+        // comparisons instead
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              float h2, d2;
-              selu_and_grad(z2[b][v], h2, d2);
-              yp = __builtin_fmaf(T(kNcfTW3, 16 * b + v), h2, yp);
-            }
-          const float y = yp + __shfl_xor(yp, 32, kWave) + bias3;
-          const float res = valid ? y - r : 0.f;
-          sq = __builtin_fmaf(res, res, sq);
-          if (it == steps) continue;  // the last pass only evaluates the loss
-          // backward: dH1 = W2^T dZ2, dZ2 = (2 res / q) w3 SELU'(z2)
-          const float dy = 2.f * res * inv_q;
-          f16 dh1[2] = {};
+        for (int q2 = 0; q2 < 32; ++q2) asm volatile("" : "+v"(cz[q2]));
+        // output and residual of this column's observation (each half holds half of the sum)
+        float yp = 0.f;
 #pragma unroll
-          for (int q2 = 0; q2 < 32; ++q2) {
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
             float h2, d2;
-            selu_and_grad(z2[q2 >> 4][q2 & 15], h2, d2);
-            const float dz2 = dy * T(kNcfTW3, q2) * d2;
-#pragma unroll
-            for (int b = 0; b < 2; ++b) dh1[b] = mfma32(T(kNcfTB, 32 * b + q2), dz2, dh1[b]);
+            selu_and_grad(z2[b][v], h2, d2);
+            z2[b][v] = d2;  // z2 now holds SELU'(z2)
+            yp = __builtin_fmaf(T(kNcfTW3, 16 * b + v), h2, yp);
           }
-          // DE += W1e^T (dH1 * SELU'(a + c))
 #pragma unroll
-          for (int q2 = 0; q2 < 32; ++q2) de = mfma32(T(kNcfTE, q2), dh1[q2 >> 4][q2 & 15] * cz[q2], de);
+        for (int q2 = 0; q2 < 32; ++q2) {
+          float d2 = z2[q2 >> 4][q2 & 15];
+          asm volatile("" : "+v"(d2));
+          z2[q2 >> 4][q2 & 15] = d2;
         }
-        if (it == steps) {
-          float ee = 0.f;
+        const float y = yp + __shfl_xor(yp, 32, kWave) + bias3;
+        const float res = valid ? y - r : 0.f;
+        sq = __builtin_fmaf(res, res, sq);
+        if (it == steps) continue;  // the last pass only evaluates the loss
+        // backward: dH1 = W2^T dZ2, dZ2 = (2 res / q) w3 SELU'(z2)
+        const float dy = 2.f * res * (q > 0 ? 1.f / (float)q : 0.f);
+        f16 dh1[2] = {};
 #pragma unroll
-          for (int v = 0; v < 16; ++v) ee = __builtin_fmaf(e[v], e[v], ee);
-          // squared residuals: one per column in each half; embedding: each half holds 16 indices
-          float sqt = g == 0 ? sq : 0.f;
+        for (int q2 = 0; q2 < 32; ++q2) {
+          const float dz2 = dy * T(kNcfTW3, q2) * z2[q2 >> 4][q2 & 15];
 #pragma unroll
-          for (int off = 1; off < 16; off <<= 1) sqt += __shfl_xor(sqt, off, kWave);
-          lossv = sqt * inv_q + mu * (ee + __shfl_xor(ee, 32, kWave));
-          break;
+          for (int b = 0; b < 2; ++b) dh1[b] = mfma32(T(kNcfTB, 32 * b + q2), dz2, dh1[b]);
         }
-        // sum DE over the application's 16 columns, then the step
+        // DE += W1e^T (dH1 * SELU'(a + c))
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float x = de[v];
+        for (int q2 = 0; q2 < 32; ++q2) de = mfma32(T(kNcfTE, q2), dh1[q2 >> 4][q2 & 15] * cz[q2], de);
+      }
+      // the squared residuals and DE summed over each application's 16 columns: the pairs' own
+      // columns, the first 8 of them as the shared tile left them
+      const bool alone = shared && full == 0;  // the shared tile is all there is
+      auto first_of = [&](float d, float as) { return shared && !second ? d : as; };
+      auto second_of = [&](float d, float as) { return shared ? dpp_mov<kDppRor8>(second ? d : as) : d; };
+      if (it == steps) {
+        float ee = 0.f;
 #pragma unroll
-          for (int off = 1; off < 16; off <<= 1) x += __shfl_xor(x, off, kWave);
-          if (live) e[v] -= eta * (x + 2.f * mu * e[v]);
+        for (int v = 0; v < 16; ++v) ee = __builtin_fmaf(e[v], e[v], ee);
+        // squared residuals: one per column in each half; embedding: each half holds 16 indices
+        float sqt;
+        if (NP == 1) {
+          sqt = sum16(g == 0 ? sq : 0.f);
+        } else if (alone) {
+          sqt = sum8(g == 0 ? sq : 0.f);
+        } else {
+          const float s0 = sum16(g == 0 ? first_of(sq, sq_aside) : 0.f);
+          const float s1 = sum16(g == 0 ? second_of(sq, sq_aside) : 0.f);
+          sqt = second ? s1 : s0;
         }
+        const float iq = live_own ? 1.f / (float)cnt_own : 0.f;
+        lossv = sqt * iq + mu * (ee + __shfl_xor(ee, 32, kWave));
+        break;
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        float s;
+        if (NP == 1) {
+          s = sum16(de[v]);
+        } else if (alone) {
+          s = sum8(de[v]);
+        } else {
+          const float s0 = sum16(first_of(de[v], aside[v])), s1 = sum16(second_of(de[v], aside[v]));
+          s = second ? s1 : s0;
+        }
+        if (live_own) e[v] -= eta * (s + 2.f * mu * e[v]);
       }
     }
-    if (has && jc == 0) {
+    const int64_t li = 2 * NP * gr + 2 * (second ? 1 : 0) + half;
+    if (li < m && (jc & (NP == 2 ? 7 : 15)) == 0) {
+      const int64_t i = list[li].row;
 #pragma unroll
       for (int v = 0; v < 16; ++v) E[i * kNcfD + ncf_row(v, g)] = e[v];
       if (g == 0) {
-        if (Lout) Lout[i] = live ? lossv : 0.f;
-        if (status) status[i] = st;
+        if (Lout) Lout[i] = live_own ? lossv : 0.f;
+        if (status) status[i] = second ? st[NP - 1] : st[0];
       }
     }
   }
@@ -706,11 +815,15 @@ extern "C" open_status open_ncf_foldin(open_ctx *ctx, const float *S, int32_t n,
   RowRef *list = nullptr;
   int64_t *cls = nullptr;
   if ((st = bucket_rows(ctx, m, row_ptr, kNcfD, &list, &cls, kSplitMin))) return st;
-  const int64_t cap = (int64_t)ctx->num_cu * 16;  // waves
-  const int64_t pairs = (m + 1) / 2;  // two applications per wavefront
-  const int64_t waves = pairs < cap ? pairs : cap;
-  OPEN_LAUNCH(ctx, "ncf_foldin", k_ncf_foldin, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, m,
-              (const RowRef *)list, col, val, n, (const float *)tab, W1, W2, b2, w3, b3, steps, eta, mu, E_out,
-              loss_out, row_status);
+  // two pairs per wavefront once the pairs alone give every SIMD its two wavefronts and more: at
+  // 8192 applications of 4..24 observations, 30 steps, 1062 us against 1343, at 6000 1053 against
+  // 1081, at 4096 (one wavefront per SIMD, longer) 755 against 648
+  const int64_t cap = (int64_t)ctx->num_cu * 64;  // waves, all blocks handed out as they end
+  const bool two = m > (int64_t)ctx->num_cu * kNcfTwoPairs;
+  const int64_t groups = two ? (m + 3) / 4 : (m + 1) / 2;
+  const int64_t waves = groups < cap ? groups : cap;
+  OPEN_LAUNCH(ctx, "ncf_foldin", (two ? k_ncf_foldin<2> : k_ncf_foldin<1>), dim3((unsigned)((waves + 3) / 4)),
+              dim3(256), 0, m, (const RowRef *)list, col, val, n, (const float *)tab, W1, W2, b2, w3, b3, steps, eta,
+              mu, E_out, loss_out, row_status);
   return OPEN_OK;
 }
