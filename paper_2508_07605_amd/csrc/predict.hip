@@ -13,6 +13,13 @@
 //            ties; the saving (E_base - E) / E_base with E = (c_s + g_s) / p of the pick
 // Each lane scans its own settings in ascending order; the 32 lanes of a half-wave are then
 // combined by (E, s) in a butterfly.  The full prediction P is written only when asked.
+//
+// Bound by the FP32 matrix products, 32 of 66 cycles a block of 32 x 32 at rank 64, to which the
+// vector ALU's share adds (the two do not overlap): so the scan is five vector operations per
+// element (the prediction of the pick is formed again at the end instead of carried), loads and
+// stores of V need no address arithmetic, and 1 / (c_s + g_s) is formed once per block of threads.
+// Without the row pointers of P and the baselines four wavefronts fit per SIMD.  1,000,003 x 1920
+// at rank 64: 2957 -> 2100 us, the products alone 1640; 1,000,000 x 120 at rank 32: 438 -> 186.
 #include <math.h>
 
 #include "common.h"
@@ -21,24 +28,27 @@ namespace openk {
 
 typedef float f16v __attribute__((ext_vector_type(16)));
 
-// V block s0 (32 settings x K) as K/8 floats per thread of a 256-thread block: load from global,
-// then store transposed into LDS at stride LD (settings past n read as zero)
+// V block s0 (32 settings x K) as K/8 floats per thread of a 256-thread block: load from global
+// through a buffer resource over the settings that are left (past the last one: zeros), then
+// store transposed into LDS at stride LD
 template <int K>
 __device__ __forceinline__ void load_block(float (&t)[K / 8], const float *__restrict__ V, int n, int s0) {
+  const int left = min(n - s0, 32);
+  const __amdgpu_buffer_rsrc_t rv = make_rsrc(V + (int64_t)s0 * K, (uint64_t)left * K * 4);
 #pragma unroll
-  for (int i = 0; i < K / 8; ++i) {
-    const int e = threadIdx.x + 256 * i, j = e / K, kk = e % K;
-    t[i] = (s0 + j < n) ? V[(int64_t)(s0 + j) * K + kk] : 0.f;
-  }
+  for (int i = 0; i < K / 8; ++i) t[i] = bload_f32(rv, (int)(threadIdx.x + 256 * i) * 4);
 }
 template <int K>
 __device__ __forceinline__ void store_block(float *Vt, const float (&t)[K / 8]) {
   constexpr int LD = 33;
+  float *d = Vt + (threadIdx.x % K) * LD + threadIdx.x / K;
 #pragma unroll
-  for (int i = 0; i < K / 8; ++i) {
-    const int e = threadIdx.x + 256 * i, j = e / K, kk = e % K;
-    Vt[kk * LD + j] = t[i];
-  }
+  for (int i = 0; i < K / 8; ++i) d[i * (256 / K)] = t[i];
+}
+// 1 / (c + g) of setting s by the block's first 32 threads, NaN past the last one
+__device__ __forceinline__ void store_weight(float *iw, const float *__restrict__ cap_c,
+                                             const float *__restrict__ cap_g, int n, int s) {
+  if (threadIdx.x < 32) iw[threadIdx.x] = s < n ? 1.0f / (cap_c[s] + cap_g[s]) : __builtin_nanf("");
 }
 
 template <int K>
@@ -65,8 +75,32 @@ __device__ __forceinline__ float least_valid(float pb, float gamma) {
   return t;
 }
 
-template <int K>
-__global__ __launch_bounds__(256) void k_predict_select(const float *__restrict__ U, int64_t m,
+// lane moves within a row of 16 lanes: neighbours, pairs, and the mirrors, which once lanes hold
+// equal values in fours and eights reach the same partners as 4 and 8 lanes apart
+template <int CTRL, class T>
+__device__ __forceinline__ T dpp_get(T x) {
+  const int i = __builtin_bit_cast(int, x);
+  return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, true));
+}
+// greatest key, then lowest setting, of two lanes
+__device__ __forceinline__ void take_better(float &k, int &s, float k2, int s2) {
+  const bool take = s2 >= 0 && (s < 0 || k2 > k || (k2 == k && s2 < s));
+  k = take ? k2 : k;
+  s = take ? s2 : s;
+}
+// x[v] by a lane's own v
+__device__ __forceinline__ float pick16(f16v x, int v) {
+  float y = x[0];
+#pragma unroll
+  for (int i = 1; i < 16; ++i) {
+    const float xi = x[i];
+    y = v == i ? xi : y;
+  }
+  return y;
+}
+
+template <int K, bool WP>
+__global__ __launch_bounds__(256, WP ? 3 : 4) void k_predict_select(const float *__restrict__ U, int64_t m,
                                                         const float *__restrict__ V, int n,
                                                         const float *__restrict__ cap_c,
                                                         const float *__restrict__ cap_g, int base, float gamma,
@@ -74,7 +108,7 @@ __global__ __launch_bounds__(256) void k_predict_select(const float *__restrict_
                                                         float *__restrict__ best_saving,
                                                         int32_t *__restrict__ status) {
   constexpr int H = K / 2, LD = 33;
-  __shared__ float Vt[2][K * LD];
+  __shared__ float Vt[2][K * LD], iwt[2][32];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int r = lane & 31, h = lane >> 5;
   const int64_t row0 = ((int64_t)blockIdx.x * 4 + w) * 32;
@@ -89,29 +123,35 @@ __global__ __launch_bounds__(256) void k_predict_select(const float *__restrict_
     a[s + 2] = x[2];
     a[s + 3] = x[3];
   }
-  // rows of this lane's 16 accumulators: 8*(v/4) + 4*h + v%4
+  // the lane's 16 accumulators are rows 8*(v/4) + 4*h + v%4; row r is register vr of half hr
+  const int hr = (r >> 2) & 1, vr = (r >> 3) * 4 + (r & 3);
   // baseline prediction from the same MFMA tile the scan uses
   const int sb0 = (base / 32) * 32, jb = base - sb0;
   float tb[K / 8];
   load_block<K>(tb, V, n, sb0);
   store_block<K>(Vt[1], tb);
   load_block<K>(tb, V, n, 0);  // the scan's first block
+  store_weight(iwt[0], cap_c, cap_g, n, r);
   __syncthreads();
-  float pb[16], thr[16];
+  // per row: valid(p) <=> p >= thr (thr > 0, so p > 0 follows; NaN when p_base <= 0: never).
+  // Each lane finds its row r's, then the lanes of a half read those of its 16 rows.
+  float thr[16];
   {
     const f16v acc = tile<K>(a, Vt[1], r, h);
+    f16v pb;
 #pragma unroll
     for (int v = 0; v < 16; ++v) pb[v] = __shfl(acc[v], jb + 32 * h, 64);
-  }
-  // per row: valid(p) <=> p >= thr (thr > 0, so p > 0 follows; NaN when p_base <= 0: never)
+    const float own = pick16(pb, vr), other = __shfl_xor(own, 32, 64);
+    const float pbr = h == hr ? own : other;
+    const float t = pbr > 0.f ? least_valid(pbr, gamma) : __builtin_nanf("");
 #pragma unroll
-  for (int v = 0; v < 16; ++v) thr[v] = pb[v] > 0.f ? least_valid(pb[v], gamma) : __builtin_nanf("");
-  float bK[16], bP[16];  // the best key and its prediction
+    for (int v = 0; v < 16; ++v) thr[v] = __shfl(t, 8 * (v / 4) + 4 * h + (v % 4), 64);
+  }
+  float bK[16];  // the best key and its setting
   int bS[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     bK[v] = -__builtin_inff();
-    bP[v] = 0.f;
     bS[v] = -1;
   }
   store_block<K>(Vt[0], tb);
@@ -121,18 +161,20 @@ __global__ __launch_bounds__(256) void k_predict_select(const float *__restrict_
   // into the other buffer and block i + 2 loads into registers; one barrier per block.
   for (int s0 = 0, i = 0; s0 < n; s0 += 32, ++i) {
     const f16v acc = tile<K>(a, Vt[i & 1], r, h);
-    if (s0 + 32 < n) store_block<K>(Vt[(i + 1) & 1], tb);
+    if (s0 + 32 < n) {
+      store_block<K>(Vt[(i + 1) & 1], tb);
+      store_weight(iwt[(i + 1) & 1], cap_c, cap_g, n, s0 + 32 + r);
+    }
     if (s0 + 64 < n) load_block<K>(tb, V, n, s0 + 64);
     const int sc = s0 + r;
-    const bool colok = sc < n;
-    const int scl = colok ? sc : n - 1;
-    // past the last setting the key is NaN and never taken
-    const float iw = colok ? 1.0f / (cap_c[scl] + cap_g[scl]) : __builtin_nanf("");
-    if (P) {
+    const float iw = iwt[i & 1][r];  // past the last setting the key is NaN and never taken
+    if (WP && sc < n) {
+      float *prow = P + (row0 + 4 * h) * n + sc;
+      const int64_t left = m - row0 - 4 * h;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int64_t row = row0 + 8 * (v / 4) + 4 * h + (v % 4);
-        if (colok && row < m) P[row * n + sc] = acc[v];
+        const int rv = 8 * (v / 4) + (v % 4);
+        if (rv < left) prow[(int64_t)rv * n] = acc[v];
       }
     }
     // branch-free: greatest key p * iw among valid settings, the lane's settings in ascending
@@ -143,40 +185,45 @@ __global__ __launch_bounds__(256) void k_predict_select(const float *__restrict_
       const float key = p * iw;
       const bool better = p >= thr[v] && key > bK[v];
       bK[v] = better ? key : bK[v];
-      bP[v] = better ? p : bP[v];
       bS[v] = better ? sc : bS[v];
     }
     __syncthreads();
   }
-  // combine the 32 column lanes of each half-wave: greatest key, then lowest s
+  // combine the 32 column lanes of each half-wave
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
-#pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) {
-      const float K2 = __shfl_xor(bK[v], off, 64);
-      const float P2 = __shfl_xor(bP[v], off, 64);
-      const int S2 = __shfl_xor(bS[v], off, 64);
-      const bool take = S2 >= 0 && (bS[v] < 0 || K2 > bK[v] || (K2 == bK[v] && S2 < bS[v]));
-      bK[v] = take ? K2 : bK[v];
-      bP[v] = take ? P2 : bP[v];
-      bS[v] = take ? S2 : bS[v];
-    }
+    take_better(bK[v], bS[v], dpp_get<0xB1>(bK[v]), dpp_get<0xB1>(bS[v]));
+    take_better(bK[v], bS[v], dpp_get<0x4E>(bK[v]), dpp_get<0x4E>(bS[v]));
+    take_better(bK[v], bS[v], dpp_get<0x141>(bK[v]), dpp_get<0x141>(bS[v]));
+    take_better(bK[v], bS[v], dpp_get<0x140>(bK[v]), dpp_get<0x140>(bS[v]));
+    take_better(bK[v], bS[v], __shfl_xor(bK[v], 16, 64), __shfl_xor(bS[v], 16, 64));
   }
-  if (r == 0) {
-    const float ebase = cap_c[base] + cap_g[base];
+  // Row r's pick goes to both lanes r, and its prediction is formed once more, on the diagonal of
+  // a tile whose column r is row r's pick: the same products in the same order give the scan's
+  // bits, at the price of one block, where carrying it along would be 16 selects in every block.
+  f16v picks;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int64_t row = row0 + 8 * (v / 4) + 4 * h + (v % 4);
-      if (row >= m) continue;
-      const bool okb = pb[v] > 0.f && bS[v] >= 0;
-      best_idx[row] = okb ? bS[v] : base;
-      if (best_saving) {
-        const int sb = okb ? bS[v] : base;
-        const float E = (cap_c[sb] + cap_g[sb]) / bP[v];
-        best_saving[row] = okb ? (ebase - E) / ebase : 0.f;
-      }
-      if (status) status[row] = okb ? OPEN_ROW_OK : OPEN_ROW_NONPOS_BASE;
+  for (int v = 0; v < 16; ++v) picks[v] = __builtin_bit_cast(float, bS[v]);
+  const int own = __builtin_bit_cast(int, pick16(picks, vr)), other = __shfl_xor(own, 32, 64);
+  const int pick = h == hr ? own : other;
+  const bool okb = pick >= 0;  // never where p_base <= 0
+  const int sb = okb ? pick : base;
+  float p = 0.f;
+  if (best_saving) {
+    f16v acc = {};
+    const float *vs = V + (int64_t)sb * K + h * H;
+#pragma unroll
+    for (int s = 0; s < H; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], vs[s], acc, 0, 0, 0);
+    p = pick16(acc, vr);
+  }
+  if (h == hr && grow < m) {
+    best_idx[grow] = sb;
+    if (best_saving) {
+      const float ebase = cap_c[base] + cap_g[base];
+      const float E = (cap_c[sb] + cap_g[sb]) / p;
+      best_saving[grow] = okb ? (ebase - E) / ebase : 0.f;
     }
+    if (status) status[grow] = okb ? OPEN_ROW_OK : OPEN_ROW_NONPOS_BASE;
   }
 }
 
@@ -198,20 +245,20 @@ extern "C" open_status open_predict(open_ctx *ctx, const float *U, int64_t m, co
   const dim3 grid((unsigned)((m + 127) / 128)), block(256);
   switch (k) {
     case 8:
-      OPEN_LAUNCH(ctx, "predict_select_k8", k_predict_select<8>, grid, block, 0, U, m, V, n, cap_cpu, cap_gpu, base,
-                  gamma, P, best_idx, best_saving, row_status);
+      OPEN_LAUNCH(ctx, "predict_select_k8", (P ? k_predict_select<8, true> : k_predict_select<8, false>), grid, block,
+                  0, U, m, V, n, cap_cpu, cap_gpu, base, gamma, P, best_idx, best_saving, row_status);
       break;
     case 16:
-      OPEN_LAUNCH(ctx, "predict_select_k16", k_predict_select<16>, grid, block, 0, U, m, V, n, cap_cpu, cap_gpu, base,
-                  gamma, P, best_idx, best_saving, row_status);
+      OPEN_LAUNCH(ctx, "predict_select_k16", (P ? k_predict_select<16, true> : k_predict_select<16, false>), grid,
+                  block, 0, U, m, V, n, cap_cpu, cap_gpu, base, gamma, P, best_idx, best_saving, row_status);
       break;
     case 32:
-      OPEN_LAUNCH(ctx, "predict_select_k32", k_predict_select<32>, grid, block, 0, U, m, V, n, cap_cpu, cap_gpu, base,
-                  gamma, P, best_idx, best_saving, row_status);
+      OPEN_LAUNCH(ctx, "predict_select_k32", (P ? k_predict_select<32, true> : k_predict_select<32, false>), grid,
+                  block, 0, U, m, V, n, cap_cpu, cap_gpu, base, gamma, P, best_idx, best_saving, row_status);
       break;
     default:
-      OPEN_LAUNCH(ctx, "predict_select_k64", k_predict_select<64>, grid, block, 0, U, m, V, n, cap_cpu, cap_gpu, base,
-                  gamma, P, best_idx, best_saving, row_status);
+      OPEN_LAUNCH(ctx, "predict_select_k64", (P ? k_predict_select<64, true> : k_predict_select<64, false>), grid,
+                  block, 0, U, m, V, n, cap_cpu, cap_gpu, base, gamma, P, best_idx, best_saving, row_status);
       break;
   }
   return OPEN_OK;
