@@ -19,6 +19,13 @@
 //            the layer-1 result already holds in that lane, 32 bk + 8 (2p + t/4) + 4 g + t%4,
 //            so h1 feeds the next MFMA without moving between lanes; W2 is permuted to match.
 //   layer 3: a per-lane dot product over the 32 held units, then the two halves are added.
+//
+// Bound by the matrix products (18 a tile: 258 GFLOP for 14,000,003 runs, 225 us at the rate of a
+// large product on this card) with about 270 vector operations a tile between them: moving a
+// quarter of those to products, or two to five wavefronts per SIMD, leaves the time as it is
+// within 3 %.  The features, 28 bytes a run, are read in whole lines and turned through LDS; the
+// seven strided reads a tile that this replaces, and b2 and w3 read from LDS in every tile, took
+// 9 % of the time.  14,000,003 runs: 334 -> 306 us.
 #include "common.h"
 
 namespace openk {
@@ -33,7 +40,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   const pbf16x2 v = {(__bf16)a, (__bf16)b};
   return __builtin_bit_cast(uint32_t, v);
 }
-// a = hi + lo (bfloat16 parts, packed in pairs); the remainder is exact in float32
+// a = hi + lo (bfloat16 parts, packed in pairs)
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t &hi, uint32_t &lo) {
   hi = pack_bf16(a, b);
   const float ha = __builtin_bit_cast(float, hi << 16), hb = __builtin_bit_cast(float, hi & 0xffff0000u);
@@ -50,7 +57,7 @@ __device__ __forceinline__ f16 mfma_bf16(uint4 a, uint4 b, f16 c) {
                                                  0, 0, 0);
 }
 
-__global__ __launch_bounds__(256) void k_perf_predict(int64_t n, const float *__restrict__ X,
+__global__ __launch_bounds__(256, 3) void k_perf_predict(int64_t n, const float *__restrict__ X,
                                                       const float *__restrict__ mu, const float *__restrict__ rs,
                                                       const float *__restrict__ W1, const float *__restrict__ b1,
                                                       const float *__restrict__ W2, const float *__restrict__ b2,
@@ -85,14 +92,6 @@ __global__ __launch_bounds__(256) void k_perf_predict(int64_t n, const float *__
     }
     la2[ob][s][l] = uint4{qq[0], qq[1], qq[2], qq[3]};
   }
-  // b2 and w3 stay in LDS (read per tile, four consecutive rows at a time), which keeps the
-  // register count low enough for more wavefronts per SIMD
-  __shared__ f4 lb2[16], lw3[16];
-  if (threadIdx.x < 64) {
-    reinterpret_cast<float *>(lb2)[threadIdx.x] = b2[threadIdx.x];
-  } else if (threadIdx.x < 128) {
-    reinterpret_cast<float *>(lw3)[threadIdx.x - 64] = w3[threadIdx.x - 64];
-  }
   __syncthreads();
   float muf[kPF], rsf[kPF];
 #pragma unroll
@@ -101,75 +100,85 @@ __global__ __launch_bounds__(256) void k_perf_predict(int64_t n, const float *__
     rsf[f] = rs[f];
   }
   const float bias3 = b3[0];
+  f16 rb2[2], rw3[2];  // b2 and w3 at the lane's rows
+#pragma unroll
+  for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int r = 32 * ob + 8 * (v / 4) + 4 * g + v % 4;
+      rb2[ob][v] = b2[r];
+      rw3[ob][v] = w3[r];
+    }
 
   const int64_t ntiles = (n + 31) >> 5;
   const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-  const int64_t tile0 = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  // the features of the next tile are loaded while the current one is computed
-  float xn[kPF];
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t tile0 = (int64_t)blockIdx.x * (blockDim.x >> 6) + wv;
+  // a tile's features, in the order of memory, through a buffer resource over its runs (past the
+  // last one: zeros), the next tile's loaded while the current one is computed
+  float xn[4];
+  __shared__ float xs_all[4][256];  // per wavefront: the tile's 32 x 7 features
+  float *xs = xs_all[wv];
+  auto load = [&](int64_t tile) {
+    const int64_t left = n - (tile << 5);
+    const int runs = left >= 32 ? 32 : left > 0 ? (int)left : 0;
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(X + (runs > 0 ? (tile << 5) * kPF : 0), (uint64_t)runs * kPF * 4);
 #pragma unroll
-  for (int f = 0; f < kPF; ++f) xn[f] = (tile0 << 5) + i32 < n ? X[((tile0 << 5) + i32) * kPF + f] : 0.f;
+    for (int f = 0; f < 4; ++f) xn[f] = bload_f32(rx, (lane + 64 * f) * 4);
+  };
+  load(tile0);
   for (int64_t tile = tile0; tile < ntiles; tile += nw) {
-    const int64_t e = (tile << 5) + i32, en = ((tile + nw) << 5) + i32;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) xs[lane + 64 * f] = xn[f];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     float z[8];
-    bool finite = true;
+    float zero = 0.f;  // stays zero for finite features, NaN otherwise
 #pragma unroll
     for (int f = 0; f < kPF; ++f) {
-      const float x = xn[f];
-      xn[f] = en < n ? X[en * kPF + f] : 0.f;
-      finite = finite && __builtin_isfinite(x);
-      z[f] = (x - muf[f]) * rsf[f];
+      const float xf = xs[i32 * kPF + f];
+      zero = __builtin_fmaf(xf, 0.f, zero);
+      z[f] = (xf - muf[f]) * rsf[f];
     }
     z[7] = 1.f;  // multiplies the layer-1 bias parts
+    load(tile + nw);
     uint32_t hi[4], lo[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) split_pair(z[2 * u], z[2 * u + 1], hi[u], lo[u]);
     lo[3] = (lo[3] & 0xffffu) | 0x3f800000u;  // slot 7 is 1 in both halves
     const uint4 bx = g == 0 ? uint4{hi[0], hi[1], hi[2], hi[3]} : uint4{lo[0], lo[1], lo[2], lo[3]};
-    f16 d1[2];
+    // layer 1, rectified and split: hh/hl[4 s + u] are slots 2 u, 2 u + 1 of step s
+    uint32_t hh[16], hl[16];
 #pragma unroll
-    for (int bk = 0; bk < 2; ++bk) d1[bk] = mfma_bf16(a1[bk], bx, f16{});
-    f16 d2[2];
+    for (int bk = 0; bk < 2; ++bk) {
+      const f16 d1 = mfma_bf16(a1[bk], bx, f16{});
 #pragma unroll
-    for (int ob = 0; ob < 2; ++ob)
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {  // rows 32 ob + 8 a + 4 g + 0..3
-        const f4 b = lb2[8 * ob + 2 * a + g];
-        d2[ob][4 * a] = b[0];
-        d2[ob][4 * a + 1] = b[1];
-        d2[ob][4 * a + 2] = b[2];
-        d2[ob][4 * a + 3] = b[3];
-      }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int bk = s >> 1, p = s & 1;
-      uint32_t hh[4], hl[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float x0 = relu(d1[bk][8 * p + 2 * u]);
-        const float x1 = relu(d1[bk][8 * p + 2 * u + 1]);
-        split_pair(x0, x1, hh[u], hl[u]);
-      }
-      const uint4 bh = uint4{hh[0], hh[1], hh[2], hh[3]}, bl = uint4{hl[0], hl[1], hl[2], hl[3]};
-#pragma unroll
-      for (int ob = 0; ob < 2; ++ob) {
-        const uint4 w = la2[ob][s][lane];
-        d2[ob] = mfma_bf16(w, bh, d2[ob]);
-        d2[ob] = mfma_bf16(w, bl, d2[ob]);
-      }
+      for (int u = 0; u < 8; ++u)
+        split_pair(relu(d1[2 * u]), relu(d1[2 * u + 1]), hh[8 * bk + u], hl[8 * bk + u]);
     }
+    // layers 2 and 3, one half of the 64 units at a time (fewer registers live).  The weights in LDS
+    // are read through an offset the compiler cannot see through, so that it reads them here in
+    // every tile instead of holding them in 32 registers.
+    int opq = 0;
+    asm volatile("" : "+v"(opq));
     float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ob = 0; ob < 2; ++ob)
+    for (int ob = 0; ob < 2; ++ob) {
+      f16 d2 = rb2[ob];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f4 w = lw3[8 * ob + 2 * a + g];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) part[c] = __builtin_fmaf(w[c], relu(d2[ob][4 * a + c]), part[c]);
+      for (int s = 0; s < 4; ++s) {
+        const uint4 w = la2[ob][s][lane + opq];
+        d2 = mfma_bf16(w, uint4{hh[4 * s], hh[4 * s + 1], hh[4 * s + 2], hh[4 * s + 3]}, d2);
+        d2 = mfma_bf16(w, uint4{hl[4 * s], hl[4 * s + 1], hl[4 * s + 2], hl[4 * s + 3]}, d2);
       }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) part[v & 3] = __builtin_fmaf(rw3[ob][v], relu(d2[v]), part[v & 3]);
+    }
     float acc = (part[0] + part[1]) + (part[2] + part[3]);
     acc += __shfl_xor(acc, 32, kWave);
-    if (g == 0 && e < n) y[e] = finite ? acc + bias3 : __builtin_nanf("");
+    const int64_t e = (tile << 5) + i32;
+    if (g == 0 && e < n) y[e] = zero == 0.f ? acc + bias3 : __builtin_nanf("");
   }
 }
 
@@ -187,7 +196,7 @@ extern "C" open_status open_perf_predict(open_ctx *ctx, const float *X, int64_t 
     return fail(ctx, OPEN_E_INVALID, "null pointer");
   OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
   const int64_t tiles = (n_runs + 31) / 32;
-  const int64_t cap = (int64_t)ctx->num_cu * 16;  // waves
+  const int64_t cap = (int64_t)ctx->num_cu * 48;  // waves, blocks handed out as they end
   const int64_t waves = tiles < cap ? tiles : cap;
   OPEN_LAUNCH(ctx, "perf_predict", k_perf_predict, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, n_runs, X, mu,
               rs, W1, b1, W2, b2, w3, b3, y);
