@@ -116,9 +116,11 @@ __global__ __launch_bounds__(kPrefixThreads) void k_split_prefix(const RowRef *_
 // emptied every kSplitFlush entries, so that a longer part loses no accuracy.  12.7M entries at
 // rank 32 (480 columns): 240 us, at rank 64 23.5M entries 1.2 ms; with 32 x 32 x 2 products (all of
 // the upper triangle too), chunks of 1024 entries (3.05 per wavefront: four rounds for some) and
-// a partial Gram written per chunk 380 us and 1.9 ms.
+// a partial Gram written per chunk 380 us and 1.9 ms.  Asking for two blocks per CU keeps the
+// accumulators out of the accumulation registers: at rank 64 each product otherwise came with two
+// register moves, which take issue time that the products need (622 -> 568 us a launch).
 template <int K>
-__global__ __launch_bounds__(64 * kGramWaves) void k_split_gram(const float *__restrict__ Uf,
+__global__ __launch_bounds__(64 * kGramWaves, 2) void k_split_gram(const float *__restrict__ Uf,
                                                                const int32_t *__restrict__ ri,
                                                                const float *__restrict__ cv,
                                                                const RowRef *__restrict__ list,
