@@ -608,6 +608,21 @@ __device__ __forceinline__ const float *stage_factors(const float *__restrict__ 
   return fl + PS;
 }
 
+// The groups of a block with primal rows are handed out to its wavefronts one by one, in the
+// order given (the longest first).  Primal groups differ by more than ten times in length, and a
+// wavefront has only two or three of them: dealt out in turn, a launch over 82,000 rows of 29..480
+// entries ran with 1.35 wavefronts per SIMD on average out of 2, the SIMDs with the longer
+// ones far behind (300 -> 257 us).  Blocks still take theirs in turn: 20 and more each even out.
+template <int W>
+struct GroupQueue {
+  int *next;  // in LDS: the block's first group not handed out
+  __device__ __forceinline__ int take() const {
+    int j = 0;
+    if ((threadIdx.x & 63) == 0) j = __hip_atomic_fetch_add(next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return __builtin_amdgcn_readfirstlane(j);
+  }
+};
+
 // Persistent kernel over the rows of classes c_lo..c_hi (contiguous in the bucketed list),
 // all solved at padded dimension D (dual) or k (primal).
 template <int K, int P, int D, bool DUAL, bool LDSF, int W, int OCC, bool BLK>
@@ -621,6 +636,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   constexpr int WL = wave_lds_floats(P, D);
   constexpr int FL = LDSF ? factor_lds_bytes<K>() / 4 : 4;
   __shared__ __attribute__((aligned(16))) float lds_all[W * WL + FL];
+  __shared__ int qnext;
+  if (!DUAL && threadIdx.x == 0) qnext = W;
   const int64_t start = cls[2 * c_lo];
   const int64_t count = cls[2 * c_hi] + cls[2 * c_hi + 1] - start;
   const int64_t end = start + count;
@@ -636,6 +653,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
     __syncthreads();
   } else {
     Fr.rs = make_rsrc(F, (uint64_t)n * K * sizeof(float));
+    if (!DUAL) __syncthreads();
   }
   float *wl = lds_all + (threadIdx.x >> 6) * WL;
   const int sme = (threadIdx.x & 63) / P;
@@ -644,6 +662,15 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
     const int64_t sl = start + (DUAL ? g : groups - 1 - g) * SYS + sme;
     return (g < groups && sl < end) ? list[sl] : RowRef{-1, 0, 0};
   };
+  if constexpr (!DUAL) {
+    const GroupQueue<W> queue{&qnext};
+    for (int64_t g = g0; g < groups; g = (int64_t)blockIdx.x + (int64_t)gridDim.x * queue.take()) {
+      const RowRef cur = fetch(g);
+      solve_group<P, D, K, DUAL, LDSF, (OCC == 1 || D <= 12), BLK>(Fr, n, cur, idx, val, lambda, weighted, X, status,
+                                                                   wl);
+    }
+    return;
+  }
   RowRef cur = fetch(g0);
   for (int64_t g = g0; g < groups; g += nw) {
     const RowRef nxt = fetch(g + nw);  // next group's records load while this group computes
@@ -684,7 +711,10 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   constexpr int SYS = 64 / P;
   constexpr int WL = multi_wave_floats<P, C...>();
   constexpr int FL = LDSF ? factor_lds_bytes<K>() / 4 : 4;
+  constexpr bool kQueue = (!C::DUAL || ...);  // some class is primal
   __shared__ __attribute__((aligned(16))) float lds_all[W * WL + FL];
+  __shared__ int qnext;
+  if (kQueue && threadIdx.x == 0) qnext = W;
   // per class: first list slot, rows, and the first group of the merged index space
   int64_t cs[NC], cc[NC], g1[NC];
   {
@@ -707,9 +737,12 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
     __syncthreads();
   } else {
     Fr.rs = make_rsrc(F, (uint64_t)n * K * sizeof(float));
+    if (kQueue) __syncthreads();
   }
   float *wl = lds_all + (threadIdx.x >> 6) * WL;
   const int sme = (threadIdx.x & 63) / P;
+  const GroupQueue<W> queue{&qnext};
+  int64_t gq = g0;  // the wave's merged group, where they are handed out
   // The wave takes the merged groups g = g0 (mod nw) in increasing order: one loop per class,
   // over the class's own groups, so that each loop holds only its class's registers.
   int ci = 0;
@@ -725,6 +758,14 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
           const int64_t sl = (C::DUAL ? q : ng - 1 - q) * SYS + sme;
           return (q < ng && sl < cc[i]) ? list[cs[i] + sl] : RowRef{-1, 0, 0};
         };
+        if constexpr (kQueue) {
+          for (; gq < g1[i]; gq = (int64_t)blockIdx.x + (int64_t)gridDim.x * queue.take()) {
+            const RowRef cur = fetch(gq - gb);
+            solve_group<P, C::D, K, C::DUAL, LDSF, (OCC == 1 || C::D <= 12), false>(Fr, n, cur, idx, val, lambda,
+                                                                                    weighted, X, status, wl);
+          }
+          return;
+        }
         RowRef cur = fetch(gl);
         for (int64_t q = gl; q < ng; q += nw) {
           const RowRef nxt = fetch(q + nw);  // next group's records load while this group computes

@@ -52,3 +52,35 @@ def test_class_boundaries(k, n):
     e = np.linalg.norm(U[:m] - ref, axis=1) / np.where(nrm > 0, nrm, 1.0)
     print("k %d n %d: max error %.2e" % (k, n, e.max()))
     assert e.max() <= 1e-4
+
+
+@pytest.mark.parametrize("k,n", [(32, 480), (32, 700), (16, 480), (8, 480)])
+def test_groups_handed_out(k, n):
+    """More groups of primal rows than wavefronts on the card, of very different lengths: every row
+    is solved once, and to the bits that it has in a batch small enough for one group each."""
+    r = np.random.default_rng([k, n])
+    m = 75_001
+    counts = np.minimum(r.zipf(1.4, size=m) + k, n - 1).astype(np.int64)
+    counts[r.integers(0, m, size=2000)] = r.integers(0, k, size=2000)  # some dual and empty rows
+    rp = np.zeros(m + 1, np.int64)
+    rp[1:] = np.cumsum(counts)
+    start = r.integers(0, n, size=m)
+    col = ((np.arange(rp[-1]) - np.repeat(rp[:-1], counts) + np.repeat(start, counts)) % n).astype(np.int32)
+    val = r.uniform(0.4, 1.0, size=len(col)).astype(np.float32)
+    V = dev((0.3 * r.normal(size=(n, k))).astype(np.float32))
+    ctx = native.Context(0)
+    try:
+        def solve(a, b):
+            st = torch.full((b - a,), -7, dtype=torch.int32, device="cuda")
+            sl = slice(int(rp[a]), int(rp[b]))
+            U = torch.full((b - a, k), float("nan"), device="cuda")
+            native.open_foldin(ctx, V, dev(rp[a:b + 1] - rp[a]), dev(col[sl]), dev(val[sl]), 0.05, True, U_out=U,
+                               row_status=st)
+            return U.cpu(), st.cpu()
+
+        U, st = solve(0, m)
+        parts = [solve(a, min(a + 25_001, m)) for a in range(0, m, 25_001)]
+    finally:
+        ctx.close()
+    assert torch.equal(U, torch.cat([p[0] for p in parts])) and torch.equal(st, torch.cat([p[1] for p in parts]))
+    assert torch.equal(st == 0, torch.from_numpy(counts > 0))
