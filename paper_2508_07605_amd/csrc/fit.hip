@@ -17,13 +17,17 @@ namespace openk {
 //   scan    per column: exclusive over the chunks of a segment, in place; then over the segments
 //           and the columns (one block), which also gives col_ptr
 //   place   position = segment base + chunk offset + rank
-// Bound by the scattered 4-byte stores of the place kernel (runs of a few entries per column and
-// chunk); consecutive chunks, which write next to each other, are dealt to one XCD's L2.
-// 12.7M entries, 200,003 x 480: count 28, scan 13, place 414 us; with chunks of 256 rows per
-// wavefront that walked its rows one by one (three quarters of the SIMDs busy, one row's loads
-// at a time) 109, 15 and 860.
+// The place kernel puts a chunk's entries in order in LDS first, so that neighbouring lanes store
+// neighbouring entries of a column (17 in a run at 480 columns, 2.6 at 1920); consecutive chunks,
+// which write next to each other, are dealt to one XCD's L2.  Bound by the latency of its steps,
+// one block of 16 wavefronts per CU.  12.7M entries, 200,003 x 480: count 28, scan 14, place
+// 128 us; stored entry by entry as ranked 358 us, and with chunks of 256 rows per wavefront that
+// walked its rows one by one 109, 15 and 860.  19.5M entries, 500,009 x 1920: place 278 us, stored
+// as ranked 577.
 constexpr int kCscRows = 128;          // rows of a chunk: two 64-bit masks per column
 constexpr int kCscThreads = 512;
+constexpr int kCscPlaceThreads = 1024;
+constexpr int kCscWin = 10240;         // entries put in order in LDS at a time (fewer for many columns)
 constexpr int kCscSeg = 64;            // chunks of a scan segment
 constexpr int kMaxCols = 4096;
 
@@ -40,15 +44,16 @@ struct CscChunk {
   int64_t r0, e0;
   int rows, len;
 };
+template <int TH>
 __device__ __forceinline__ CscChunk csc_begin(int64_t m, int n, const int64_t *__restrict__ ptr, int chunk,
                                               int *rp, unsigned long long *mask) {
   CscChunk c;
   c.r0 = (int64_t)chunk * kCscRows;
   c.rows = (int)(m - c.r0 < kCscRows ? m - c.r0 : kCscRows);
   c.e0 = ptr[c.r0];
-  for (int i = threadIdx.x; i <= kCscRows; i += kCscThreads)
+  for (int i = threadIdx.x; i <= kCscRows; i += TH)
     rp[i] = (int)(ptr[c.r0 + (i < c.rows ? i : c.rows)] - c.e0);
-  for (int j = threadIdx.x; j < 2 * n; j += kCscThreads) mask[j] = 0ull;
+  for (int j = threadIdx.x; j < 2 * n; j += TH) mask[j] = 0ull;
   __syncthreads();
   c.len = rp[kCscRows];
   return c;
@@ -60,9 +65,10 @@ __device__ __forceinline__ int csc_row(const int *rp, int t) {
   for (int s = kCscRows / 2; s > 0; s >>= 1) r += rp[r + s] <= t ? s : 0;
   return r;
 }
+template <int TH>
 __device__ __forceinline__ void csc_masks(const CscChunk &c, int n, const int32_t *__restrict__ col, const int *rp,
                                           unsigned long long *mask) {
-  for (int t = threadIdx.x; t < c.len; t += kCscThreads) {
+  for (int t = threadIdx.x; t < c.len; t += TH) {
     const int j = col[c.e0 + t];
     if (j < 0 || j >= n) continue;  // rejected by the index check
     const int r = csc_row(rp, t);
@@ -78,8 +84,8 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_count(int64_t m, int n, con
   __shared__ int rp[kCscRows + 1];
   const int chunk = csc_chunk(nchunk);
   if (chunk < 0) return;
-  const CscChunk c = csc_begin(m, n, ptr, chunk, rp, mask_s);
-  csc_masks(c, n, col, rp, mask_s);
+  const CscChunk c = csc_begin<kCscThreads>(m, n, ptr, chunk, rp, mask_s);
+  csc_masks<kCscThreads>(c, n, col, rp, mask_s);
   for (int j = threadIdx.x; j < n; j += kCscThreads)
     hist[(int64_t)chunk * n + j] = __popcll(mask_s[2 * j]) + __popcll(mask_s[2 * j + 1]);
 }
@@ -148,31 +154,73 @@ __global__ __launch_bounds__(1024) void k_csc_bases(int n, int nseg, int64_t *__
   if (threadIdx.x == 0) col_ptr[n] = before;
 }
 
-__global__ __launch_bounds__(kCscThreads) void k_csc_place(int64_t m, int n, const int64_t *__restrict__ ptr,
-                                                           const int32_t *__restrict__ col,
-                                                           const float *__restrict__ val, int nchunk,
-                                                           const int32_t *__restrict__ hist,
-                                                           const int64_t *__restrict__ seg,
-                                                           int32_t *__restrict__ row_idx, float *__restrict__ cval) {
-  extern __shared__ unsigned long long mask_s[];  // [n][2] masks, then [n] positions
-  __shared__ int rp[kCscRows + 1];
-  int64_t *pos = reinterpret_cast<int64_t *>(mask_s + 2 * n);
+// The chunk's entries are first put in order in LDS, `win` of them at a time, and then written out
+// in that order: neighbouring lanes write neighbouring entries of a column.
+__global__ __launch_bounds__(kCscPlaceThreads) void k_csc_place(int64_t m, int n, const int64_t *__restrict__ ptr,
+                                                                const int32_t *__restrict__ col,
+                                                                const float *__restrict__ val, int nchunk, int win,
+                                                                const int32_t *__restrict__ hist,
+                                                                const int64_t *__restrict__ seg,
+                                                                int32_t *__restrict__ row_idx,
+                                                                float *__restrict__ cval) {
+  constexpr int TH = kCscPlaceThreads;
+  // [n][2] masks, [n] global minus chunk position of a column's first entry, [win] entries
+  // (column and row of the chunk, value), [n] chunk position
+  extern __shared__ unsigned long long mask_s[];
+  __shared__ int rp[kCscRows + 1], wsum[TH / 64];
+  int64_t *shift = reinterpret_cast<int64_t *>(mask_s + 2 * n);
+  uint2 *ent = reinterpret_cast<uint2 *>(shift + n);
+  int *first = reinterpret_cast<int *>(ent + win);
   const int chunk = csc_chunk(nchunk);
   if (chunk < 0) return;
-  for (int j = threadIdx.x; j < n; j += kCscThreads)
-    pos[j] = seg[(int64_t)(chunk / kCscSeg) * n + j] + hist[(int64_t)chunk * n + j];
-  const CscChunk c = csc_begin(m, n, ptr, chunk, rp, mask_s);
-  csc_masks(c, n, col, rp, mask_s);
-  for (int t = threadIdx.x; t < c.len; t += kCscThreads) {
-    const int j = col[c.e0 + t];
-    if (j < 0 || j >= n) continue;
-    const int r = csc_row(rp, t);
-    const unsigned long long lo = mask_s[2 * j], hi = mask_s[2 * j + 1];
-    const unsigned long long below = (1ull << (r & 63)) - 1ull;
-    const int rank = r < 64 ? __popcll(lo & below) : __popcll(lo) + __popcll(hi & below);
-    const int64_t p = pos[j] + rank;
-    row_idx[p] = (int32_t)(c.r0 + r);
-    cval[p] = val[c.e0 + t];
+  const CscChunk c = csc_begin<TH>(m, n, ptr, chunk, rp, mask_s);
+  csc_masks<TH>(c, n, col, rp, mask_s);
+  // exclusive scan of the columns' counts: thread t owns columns per t .. per t + per - 1
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, per = (n + TH - 1) / TH;
+  auto count = [&](int j) { return __popcll(mask_s[2 * j]) + __popcll(mask_s[2 * j + 1]); };
+  int own = 0;
+  for (int j = per * threadIdx.x; j < per * ((int)threadIdx.x + 1) && j < n; ++j) own += count(j);
+  int run = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int x = __shfl_up(run, off, 64);
+    run += lane >= off ? x : 0;
+  }
+  if (lane == 63) wsum[w] = run;
+  __syncthreads();
+  int total = 0;
+  run -= own;
+#pragma unroll
+  for (int i = 0; i < TH / 64; ++i) {
+    run += i < w ? wsum[i] : 0;
+    total += wsum[i];
+  }
+  for (int j = per * threadIdx.x; j < per * ((int)threadIdx.x + 1) && j < n; ++j) {
+    first[j] = run;
+    shift[j] = seg[(int64_t)(chunk / kCscSeg) * n + j] + hist[(int64_t)chunk * n + j] - run;
+    run += count(j);
+  }
+  for (int w0 = 0; w0 < total; w0 += win) {
+    __syncthreads();
+    for (int t = threadIdx.x; t < c.len; t += TH) {
+      const int j = col[c.e0 + t];
+      if (j < 0 || j >= n) continue;
+      const int r = csc_row(rp, t);
+      const unsigned long long lo = mask_s[2 * j], hi = mask_s[2 * j + 1];
+      const unsigned long long below = (1ull << (r & 63)) - 1ull;
+      const int rank = r < 64 ? __popcll(lo & below) : __popcll(lo) + __popcll(hi & below);
+      const int q = first[j] + rank - w0;
+      if (q >= 0 && q < win) ent[q] = uint2{(uint32_t)(j * kCscRows + r), __builtin_bit_cast(uint32_t, val[c.e0 + t])};
+    }
+    __syncthreads();
+    const int nw = total - w0 < win ? total - w0 : win;
+    for (int q = threadIdx.x; q < nw; q += TH) {
+      const uint2 e = ent[q];
+      const int64_t p = shift[e.x / kCscRows] + w0 + q;
+      const uint32_t v = e.y;
+      row_idx[p] = (int32_t)(c.r0 + (int)(e.x % kCscRows));
+      cval[p] = __builtin_bit_cast(float, v);
+    }
   }
 }
 
@@ -221,8 +269,11 @@ open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, const int64_t *row_p
   }
   OPEN_LAUNCH(ctx, "csc_bases", k_csc_bases, dim3(1), dim3(1024), 0, n, nseg, (int64_t *)seg, col_ptr);
   if (nchunk > 0) {
-    OPEN_LAUNCH(ctx, "csc_place", k_csc_place, blocks, threads, lds + sizeof(int64_t) * (size_t)n, m, n, row_ptr, col,
-                val, nchunk, (const int32_t *)hist, (const int64_t *)seg, row_idx, cval);
+    const size_t cols = (2 * sizeof(unsigned long long) + sizeof(int64_t) + sizeof(int)) * (size_t)n;
+    const size_t room = (size_t)(156 * 1024 - cols) / sizeof(uint2);  // n <= kMaxCols: at least 5632
+    const int win = room < (size_t)kCscWin ? (int)room : kCscWin;
+    OPEN_LAUNCH(ctx, "csc_place", k_csc_place, blocks, dim3(kCscPlaceThreads), cols + sizeof(uint2) * (size_t)win, m, n,
+                row_ptr, col, val, nchunk, win, (const int32_t *)hist, (const int64_t *)seg, row_idx, cval);
   }
   return OPEN_OK;
 }

@@ -222,3 +222,21 @@ def test_csc_chunk_edges(ctx, m, n):
     assert np.array_equal(cp.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(col[:nnz], minlength=n))]))
     assert np.array_equal(ri.cpu().numpy()[:nnz], rows[order])
     assert np.array_equal(cv.cpu().numpy()[:nnz], val[:nnz][order])
+
+
+@pytest.mark.parametrize("m,n,lo", [(300, 480, 480), (259, 4096, 1500), (140, 100, 60), (1027, 1024, 75)])
+def test_csc_windows(ctx, m, n, lo):
+    # chunks of more entries than are put in order in LDS at a time, and of about as many
+    r = np.random.default_rng([m, n])
+    counts = r.integers(lo, min(n, lo + 10) + 1, size=m)
+    rp = np.zeros(m + 1, np.int64)
+    rp[1:] = np.cumsum(counts)
+    col = np.concatenate([np.sort(r.choice(n, size=c, replace=False)) for c in counts]).astype(np.int32)
+    val = r.uniform(size=len(col)).astype(np.float32)
+    cp, ri, cv = native.open_csr_to_csc(ctx, dev(rp), dev(col), dev(val), n)
+    torch.cuda.synchronize()
+    rows = np.repeat(np.arange(m), counts)
+    order = np.lexsort((rows, col))
+    assert np.array_equal(cp.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(col, minlength=n))]))
+    assert np.array_equal(ri.cpu().numpy(), rows[order])
+    assert np.array_equal(cv.cpu().numpy(), val[order])
