@@ -17,15 +17,15 @@
 //          back substitution is a sum per lane and a reduction over the 16 lanes per unknown.
 //   Output lane i writes the dimensions 4 i .. 4 i + 3 of its system (16 bytes).
 // Bound by the matrix units (80 cycles per observation and SIMD) and the solve's VALU (8000 per row);
-// two wavefronts per SIMD overlap part of it.  78,000 rows of 33 to 1023 entries (11.9M): 0.91 ms,
-// of which the products need 0.39; with one row per wavefront (32 x 32 x 2 products, one column per
-// lane, every pivot row through LDS: 22,000 cycles a solve) 1.2 ms, 1.33 before the rows were
-// taken longest first.
+// two wavefronts per SIMD overlap part of it.  78,000 rows of 33 to 1023 entries (11.9M): 0.83 ms,
+// of which the products need 0.39; 0.93 with the units dealt to the wavefronts in turn; with one row
+// per wavefront (32 x 32 x 2 products, one column per lane, every pivot row through LDS: 22,000
+// cycles a solve) 1.2 ms, 1.33 before the rows were taken longest first.
 #include "rowsolve.h"
 
 namespace openk {
 
-constexpr int kP64Waves = 4;    // wavefronts per block
+constexpr int kP64Waves = 8;    // wavefronts per block
 constexpr int kP64Rows = 4;     // rows of a wavefront
 constexpr int kP64Stage = 256;  // entries staged per wavefront, twice
 constexpr int kP64Steps = 4;    // MFMA steps (four observations each) whose rows load together
@@ -72,14 +72,18 @@ __global__ __launch_bounds__(64 * kP64Waves) __attribute__((amdgpu_waves_per_eu(
     float *__restrict__ X, int32_t *__restrict__ status) {
   __shared__ int jl_all[kP64Waves][2][kP64Stage];
   __shared__ float rl_all[kP64Waves][2][kP64Stage];
+  __shared__ int qnext;
+  if (threadIdx.x == 0) qnext = kP64Waves;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int i16 = lane & 15, o = lane >> 4;
   const int64_t first = cls[2 * c_lo];
   const int64_t count = cls[2 * c_hi] + cls[2 * c_hi + 1] - first;
   const int64_t units = (count + kP64Rows - 1) / kP64Rows;
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(F, (uint64_t)n * 64 * sizeof(float));
-  const int64_t nw = (int64_t)gridDim.x * kP64Waves;
-  // wave-major and the longest rows first: units that cost alike go to different compute units
+  __syncthreads();
+  const GroupQueue<kP64Waves> queue{&qnext};
+  // wave-major and the longest rows first: units that cost alike go to different compute units; a
+  // block's units are handed out to its wavefronts, one ahead (its records load meanwhile)
   const int64_t u0 = (int64_t)blockIdx.x + (int64_t)gridDim.x * w;
   // the unit's records, row q in lane q
   auto records = [&](int64_t u) -> RowRef {
@@ -99,8 +103,9 @@ __global__ __launch_bounds__(64 * kP64Waves) __attribute__((amdgpu_waves_per_eu(
   };
   int stg = 0;  // staging buffer in use
   if (u0 < units) fetch(readlane_i64(rec.beg, 0), __builtin_amdgcn_readlane(rec.cnt, 0), 0);
-  for (int64_t u = u0; u < units; u += nw) {
-    const RowRef nxt = records(u + nw);
+  for (int64_t u = u0, un; u < units; u = un) {
+    un = (int64_t)blockIdx.x + (int64_t)gridDim.x * queue.take();
+    const RowRef nxt = records(un);
     float g[kP64Rows][40];  // the four lower block triangles, block (b, c <= b), register e: [4 tri(b, c) + e]
     float rhs[4] = {0.f, 0.f, 0.f, 0.f};
     int flags = 0;          // of the lane row's system: 1 non-finite value, 2 index outside [0, n)
@@ -267,11 +272,11 @@ __global__ __launch_bounds__(64 * kP64Waves) __attribute__((amdgpu_waves_per_eu(
 }
 
 // The group of the primal size classes at rank 64 (n_i > 32 below the split-K length): one
-// variant, a persistent grid of up to two blocks per CU.
+// variant, a persistent grid of up to one block per CU.
 OPEN_GROUP(g_k64_primal) {
   if (choice != 0) return fail(ctx, OPEN_E_INVALID, "kernel variant out of range");
   int64_t blocks = (m + kP64Waves * kP64Rows - 1) / (kP64Waves * kP64Rows);
-  const int64_t cap = (int64_t)ctx->num_cu * 2;
+  const int64_t cap = ctx->num_cu;
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
   OPEN_LAUNCH(ctx, "ridge_k64_primal", k_primal64, dim3((unsigned)blocks), dim3(64 * kP64Waves), 0, F, n, idx, val,
