@@ -608,11 +608,13 @@ __device__ __forceinline__ const float *stage_factors(const float *__restrict__ 
   return fl + PS;
 }
 
-// The groups of a block with primal rows are handed out to its wavefronts one by one, in the
-// order given (the longest first).  Primal groups differ by more than ten times in length, and a
-// wavefront has only two or three of them: dealt out in turn, a launch over 82,000 rows of 29..480
-// entries ran with 1.35 wavefronts per SIMD on average out of 2, the SIMDs with the longer
-// ones far behind (300 -> 257 us).  Blocks still take theirs in turn: 20 and more each even out.
+// The groups of a block are handed out to its wavefronts one by one, in the order given (the
+// costliest first); blocks take theirs in turn.  Primal groups differ by more than ten times in
+// length, and a wavefront has only two or three of them: dealt out in turn, a launch over 82,000
+// rows of 29..480 entries ran with 1.35 wavefronts per SIMD on average out of 2, the SIMDs with the
+// longer ones far behind (300 -> 257 us).  Where all groups are dual, and short, a wavefront takes
+// the next one before it computes, so that its records load meanwhile (100,000 rows of 4..24
+// entries at rank 32, three launches and the bucketing: 51.8 -> 49.5 us).
 template <int W>
 struct GroupQueue {
   int *next;  // in LDS: the block's first group not handed out
@@ -637,11 +639,10 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   constexpr int FL = LDSF ? factor_lds_bytes<K>() / 4 : 4;
   __shared__ __attribute__((aligned(16))) float lds_all[W * WL + FL];
   __shared__ int qnext;
-  if (!DUAL && threadIdx.x == 0) qnext = W;
+  if (threadIdx.x == 0) qnext = W;
   const int64_t start = cls[2 * c_lo];
   const int64_t count = cls[2 * c_hi] + cls[2 * c_hi + 1] - start;
   const int64_t end = start + count;
-  const int64_t nw = (int64_t)gridDim.x * W;
   // wave-major: consecutive groups, which cost alike, go to different compute units
   const int64_t g0 = (int64_t)blockIdx.x + (int64_t)gridDim.x * (threadIdx.x >> 6);
   const int64_t groups = (count + SYS - 1) / SYS;
@@ -653,7 +654,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
     __syncthreads();
   } else {
     Fr.rs = make_rsrc(F, (uint64_t)n * K * sizeof(float));
-    if (!DUAL) __syncthreads();
+    __syncthreads();
   }
   float *wl = lds_all + (threadIdx.x >> 6) * WL;
   const int sme = (threadIdx.x & 63) / P;
@@ -662,21 +663,24 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
     const int64_t sl = start + (DUAL ? g : groups - 1 - g) * SYS + sme;
     return (g < groups && sl < end) ? list[sl] : RowRef{-1, 0, 0};
   };
-  if constexpr (!DUAL) {
-    const GroupQueue<W> queue{&qnext};
-    for (int64_t g = g0; g < groups; g = (int64_t)blockIdx.x + (int64_t)gridDim.x * queue.take()) {
-      const RowRef cur = fetch(g);
-      solve_group<P, D, K, DUAL, LDSF, (OCC == 1 || D <= 12), BLK>(Fr, n, cur, idx, val, lambda, weighted, X, status,
-                                                                   wl);
-    }
-    return;
-  }
+  const GroupQueue<W> queue{&qnext};
+  auto next = [&] { return (int64_t)blockIdx.x + (int64_t)gridDim.x * queue.take(); };
   RowRef cur = fetch(g0);
-  for (int64_t g = g0; g < groups; g += nw) {
-    const RowRef nxt = fetch(g + nw);  // next group's records load while this group computes
+  for (int64_t g = g0; g < groups;) {
+    int64_t gn = 0;
+    RowRef nxt;
+    if constexpr (DUAL) {
+      gn = next();
+      nxt = fetch(gn);
+    }
     // operand prefetch in the Gram loop when a single wave per SIMD has to hide the latency
     solve_group<P, D, K, DUAL, LDSF, (OCC == 1 || D <= 12), BLK>(Fr, n, cur, idx, val, lambda, weighted, X, status,
                                                                  wl);
+    if constexpr (!DUAL) {
+      gn = next();
+      nxt = fetch(gn);
+    }
+    g = gn;
     cur = nxt;
   }
 }
@@ -711,10 +715,9 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   constexpr int SYS = 64 / P;
   constexpr int WL = multi_wave_floats<P, C...>();
   constexpr int FL = LDSF ? factor_lds_bytes<K>() / 4 : 4;
-  constexpr bool kQueue = (!C::DUAL || ...);  // some class is primal
   __shared__ __attribute__((aligned(16))) float lds_all[W * WL + FL];
   __shared__ int qnext;
-  if (kQueue && threadIdx.x == 0) qnext = W;
+  if (threadIdx.x == 0) qnext = W;
   // per class: first list slot, rows, and the first group of the merged index space
   int64_t cs[NC], cc[NC], g1[NC];
   {
@@ -725,7 +728,6 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
      ...);
   }
   const int64_t total = g1[NC - 1];  // groups of all classes
-  const int64_t nw = (int64_t)gridDim.x * W;
   (void)ptr;
   // wave-major: consecutive groups, which cost alike, go to different compute units
   const int64_t g0 = (int64_t)blockIdx.x + (int64_t)gridDim.x * (threadIdx.x >> 6);
@@ -737,40 +739,43 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
     __syncthreads();
   } else {
     Fr.rs = make_rsrc(F, (uint64_t)n * K * sizeof(float));
-    if (kQueue) __syncthreads();
+    __syncthreads();
   }
   float *wl = lds_all + (threadIdx.x >> 6) * WL;
   const int sme = (threadIdx.x & 63) / P;
   const GroupQueue<W> queue{&qnext};
-  int64_t gq = g0;  // the wave's merged group, where they are handed out
-  // The wave takes the merged groups g = g0 (mod nw) in increasing order: one loop per class,
-  // over the class's own groups, so that each loop holds only its class's registers.
+  auto next = [&] { return (int64_t)blockIdx.x + (int64_t)gridDim.x * queue.take(); };
+  constexpr bool kAhead = (C::DUAL && ...);  // after primal classes the dual ones even out the end
+  int64_t g = g0;                            // the wave's merged group
+  // The merged groups are taken in increasing order: one loop per class, over the class's own
+  // groups, so that each loop holds only its class's registers.
   int ci = 0;
   (
       [&] {
         const int i = ci++;
         const int64_t gb = i ? g1[i - 1] : 0;  // first merged group of the class
         const int64_t ng = g1[i] - gb;
-        int64_t gl = (g0 - gb) % nw;           // the wave's first group of the class
-        if (gl < 0) gl += nw;
         auto fetch = [&](int64_t q) -> RowRef {
           // primal classes hold ascending lengths: the longest first
           const int64_t sl = (C::DUAL ? q : ng - 1 - q) * SYS + sme;
           return (q < ng && sl < cc[i]) ? list[cs[i] + sl] : RowRef{-1, 0, 0};
         };
-        if constexpr (kQueue) {
-          for (; gq < g1[i]; gq = (int64_t)blockIdx.x + (int64_t)gridDim.x * queue.take()) {
-            const RowRef cur = fetch(gq - gb);
-            solve_group<P, C::D, K, C::DUAL, LDSF, (OCC == 1 || C::D <= 12), false>(Fr, n, cur, idx, val, lambda,
-                                                                                    weighted, X, status, wl);
+        if (g >= g1[i]) return;
+        RowRef cur = fetch(g - gb);
+        while (g < g1[i]) {
+          int64_t gn = 0;
+          RowRef nxt;
+          if constexpr (kAhead) {
+            gn = next();
+            nxt = fetch(gn - gb);
           }
-          return;
-        }
-        RowRef cur = fetch(gl);
-        for (int64_t q = gl; q < ng; q += nw) {
-          const RowRef nxt = fetch(q + nw);  // next group's records load while this group computes
           solve_group<P, C::D, K, C::DUAL, LDSF, (OCC == 1 || C::D <= 12), false>(Fr, n, cur, idx, val, lambda,
                                                                                   weighted, X, status, wl);
+          if constexpr (!kAhead) {
+            gn = next();
+            nxt = fetch(gn - gb);
+          }
+          g = gn;
           cur = nxt;
         }
       }(),
