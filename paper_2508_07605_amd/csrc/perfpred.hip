@@ -25,7 +25,7 @@
 // quarter of those to products, or two to five wavefronts per SIMD, leaves the time as it is
 // within 3 %.  The features, 28 bytes a run, are read in whole lines and turned through LDS; the
 // seven strided reads a tile that this replaces, and b2 and w3 read from LDS in every tile, took
-// 9 % of the time.  14,000,003 runs: 334 -> 306 us.
+// 9 % of the time.  14,000,003 runs: 347 -> 326 us, 500,000: 17.2 -> 15.1.
 #include "common.h"
 
 namespace openk {
@@ -196,7 +196,9 @@ extern "C" open_status open_perf_predict(open_ctx *ctx, const float *X, int64_t 
     return fail(ctx, OPEN_E_INVALID, "null pointer");
   OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
   const int64_t tiles = (n_runs + 31) / 32;
-  const int64_t cap = (int64_t)ctx->num_cu * 48;  // waves, blocks handed out as they end
+  // three wavefronts per SIMD stay resident: with four times as many, 300,000 runs took 14.8 us
+  // instead of 11.3 (the weights are laid out again by every block) and 14M as long as now
+  const int64_t cap = (int64_t)ctx->num_cu * 12;  // waves
   const int64_t waves = tiles < cap ? tiles : cap;
   OPEN_LAUNCH(ctx, "perf_predict", k_perf_predict, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, n_runs, X, mu,
               rs, W1, b1, W2, b2, w3, b3, y);
