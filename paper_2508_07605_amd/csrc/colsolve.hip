@@ -112,8 +112,8 @@ __global__ __launch_bounds__(kPrefixThreads) void k_split_prefix(const RowRef *_
 // grid); workgroups are dealt to the 8 XCDs round-robin.
 //
 // Bound by the matrix units (24 cycles per observation and SIMD at rank 32, 80 at rank 64) and the
-// gathers from L2.  Parts of equal length keep the wavefronts busy to the end; accumulators are
-// emptied every kSplitFlush entries, so that a longer part loses no accuracy.  12.7M entries at
+// gathers from L2.  Parts of equal length keep the wavefronts busy to the end; the accumulators of
+// both sums are emptied every kSplitFlush entries, so that a longer part loses no accuracy.  12.7M entries at
 // rank 32 (480 columns): 240 us, at rank 64 23.5M entries 1.2 ms; with 32 x 32 x 2 products (all of
 // the upper triangle too), chunks of 1024 entries (3.05 per wavefront: four rounds for some) and
 // a partial Gram written per chunk 380 us and 1.9 ms.  Asking for two blocks per CU keeps the
@@ -156,11 +156,11 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void k_split_gram(const float *
     const int32_t *ip = ri + rr.beg + e0;
     const float *vp = cv + rr.beg + e0;
     f4 acc[NB], sum[NB];
-    float b[KB];
+    float b[KB], bsum[KB];
 #pragma unroll
     for (int q = 0; q < NB; ++q) acc[q] = sum[q] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < KB; ++q) b[q] = 0.f;
+    for (int q = 0; q < KB; ++q) b[q] = bsum[q] = 0.f;
     int flags = 0;  // 1: non-finite value, 2: index outside [0, nF)
     // indices and values of a stage: loaded a stage ahead, then kept in LDS; rejected or absent
     // entries get the index -1, which reads zeros through the buffer resource
@@ -245,6 +245,11 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void k_split_gram(const float *
           sum[q] += acc[q];
           acc[q] = f4{0.f, 0.f, 0.f, 0.f};
         }
+#pragma unroll
+        for (int q = 0; q < KB; ++q) {
+          bsum[q] += b[q];
+          b[q] = 0.f;
+        }
       }
     }
     float *dst = part + (p0 + p) * G::PST;
@@ -257,6 +262,7 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void k_split_gram(const float *
     // the right-hand side over the four observation slots, in dimension order
 #pragma unroll
     for (int q = 0; q < KB; ++q) {
+      b[q] += bsum[q];
       b[q] += __shfl_xor(b[q], 16, 64);
       b[q] += __shfl_xor(b[q], 32, 64);
       if (lane < 16) dst[G::GRAM + KB * lane + q] = b[q];
