@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kPrefixThreads) void k_split_prefix(const RowRef *_
 // a partial Gram written per chunk 380 us and 1.9 ms.  Asking for two blocks per CU keeps the
 // accumulators out of the accumulation registers: at rank 64 each product otherwise came with two
 // register moves, which take issue time that the products need (622 -> 568 us a launch).
-template <int K>
+template <int K, bool FAR>
 __global__ __launch_bounds__(64 * kGramWaves, 2) void k_split_gram(const float *__restrict__ Uf,
                                                                const int32_t *__restrict__ ri,
                                                                const float *__restrict__ cv,
@@ -201,8 +201,12 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void k_split_gram(const float *
       for (int u = 0; u < ST; ++u) {
         const int j = jl[4 * u + o];
         vn[u] = rl[4 * u + o];
-        const uint32_t off = dim_ok ? (uint32_t)(j * K + KB * i16) * 4u : 0xfffffff0u;
-        if constexpr (KB == 1)
+        const uint32_t off = dim_ok ? ((uint32_t)j * K + KB * i16) * 4u : 0xfffffff0u;
+        if constexpr (FAR && KB == 1)
+          un[u][0] = far_load<1>(Uf, dim_ok ? j : -1, K, dim_ok ? i16 : 0)[0];
+        else if constexpr (FAR)
+          un[u] = far_load<KB>(Uf, j, K, KB * i16);
+        else if constexpr (KB == 1)
           un[u][0] = bload_f32(urs, (int)off);
         else if constexpr (KB == 2)
           un[u] = __builtin_bit_cast(fkb, __builtin_amdgcn_raw_buffer_load_b64(urs, (int)off, 0, 0));
@@ -381,7 +385,7 @@ static open_status split_launch_k(open_ctx *ctx, const float *F, int nF, const i
                                   int64_t max_rows, int ranges, unsigned blocks) {
   OPEN_LAUNCH(ctx, "split_prefix", k_split_prefix, dim3(1), dim3(kPrefixThreads), 0, list, cls, ranges,
               (int)(blocks * kGramWaves / kXcds), start);
-  OPEN_LAUNCH(ctx, "split_gram", k_split_gram<K>, dim3(blocks), dim3(64 * kGramWaves), 0, F, ri, cv, list, cls,
+  OPEN_LAUNCH(ctx, "split_gram", (far_factors(nF, K) ? k_split_gram<K, true> : k_split_gram<K, false>), dim3(blocks), dim3(64 * kGramWaves), 0, F, ri, cv, list, cls,
               ranges, (const int64_t *)start, nF, part, pflag);
   OPEN_LAUNCH(ctx, "split_solve", k_split_solve<K>, dim3((unsigned)max_rows), dim3(64), 0, list, cls,
               (const int64_t *)start, (const float *)part, (const int32_t *)pflag, lambda, weighted, X, status);

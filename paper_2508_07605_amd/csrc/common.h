@@ -67,6 +67,19 @@ __device__ __forceinline__ f4 bload_f4(__amdgpu_buffer_rsrc_t r, int off_bytes) 
   return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, off_bytes, 0, 0));
 }
 
+// Whether a factor matrix is out of a buffer resource's reach: its offsets are 32-bit bytes, and the
+// offset that row index -1 wraps to has to stay past the last row.
+inline bool far_factors(int64_t rows, int k) { return (rows + 1) * k * (int64_t)sizeof(float) > int64_t(1) << 32; }
+// N floats from column c of row j of a matrix with `width` columns, by 64-bit address; zeros for
+// j < 0 (row 0 is read instead)
+template <int N>
+__device__ __forceinline__ auto far_load(const float *F, int j, int width, int c) {
+  typedef float fv __attribute__((ext_vector_type(N)));
+  typedef float fu __attribute__((ext_vector_type(N), aligned(4)));
+  const fv x = *reinterpret_cast<const fu *>(F + (int64_t)(j < 0 ? 0 : j) * width + c);
+  return j < 0 ? fv{} : x;
+}
+
 // 16 independent 4x4 outer products: lanes 4b..4b+3 form block b; block b accumulates
 // D_b[i][j] += A_b[i] * B_b[j] with A_b[i] from lane 4b+i and B_b[j] from lane 4b+j.
 // Result layout: lane 4b+j holds column j of block b, register v = row v.

@@ -40,12 +40,12 @@ struct SmallSection {
     return m;
   }
   // the section's solve at dimension d (wave-uniform)
-  template <int K, bool LDSF, int OCC>
-  static __device__ __forceinline__ void solve(int d, const FRows<K, LDSF> &Fr, int n, const RowRef &r,
+  template <int K, int SRC, int OCC>
+  static __device__ __forceinline__ void solve(int d, const FRows<K, SRC> &Fr, int n, const RowRef &r,
                                                const int32_t *__restrict__ idx, const float *__restrict__ val,
                                                float lambda, int weighted, float *__restrict__ X,
                                                int32_t *__restrict__ status, float *__restrict__ wl) {
-    ((d == D_ ? solve_group<P_, D_, K, DUAL_, LDSF, (OCC == 1 || D_ <= 12), false>(Fr, n, r, idx, val, lambda,
+    ((d == D_ ? solve_group<P_, D_, K, DUAL_, SRC, (OCC == 1 || D_ <= 12), false>(Fr, n, r, idx, val, lambda,
                                                                                   weighted, X, status, wl)
               : (void)0),
      ...);
@@ -59,14 +59,14 @@ __host__ __device__ constexpr int small_wave_floats() {
   return m;
 }
 
-template <int K, bool LDSF, int W, int OCC, typename... S>
+template <int K, int SRC, int W, int OCC, typename... S>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_waves_per_eu(OCC))) void k_foldin_small(
     const float *__restrict__ F, int n, const int64_t *__restrict__ ptr, const int32_t *__restrict__ idx,
     const float *__restrict__ val, const uint8_t *__restrict__ mask, float lambda, int weighted,
     float *__restrict__ X, int32_t *__restrict__ status, int64_t m) {
   constexpr int NS = sizeof...(S);
   constexpr int WL = small_wave_floats<S...>();
-  constexpr int FL = LDSF ? factor_lds_bytes<K>() / 4 : 4;
+  constexpr int FL = SRC == kRowsLds ? factor_lds_bytes<K>() / 4 : 4;
   static_assert(64 * W >= 4 * kSmallRows, "four threads per row");
   __shared__ __attribute__((aligned(16))) float lds_all[W * WL + FL];
   __shared__ int64_t beg_s[kSmallRows];
@@ -77,11 +77,11 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   __shared__ uint8_t order_s[kSmallRows];  // the rows in that order, section after section
   __shared__ int nrow_s[NS];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  FRows<K, LDSF> Fr;
-  if constexpr (LDSF) {
+  FRows<K, SRC> Fr;
+  if constexpr (SRC == kRowsLds) {
     Fr.lds = stage_factors<K, W>(F, n, lds_all + W * WL);  // completes at the wait below
   } else {
-    Fr.rs = make_rsrc(F, (uint64_t)n * K * sizeof(float));
+    Fr.global(F, n);
   }
   // ---- the block's rows: section and dimension of each
   constexpr int none = 1 << 30;
@@ -127,7 +127,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
       if (lane == 0) atomicAdd(&nrow_s[q], rows);
     }
   }
-  if constexpr (LDSF) __builtin_amdgcn_s_waitcnt(0);
+  if constexpr (SRC == kRowsLds) __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   // ---- groups, section by section, dealt to the wavefronts in order
   float *wl = lds_all + w * WL;
@@ -143,7 +143,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
             const int t = order_s[first + i];
             r = RowRef{(int32_t)(row0 + t), cnt_s[t], beg_s[t]};
           }
-          S::template solve<K, LDSF, OCC>(__builtin_amdgcn_readfirstlane(d), Fr, n, r, idx, val, lambda, weighted, X,
+          S::template solve<K, SRC, OCC>(__builtin_amdgcn_readfirstlane(d), Fr, n, r, idx, val, lambda, weighted, X,
                                           status, wl);
         }
         g -= groups;
@@ -159,10 +159,10 @@ open_status launch_small(open_ctx *ctx, const char *name, const float *F, int n,
                          float *X, int32_t *status, int64_t m) {
   const dim3 grid((unsigned)((m + kSmallRows - 1) / kSmallRows));
   if (n <= kFactorLdsRows) {
-    OPEN_LAUNCH(ctx, name, (k_foldin_small<K, true, W, OCC, S...>), grid, dim3(64 * W), 0, F, n, ptr, idx, val, mask,
+    OPEN_LAUNCH(ctx, name, (k_foldin_small<K, kRowsLds, W, OCC, S...>), grid, dim3(64 * W), 0, F, n, ptr, idx, val, mask,
                 lambda, weighted, X, status, m);
   } else {
-    OPEN_LAUNCH(ctx, name, (k_foldin_small<K, false, W, OCC, S...>), grid, dim3(64 * W), 0, F, n, ptr, idx, val, mask,
+    OPEN_LAUNCH(ctx, name, (k_foldin_small<K, kRowsBuffer, W, OCC, S...>), grid, dim3(64 * W), 0, F, n, ptr, idx, val, mask,
                 lambda, weighted, X, status, m);
   }
   return OPEN_OK;

@@ -66,6 +66,7 @@ __device__ __forceinline__ void swap_lane_rows(float &x0, float &x1, float &x2, 
   quarter(x2, x3);
 }
 
+template <bool FAR>
 __global__ __launch_bounds__(64 * kP64Waves) __attribute__((amdgpu_waves_per_eu(2))) void k_primal64(
     const float *__restrict__ F, int n, const int32_t *__restrict__ idx, const float *__restrict__ val,
     const RowRef *__restrict__ list, const int64_t *__restrict__ cls, int c_lo, int c_hi, float lambda, int weighted,
@@ -152,7 +153,10 @@ __global__ __launch_bounds__(64 * kP64Waves) __attribute__((amdgpu_waves_per_eu(
         for (int e = 0; e < kP64Steps; ++e) {
           const int j = jl[4 * e + o];
           vn[e] = rl[4 * e + o];
-          un[e] = bload_f4(rs, (int)((uint32_t)(j * 64 + 4 * i16) * 4u));  // j = -1 wraps out of range: zeros
+          if constexpr (FAR)
+            un[e] = far_load<4>(F, j, 64, 4 * i16);
+          else
+            un[e] = bload_f4(rs, (int)(((uint32_t)j * 64u + 4u * i16) * 4u));  // j = -1 wraps out of range: zeros
         }
       };
       stage(0);
@@ -279,7 +283,7 @@ OPEN_GROUP(g_k64_primal) {
   const int64_t cap = ctx->num_cu;
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
-  OPEN_LAUNCH(ctx, "ridge_k64_primal", k_primal64, dim3((unsigned)blocks), dim3(64 * kP64Waves), 0, F, n, idx, val,
+  OPEN_LAUNCH(ctx, "ridge_k64_primal", (far_factors(n, 64) ? k_primal64<true> : k_primal64<false>), dim3((unsigned)blocks), dim3(64 * kP64Waves), 0, F, n, idx, val,
               list, cls, kPrimalLo, kPrimalHi, lambda, weighted, X, status);
   return OPEN_OK;
 }

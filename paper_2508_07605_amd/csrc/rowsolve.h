@@ -65,27 +65,41 @@ __device__ __forceinline__ float pick(const float *v, int pi) {
 }
 
 // ---------------------------------------------------------------- factor-row access
-// F rows from LDS or from global memory through a bounds-checked buffer resource.  In LDS a
-// row occupies K + 4 floats (one pad chunk, so that lanes reading the same chunk of different
-// rows spread over the banks) and a row of zeros sits just before row 0: the row index -1 of
-// padded and rejected entries reads zeros without a test, as it does from the buffer
-// resource (a negative offset is out of range there).
-template <int K, bool LDS>
+// F rows from LDS or from global memory, there through a bounds-checked buffer resource or, where
+// its 32-bit offsets do not reach (far_factors), by 64-bit addresses.  In LDS a row occupies K + 4
+// floats (one pad chunk, so that lanes reading the same chunk of different rows spread over the
+// banks) and a row of zeros sits just before row 0: the row index -1 of padded and rejected
+// entries reads zeros without a test, as it does from the buffer resource (a negative offset is
+// out of range there); by address it reads row 0 and drops it.
+enum { kRowsBuffer, kRowsLds, kRowsFar };
+template <int K, int SRC>
 struct FRows {
   static constexpr int PS = K + 4;  // LDS row pitch in floats
   const float *lds;                 // row 0 (row -1 is the zero row)
   __amdgpu_buffer_rsrc_t rs;
+  const float *far;
   __device__ __forceinline__ f4 row4(int j, int k0) const {
-    if constexpr (LDS)
+    if constexpr (SRC == kRowsLds)
       return *reinterpret_cast<const f4 *>(lds + j * PS + k0);
+    else if constexpr (SRC == kRowsFar)
+      return far_load<4>(far, j, K, k0);
     else
-      return bload_f4(rs, (j * K + k0) * 4);
+      return bload_f4(rs, (int)(((uint32_t)j * K + k0) * 4u));
   }
   __device__ __forceinline__ float row1(int j, int k) const {
-    if constexpr (LDS)
+    if constexpr (SRC == kRowsLds)
       return lds[j * PS + k];
+    else if constexpr (SRC == kRowsFar)
+      return far_load<1>(far, j, K, k)[0];
     else
-      return bload_f32(rs, (j * K + k) * 4);
+      return bload_f32(rs, (int)(((uint32_t)j * K + k) * 4u));
+  }
+  // before the first read: from buffer or far, with F and its rows
+  __device__ __forceinline__ void global(const float *F, int n) {
+    if constexpr (SRC == kRowsFar)
+      far = F;
+    else
+      rs = make_rsrc(F, (uint64_t)n * K * sizeof(float));
   }
 };
 
@@ -96,8 +110,8 @@ __host__ __device__ constexpr int wave_lds_floats(int P, int D) {
   return (P < 4 ? 16 * tri_stride(D) : 0) + 2 * (64 / P) * (D + 1);
 }
 
-template <int P, int D, int K, bool DUAL, bool LDSF, bool PF, bool BLK>
-__device__ __forceinline__ void solve_group(const FRows<K, LDSF> &Fr, int n, const RowRef mine,
+template <int P, int D, int K, bool DUAL, int SRC, bool PF, bool BLK>
+__device__ __forceinline__ void solve_group(const FRows<K, SRC> &Fr, int n, const RowRef mine,
                                             const int32_t *__restrict__ idx, const float *__restrict__ val,
                                             float lambda, int weighted, float *__restrict__ X,
                                             int32_t *__restrict__ status, float *__restrict__ wl) {
@@ -627,7 +641,7 @@ struct GroupQueue {
 
 // Persistent kernel over the rows of classes c_lo..c_hi (contiguous in the bucketed list),
 // all solved at padded dimension D (dual) or k (primal).
-template <int K, int P, int D, bool DUAL, bool LDSF, int W, int OCC, bool BLK>
+template <int K, int P, int D, bool DUAL, int SRC, int W, int OCC, bool BLK>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_waves_per_eu(OCC))) void k_solve_class(const float *__restrict__ F, int n,
                                                      const int64_t *__restrict__ ptr, const int32_t *__restrict__ idx,
                                                      const float *__restrict__ val, const RowRef *__restrict__ list,
@@ -636,7 +650,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
                                                      int32_t *__restrict__ status) {
   constexpr int SYS = 64 / P;
   constexpr int WL = wave_lds_floats(P, D);
-  constexpr int FL = LDSF ? factor_lds_bytes<K>() / 4 : 4;
+  constexpr int FL = SRC == kRowsLds ? factor_lds_bytes<K>() / 4 : 4;
   __shared__ __attribute__((aligned(16))) float lds_all[W * WL + FL];
   __shared__ int qnext;
   if (threadIdx.x == 0) qnext = W;
@@ -647,13 +661,13 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   const int64_t g0 = (int64_t)blockIdx.x + (int64_t)gridDim.x * (threadIdx.x >> 6);
   const int64_t groups = (count + SYS - 1) / SYS;
   if ((int64_t)blockIdx.x >= groups) return;  // block has no work (uniform)
-  FRows<K, LDSF> Fr;
-  if constexpr (LDSF) {
+  FRows<K, SRC> Fr;
+  if constexpr (SRC == kRowsLds) {
     Fr.lds = stage_factors<K, W>(F, n, lds_all + W * WL);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   } else {
-    Fr.rs = make_rsrc(F, (uint64_t)n * K * sizeof(float));
+    Fr.global(F, n);
     __syncthreads();
   }
   float *wl = lds_all + (threadIdx.x >> 6) * WL;
@@ -674,7 +688,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
       nxt = fetch(gn);
     }
     // operand prefetch in the Gram loop when a single wave per SIMD has to hide the latency
-    solve_group<P, D, K, DUAL, LDSF, (OCC == 1 || D <= 12), BLK>(Fr, n, cur, idx, val, lambda, weighted, X, status,
+    solve_group<P, D, K, DUAL, SRC, (OCC == 1 || D <= 12), BLK>(Fr, n, cur, idx, val, lambda, weighted, X, status,
                                                                  wl);
     if constexpr (!DUAL) {
       gn = next();
@@ -706,7 +720,7 @@ __host__ __device__ constexpr int multi_wave_floats() {
 // classes, in the order given (the costliest first, so that the cheap ones fill the tail), are
 // one index space that the waves stride through.  Each group is solved exactly as by the
 // class's own kernel.
-template <int K, int P, bool LDSF, int W, int OCC, typename... C>
+template <int K, int P, int SRC, int W, int OCC, typename... C>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_waves_per_eu(OCC))) void k_solve_multi(
     const float *__restrict__ F, int n, const int64_t *__restrict__ ptr, const int32_t *__restrict__ idx,
     const float *__restrict__ val, const RowRef *__restrict__ list, const int64_t *__restrict__ cls, float lambda,
@@ -714,7 +728,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   constexpr int NC = sizeof...(C);
   constexpr int SYS = 64 / P;
   constexpr int WL = multi_wave_floats<P, C...>();
-  constexpr int FL = LDSF ? factor_lds_bytes<K>() / 4 : 4;
+  constexpr int FL = SRC == kRowsLds ? factor_lds_bytes<K>() / 4 : 4;
   __shared__ __attribute__((aligned(16))) float lds_all[W * WL + FL];
   __shared__ int qnext;
   if (threadIdx.x == 0) qnext = W;
@@ -732,13 +746,13 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
   // wave-major: consecutive groups, which cost alike, go to different compute units
   const int64_t g0 = (int64_t)blockIdx.x + (int64_t)gridDim.x * (threadIdx.x >> 6);
   if ((int64_t)blockIdx.x >= total) return;  // block has no work (uniform)
-  FRows<K, LDSF> Fr;
-  if constexpr (LDSF) {
+  FRows<K, SRC> Fr;
+  if constexpr (SRC == kRowsLds) {
     Fr.lds = stage_factors<K, W>(F, n, lds_all + W * WL);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   } else {
-    Fr.rs = make_rsrc(F, (uint64_t)n * K * sizeof(float));
+    Fr.global(F, n);
     __syncthreads();
   }
   float *wl = lds_all + (threadIdx.x >> 6) * WL;
@@ -769,7 +783,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_wa
             gn = next();
             nxt = fetch(gn - gb);
           }
-          solve_group<P, C::D, K, C::DUAL, LDSF, (OCC == 1 || C::D <= 12), false>(Fr, n, cur, idx, val, lambda,
+          solve_group<P, C::D, K, C::DUAL, SRC, (OCC == 1 || C::D <= 12), false>(Fr, n, cur, idx, val, lambda,
                                                                                   weighted, X, status, wl);
           if constexpr (!kAhead) {
             gn = next();
@@ -801,12 +815,12 @@ open_status launch_multi(const char *name, open_ctx *ctx, const float *F, int n,
   if (blocks < 1) blocks = 1;
   if constexpr (fl_fits) {
     if (fl) {
-      OPEN_LAUNCH(ctx, name, (k_solve_multi<K, P, true, W, OCC, C...>), dim3((unsigned)blocks), dim3(64 * W), 0, F, n,
+      OPEN_LAUNCH(ctx, name, (k_solve_multi<K, P, kRowsLds, W, OCC, C...>), dim3((unsigned)blocks), dim3(64 * W), 0, F, n,
                   ptr, idx, val, list, cls, lambda, weighted, X, status);
       return OPEN_OK;
     }
   }
-  OPEN_LAUNCH(ctx, name, (k_solve_multi<K, P, false, W, OCC, C...>), dim3((unsigned)blocks), dim3(64 * W), 0, F, n,
+  OPEN_LAUNCH(ctx, name, (k_solve_multi<K, P, kRowsBuffer, W, OCC, C...>), dim3((unsigned)blocks), dim3(64 * W), 0, F, n,
               ptr, idx, val, list, cls, lambda, weighted, X, status);
   return OPEN_OK;
 }
@@ -814,7 +828,7 @@ open_status launch_multi(const char *name, open_ctx *ctx, const float *F, int n,
 // Launch the kernel of one size class with a persistent grid sized for m rows: blocks of W
 // waves (sharing one LDS copy of the factors), as many per CU as LDS and the register
 // budget of OCC waves per SIMD allow.
-template <int K, int P, int D, bool DUAL, int W = 4, int OCC = 1, bool BLK = false>
+template <int K, int P, int D, bool DUAL, int W, int OCC, bool BLK, bool FAR>
 open_status launch_class(const char *name, open_ctx *ctx, const float *F, int n, const int64_t *ptr,
                          const int32_t *idx, const float *val, float lambda, int weighted, const RowRef *list,
                          const int64_t *cls, int c_lo, int c_hi, float *X, int32_t *status, int64_t m) {
@@ -823,7 +837,7 @@ open_status launch_class(const char *name, open_ctx *ctx, const float *F, int n,
   int64_t blocks = (groups + W - 1) / W;
   constexpr int waves_b = W * wave_bytes<K, P, D>();
   constexpr int flb = factor_lds_bytes<K>();
-  constexpr bool fl_fits = waves_b + flb <= kLdsBytes;
+  constexpr bool fl_fits = !FAR && waves_b + flb <= kLdsBytes;
   static_assert(waves_b + 16 <= kLdsBytes, "per-wave buffers exceed LDS");
   // stage the factors in LDS when they fit beside the per-wave buffers
   const bool fl = fl_fits && n <= kFactorLdsRows;
@@ -835,12 +849,13 @@ open_status launch_class(const char *name, open_ctx *ctx, const float *F, int n,
   if (blocks < 1) blocks = 1;
   if constexpr (fl_fits) {
     if (fl) {
-      OPEN_LAUNCH(ctx, name, (k_solve_class<K, P, D, DUAL, true, W, OCC, BLK>), dim3((unsigned)blocks), dim3(64 * W), 0,
+      OPEN_LAUNCH(ctx, name, (k_solve_class<K, P, D, DUAL, kRowsLds, W, OCC, BLK>), dim3((unsigned)blocks), dim3(64 * W), 0,
                   F, n, ptr, idx, val, list, cls, c_lo, c_hi, lambda, weighted, X, status);
       return OPEN_OK;
     }
   }
-  OPEN_LAUNCH(ctx, name, (k_solve_class<K, P, D, DUAL, false, W, OCC, BLK>), dim3((unsigned)blocks), dim3(64 * W), 0, F,
+  constexpr int src = FAR ? kRowsFar : kRowsBuffer;
+  OPEN_LAUNCH(ctx, name, (k_solve_class<K, P, D, DUAL, src, W, OCC, BLK>), dim3((unsigned)blocks), dim3(64 * W), 0, F,
               n, ptr, idx, val, list, cls, c_lo, c_hi, lambda, weighted, X, status);
   return OPEN_OK;
 }
@@ -856,16 +871,30 @@ open_status launch_class(const char *name, open_ctx *ctx, const float *F, int n,
 // update) elimination.
 constexpr int cfg(int P, int W, int OCC, int BLK = 0) { return BLK * 1000000 + P * 10000 + W * 100 + OCC; }
 
-// Launch configuration number `choice` of C... for one class group.
+// Launch configuration number `choice` of C... for one class group (the first one for factors out
+// of a buffer resource's reach).
 template <int K, int D, bool DUAL, int... C>
 open_status launch_variant(int choice, const char *name, int c_lo, int c_hi, OPEN_TIER_ARGS) {
   open_status st = OPEN_OK;
   int i = 0;
   bool done = false;
-  ((i++ == choice ? (void)(done = true, st = launch_class<K, (C / 10000) % 100, D, DUAL, (C / 100) % 100, C % 100, (C / 1000000) != 0>(
-                                            name, OPEN_TIER_PASS, c_lo, c_hi, X, status, m))
-                  : (void)0),
-   ...);
+  const bool far = far_factors(n, K);
+  auto one = [&](auto Cc, auto First) {
+    constexpr int c = decltype(Cc)::value, p = (c / 10000) % 100, w = (c / 100) % 100, occ = c % 100;
+    constexpr bool blk = (c / 1000000) != 0;
+    if constexpr (decltype(First)::value) {
+      if (far && choice >= 0 && choice < (int)sizeof...(C)) {
+        done = true;
+        st = launch_class<K, p, D, DUAL, w, occ, blk, true>(name, OPEN_TIER_PASS, c_lo, c_hi, X, status, m);
+      }
+    }
+    if (!far && i++ == choice) {
+      done = true;
+      st = launch_class<K, p, D, DUAL, w, occ, blk, false>(name, OPEN_TIER_PASS, c_lo, c_hi, X, status, m);
+    }
+  };
+  constexpr int c0 = [](int first, auto...) { return first; }(C...);
+  (one(std::integral_constant<int, C>{}, std::integral_constant<bool, C == c0>{}), ...);
   if (!done) return fail(ctx, OPEN_E_INVALID, "kernel variant out of range");
   return st;
 }

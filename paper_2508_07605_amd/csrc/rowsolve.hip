@@ -97,7 +97,8 @@ open_status rowsolve_launch(open_ctx *ctx, const float *F, int n, int k, const i
   const ClassGroup *g = class_groups(k, &ng);
   if (!g) return fail(ctx, OPEN_E_UNSUPPORTED, "rank must be 8, 16, 32 or 64");
   const int ri = rank_index(k);
-  if (launch_mode(ctx, k, g, ng) == 0) return rowsolve_k32_merged(OPEN_TIER_PASS, X, status, m);
+  if (launch_mode(ctx, k, g, ng) == 0 && !far_factors(n, k))
+    return rowsolve_k32_merged(OPEN_TIER_PASS, X, status, m);
   for (int i = 0; i < ng; ++i) {
     if (!g[i].fn) continue;
     open_status st = g[i].fn(ctx->tune[ri][i], OPEN_TIER_PASS, X, status, m);
