@@ -62,17 +62,46 @@ __device__ __forceinline__ f16v tile(const float (&a)[K / 2], const float *Vt, i
 
 // The rule's validity test 1 - p / p_base <= gamma (float32, correctly rounded division and
 // subtraction) is monotone in p for p_base > 0: fl(p / p_base) does not decrease as p grows and
-// fl(1 - x) does not increase as x grows.  So it holds exactly for p >= t, t the least float
-// for which it holds, found once per row from the real threshold (1 - gamma) p_base by stepping
-// a few units in the last place (the two roundings move it by about two).
-__device__ __forceinline__ bool loss_ok(float p, float pb, float gamma) { return (1.0f - p / pb) <= gamma; }
+// fl(1 - x) does not increase as x grows.  So it holds exactly for p >= t, t the least float for
+// which it holds, found once per row.  The real threshold (1 - gamma) p_base is one or two units in
+// the last place off at small gamma, so five neighbours are tried at once; as gamma nears 1 the
+// rounding of 1 - x spans many units (400 at 0.999, 3 % of t at 0.999999), and the distance doubles
+// until t is enclosed and is then halved.  (The bits of positive floats are ordered as the floats
+// are; negative numbers and NaN fail.)
+__device__ __forceinline__ bool loss_ok(int p, float pb, float gamma) {
+  return (1.0f - __builtin_bit_cast(float, p) / pb) <= gamma;
+}
 __device__ __forceinline__ float least_valid(float pb, float gamma) {
-  float t = (1.0f - gamma) * pb;
-  if (!(t > 0.f)) return __builtin_bit_cast(float, 1);  // gamma >= 1: every p > 0 passes
-  auto step = [](float x, int d) { return __builtin_bit_cast(float, __builtin_bit_cast(int, x) + d); };
-  for (int i = 0; i < 64 && loss_ok(step(t, -1), pb, gamma); ++i) t = step(t, -1);
-  for (int i = 0; i < 64 && !loss_ok(t, pb, gamma); ++i) t = step(t, 1);
-  return t;
+  if (gamma >= 1.0f) return __builtin_bit_cast(float, 1);  // every p > 0 passes
+  if (!(pb < __builtin_inff())) return __builtin_nanf("");  // 1 - 0 and 1 - inf / inf: none passes
+  const int top = __builtin_bit_cast(int, pb);  // passes: 1 - 1 <= gamma
+  const int t = __builtin_bit_cast(int, (1.0f - gamma) * pb);
+  int lo = t, hi = t;  // lo fails, hi passes
+  bool ok[5];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) ok[i] = loss_ok(t - 2 + i, pb, gamma);
+  if (!ok[0] && ok[4]) return __builtin_bit_cast(float, t + 2 - ok[1] - ok[2] - ok[3]);
+  if (ok[2]) {
+    for (int d = 1;; d *= 2) {
+      lo = hi - d > 0 ? hi - d : 0;  // 0 fails
+      if (lo == 0 || !loss_ok(lo, pb, gamma)) break;
+      hi = lo;
+    }
+  } else {
+    for (int d = 1;; d *= 2) {
+      hi = top - lo > d ? lo + d : top;
+      if (hi == top || loss_ok(hi, pb, gamma)) break;
+      lo = hi;
+    }
+  }
+  while (hi - lo > 1) {
+    const int mid = lo + (hi - lo) / 2;
+    if (loss_ok(mid, pb, gamma))
+      hi = mid;
+    else
+      lo = mid;
+  }
+  return __builtin_bit_cast(float, hi);
 }
 
 // lane moves within a row of 16 lanes: neighbours, pairs, and the mirrors, which once lanes hold
