@@ -23,11 +23,15 @@ namespace openk {
 // one block of 16 wavefronts per CU.  12.7M entries, 200,003 x 480: count 28, scan 14, place
 // 128 us; stored entry by entry as ranked 358 us, and with chunks of 256 rows per wavefront that
 // walked its rows one by one 109, 15 and 860.  19.5M entries, 500,009 x 1920: place 278 us, stored
-// as ranked 577.
+// as ranked 577.  Every window ranks all of the chunk's entries again, so a chunk of more than
+// kCscMaxWins windows stores them as ranked, once: whole view of full rows, windows against as
+// ranked, 50,000 x 1920 (24 windows) 9.2 and 4.9 ms, 3000 x 4096 (94) 32 and 2.0, 100,000 x 960
+// (12) 4.7 and 4.4, 50,000 rows of 900 in 1920 (11) 2.33 and 2.46, 100,000 x 480 (6) 1.5 and 2.0.
 constexpr int kCscRows = 128;          // rows of a chunk: two 64-bit masks per column
 constexpr int kCscThreads = 512;
 constexpr int kCscPlaceThreads = 1024;
 constexpr int kCscWin = 10240;         // entries put in order in LDS at a time (fewer for many columns)
+constexpr int kCscMaxWins = 12;        // more of them in a chunk: its entries are stored as ranked
 constexpr int kCscSeg = 64;            // chunks of a scan segment
 constexpr int kMaxCols = 4096;
 
@@ -155,7 +159,8 @@ __global__ __launch_bounds__(1024) void k_csc_bases(int n, int nseg, int64_t *__
 }
 
 // The chunk's entries are first put in order in LDS, `win` of them at a time, and then written out
-// in that order: neighbouring lanes write neighbouring entries of a column.
+// in that order: neighbouring lanes write neighbouring entries of a column.  (Too many for that:
+// stored as ranked.)
 __global__ __launch_bounds__(kCscPlaceThreads) void k_csc_place(int64_t m, int n, const int64_t *__restrict__ ptr,
                                                                 const int32_t *__restrict__ col,
                                                                 const float *__restrict__ val, int nchunk, int win,
@@ -200,16 +205,32 @@ __global__ __launch_bounds__(kCscPlaceThreads) void k_csc_place(int64_t m, int n
     shift[j] = seg[(int64_t)(chunk / kCscSeg) * n + j] + hist[(int64_t)chunk * n + j] - run;
     run += count(j);
   }
+  // rank of the entry of row r among the chunk's entries of column j
+  auto rank_of = [&](int j, int r) {
+    const unsigned long long lo = mask_s[2 * j], hi = mask_s[2 * j + 1];
+    const unsigned long long below = (1ull << (r & 63)) - 1ull;
+    return r < 64 ? __popcll(lo & below) : __popcll(lo) + __popcll(hi & below);
+  };
+  if (total > kCscMaxWins * win) {
+    __syncthreads();
+#pragma unroll 4
+    for (int t = threadIdx.x; t < c.len; t += TH) {
+      const int j = col[c.e0 + t];
+      if (j < 0 || j >= n) continue;
+      const int r = csc_row(rp, t);
+      const int64_t p = shift[j] + first[j] + rank_of(j, r);
+      row_idx[p] = (int32_t)(c.r0 + r);
+      cval[p] = val[c.e0 + t];
+    }
+    return;
+  }
   for (int w0 = 0; w0 < total; w0 += win) {
     __syncthreads();
     for (int t = threadIdx.x; t < c.len; t += TH) {
       const int j = col[c.e0 + t];
       if (j < 0 || j >= n) continue;
       const int r = csc_row(rp, t);
-      const unsigned long long lo = mask_s[2 * j], hi = mask_s[2 * j + 1];
-      const unsigned long long below = (1ull << (r & 63)) - 1ull;
-      const int rank = r < 64 ? __popcll(lo & below) : __popcll(lo) + __popcll(hi & below);
-      const int q = first[j] + rank - w0;
+      const int q = first[j] + rank_of(j, r) - w0;
       if (q >= 0 && q < win) ent[q] = uint2{(uint32_t)(j * kCscRows + r), __builtin_bit_cast(uint32_t, val[c.e0 + t])};
     }
     __syncthreads();
