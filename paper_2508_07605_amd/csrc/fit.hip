@@ -33,14 +33,17 @@ constexpr int kCscPlaceThreads = 1024;
 constexpr int kCscWin = 10240;         // entries put in order in LDS at a time (fewer for many columns)
 constexpr int kCscMaxWins = 12;        // more of them in a chunk: its entries are stored as ranked
 constexpr int kCscSeg = 64;            // chunks of a scan segment
+// chunks of a launch: a grid holds fewer than 2^32 threads, which 2^31 rows would pass
+constexpr int kCscLaunchChunks = 1 << 21;
+static_assert(kCscLaunchChunks % kCscSeg == 0, "a launch holds whole segments");
 constexpr int kMaxCols = 4096;
 
-// the chunk of a block: blocks are dealt to the 8 XCDs round-robin, so XCD x walks the x-th
-// eighth of the chunks
-__device__ __forceinline__ int csc_chunk(int nchunk) {
-  const int per = (nchunk + 7) / 8;
+// the chunk of a block among the launch's `count` from chunk0 on: blocks are dealt to the 8 XCDs
+// round-robin, so XCD x walks the x-th eighth of them
+__device__ __forceinline__ int csc_chunk(int chunk0, int count) {
+  const int per = (count + 7) / 8;
   const int c = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-  return (int)(blockIdx.x >> 3) < per && c < nchunk ? c : -1;
+  return (int)(blockIdx.x >> 3) < per && c < count ? chunk0 + c : -1;
 }
 
 // the chunk's row pointers relative to its first entry, and the column masks
@@ -82,11 +85,11 @@ __device__ __forceinline__ void csc_masks(const CscChunk &c, int n, const int32_
 }
 
 __global__ __launch_bounds__(kCscThreads) void k_csc_count(int64_t m, int n, const int64_t *__restrict__ ptr,
-                                                           const int32_t *__restrict__ col, int nchunk,
+                                                           const int32_t *__restrict__ col, int chunk0, int count,
                                                            int32_t *__restrict__ hist) {
   extern __shared__ unsigned long long mask_s[];  // [n][2]
   __shared__ int rp[kCscRows + 1];
-  const int chunk = csc_chunk(nchunk);
+  const int chunk = csc_chunk(chunk0, count);
   if (chunk < 0) return;
   const CscChunk c = csc_begin<kCscThreads>(m, n, ptr, chunk, rp, mask_s);
   csc_masks<kCscThreads>(c, n, col, rp, mask_s);
@@ -95,9 +98,9 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_count(int64_t m, int n, con
 }
 
 // hist[c][j] -> entries of column j in the chunks of c's segment before c; seg[s][j] = its total
-__global__ __launch_bounds__(256) void k_csc_segments(int n, int nchunk, int32_t *__restrict__ hist,
+__global__ __launch_bounds__(256) void k_csc_segments(int n, int nchunk, int seg0, int32_t *__restrict__ hist,
                                                       int64_t *__restrict__ seg) {
-  const int j = blockIdx.x * 256 + threadIdx.x, c0 = blockIdx.y * kCscSeg;
+  const int j = blockIdx.x * 256 + threadIdx.x, sg = seg0 + (int)blockIdx.y, c0 = sg * kCscSeg;
   if (j >= n) return;
   int run = 0;
   for (int b = 0; b < kCscSeg; b += 16) {
@@ -110,7 +113,7 @@ __global__ __launch_bounds__(256) void k_csc_segments(int n, int nchunk, int32_t
       run += v[e];
     }
   }
-  seg[(int64_t)blockIdx.y * n + j] = run;
+  seg[(int64_t)sg * n + j] = run;
 }
 
 // seg[s][j] -> position of segment s's first entry of column j; col_ptr.  One block; thread t owns
@@ -163,7 +166,8 @@ __global__ __launch_bounds__(1024) void k_csc_bases(int n, int nseg, int64_t *__
 // stored as ranked.)
 __global__ __launch_bounds__(kCscPlaceThreads) void k_csc_place(int64_t m, int n, const int64_t *__restrict__ ptr,
                                                                 const int32_t *__restrict__ col,
-                                                                const float *__restrict__ val, int nchunk, int win,
+                                                                const float *__restrict__ val, int chunk0, int count,
+                                                                int win,
                                                                 const int32_t *__restrict__ hist,
                                                                 const int64_t *__restrict__ seg,
                                                                 int32_t *__restrict__ row_idx,
@@ -176,15 +180,15 @@ __global__ __launch_bounds__(kCscPlaceThreads) void k_csc_place(int64_t m, int n
   int64_t *shift = reinterpret_cast<int64_t *>(mask_s + 2 * n);
   uint2 *ent = reinterpret_cast<uint2 *>(shift + n);
   int *first = reinterpret_cast<int *>(ent + win);
-  const int chunk = csc_chunk(nchunk);
+  const int chunk = csc_chunk(chunk0, count);
   if (chunk < 0) return;
   const CscChunk c = csc_begin<TH>(m, n, ptr, chunk, rp, mask_s);
   csc_masks<TH>(c, n, col, rp, mask_s);
   // exclusive scan of the columns' counts: thread t owns columns per t .. per t + per - 1
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, per = (n + TH - 1) / TH;
-  auto count = [&](int j) { return __popcll(mask_s[2 * j]) + __popcll(mask_s[2 * j + 1]); };
+  auto entries = [&](int j) { return __popcll(mask_s[2 * j]) + __popcll(mask_s[2 * j + 1]); };
   int own = 0;
-  for (int j = per * threadIdx.x; j < per * ((int)threadIdx.x + 1) && j < n; ++j) own += count(j);
+  for (int j = per * threadIdx.x; j < per * ((int)threadIdx.x + 1) && j < n; ++j) own += entries(j);
   int run = own;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -203,7 +207,7 @@ __global__ __launch_bounds__(kCscPlaceThreads) void k_csc_place(int64_t m, int n
   for (int j = per * threadIdx.x; j < per * ((int)threadIdx.x + 1) && j < n; ++j) {
     first[j] = run;
     shift[j] = seg[(int64_t)(chunk / kCscSeg) * n + j] + hist[(int64_t)chunk * n + j] - run;
-    run += count(j);
+    run += entries(j);
   }
   // rank of the entry of row r among the chunk's entries of column j
   auto rank_of = [&](int j, int r) {
@@ -281,20 +285,25 @@ open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, const int64_t *row_p
     return st;
   if ((st = ws_get(ctx, open_ctx::WS_SPLIT, sizeof(int64_t) * (size_t)n * (size_t)(nseg > 0 ? nseg : 1), &seg)))
     return st;
-  const dim3 blocks(8 * (unsigned)((nchunk + 7) / 8)), threads(kCscThreads);
   const size_t lds = sizeof(unsigned long long) * 2 * (size_t)n;
-  if (nchunk > 0) {
-    OPEN_LAUNCH(ctx, "csc_count", k_csc_count, blocks, threads, lds, m, n, row_ptr, col, nchunk, (int32_t *)hist);
-    OPEN_LAUNCH(ctx, "csc_segments", k_csc_segments, dim3((unsigned)((n + 255) / 256), (unsigned)nseg), dim3(256), 0, n,
-                nchunk, (int32_t *)hist, (int64_t *)seg);
+  const size_t cols = (2 * sizeof(unsigned long long) + sizeof(int64_t) + sizeof(int)) * (size_t)n;
+  const size_t room = (size_t)(156 * 1024 - cols) / sizeof(uint2);  // n <= kMaxCols: at least 5632
+  const int win = room < (size_t)kCscWin ? (int)room : kCscWin;
+  auto launch_chunks = [&](int c0) { return nchunk - c0 < kCscLaunchChunks ? nchunk - c0 : kCscLaunchChunks; };
+  auto launch_blocks = [](int count) { return dim3(8 * (unsigned)((count + 7) / 8)); };
+  for (int c0 = 0; c0 < nchunk; c0 += launch_chunks(c0)) {
+    const int count = launch_chunks(c0), segs = (count + kCscSeg - 1) / kCscSeg;
+    OPEN_LAUNCH(ctx, "csc_count", k_csc_count, launch_blocks(count), dim3(kCscThreads), lds, m, n, row_ptr, col, c0,
+                count, (int32_t *)hist);
+    OPEN_LAUNCH(ctx, "csc_segments", k_csc_segments, dim3((unsigned)((n + 255) / 256), (unsigned)segs), dim3(256), 0, n,
+                nchunk, c0 / kCscSeg, (int32_t *)hist, (int64_t *)seg);
   }
   OPEN_LAUNCH(ctx, "csc_bases", k_csc_bases, dim3(1), dim3(1024), 0, n, nseg, (int64_t *)seg, col_ptr);
-  if (nchunk > 0) {
-    const size_t cols = (2 * sizeof(unsigned long long) + sizeof(int64_t) + sizeof(int)) * (size_t)n;
-    const size_t room = (size_t)(156 * 1024 - cols) / sizeof(uint2);  // n <= kMaxCols: at least 5632
-    const int win = room < (size_t)kCscWin ? (int)room : kCscWin;
-    OPEN_LAUNCH(ctx, "csc_place", k_csc_place, blocks, dim3(kCscPlaceThreads), cols + sizeof(uint2) * (size_t)win, m, n,
-                row_ptr, col, val, nchunk, win, (const int32_t *)hist, (const int64_t *)seg, row_idx, cval);
+  for (int c0 = 0; c0 < nchunk; c0 += launch_chunks(c0)) {
+    const int count = launch_chunks(c0);
+    OPEN_LAUNCH(ctx, "csc_place", k_csc_place, launch_blocks(count), dim3(kCscPlaceThreads),
+                cols + sizeof(uint2) * (size_t)win, m, n, row_ptr, col, val, c0, count, win, (const int32_t *)hist,
+                (const int64_t *)seg, row_idx, cval);
   }
   return OPEN_OK;
 }

@@ -1,0 +1,35 @@
+"""More rows than one launch's threads can cover (a grid holds fewer than 2^32): the column view past
+2^29 rows, of which only a few hold entries."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2508_07605_amd import native
+
+pytestmark = pytest.mark.gpu
+
+
+def row_pointers(m, rows):
+    """Row pointers of m rows of which `rows` (ascending) hold one entry each."""
+    rp = torch.zeros(m + 1, dtype=torch.int64, device="cuda")
+    for e, i in enumerate(rows):
+        rp[i + 1:] = e + 1
+    return rp
+
+
+def test_column_view():
+    m, n = 2 ** 29 + 128 * 8200 + 5, 5
+    rows = [0, 127, 128, 2 ** 28 - 1, 2 ** 28, 2 ** 28 + 127, 2 ** 29 - 1, 2 ** 29, 2 ** 29 + 128 * 8192, m - 1]
+    col = np.array([4, 0, 4, 2, 4, 2, 0, 0, 2, 4], np.int32)
+    val = np.arange(1, 11, dtype=np.float32)
+    ctx = native.Context(0)
+    try:
+        cp, ri, cv = native.open_csr_to_csc(ctx, row_pointers(m, rows), torch.from_numpy(col).cuda(),
+                                            torch.from_numpy(val).cuda(), n)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    order = np.lexsort((rows, col))
+    assert cp.cpu().tolist() == [0, 3, 3, 6, 6, 10]
+    assert np.array_equal(ri.cpu().numpy(), np.array(rows)[order])
+    assert np.array_equal(cv.cpu().numpy(), val[order])
