@@ -708,9 +708,15 @@ open_status open_mlp_forward(open_mlp *p, int64_t m, const int64_t *row_ptr, con
     return fail(ctx, OPEN_E_INVALID, "bad shape or pointer");
   OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
   if (m == 0) return OPEN_OK;
-  MlpBatch b = mlp_batch(p, m, nullptr, 0, row_ptr, col, val);
-  b.out = U_hat;
-  return mlp_batch_launch(ctx, b, true);
+  // a launch takes 2^26 rows at most: 512 threads for every 32 rows, fewer than 2^32 in a grid
+  constexpr int64_t kLaunchRows = int64_t(1) << 26;
+  open_status st = OPEN_OK;
+  for (int64_t r0 = 0; r0 < m && !st; r0 += kLaunchRows) {
+    MlpBatch b = mlp_batch(p, m - r0 < kLaunchRows ? m - r0 : kLaunchRows, nullptr, 0, row_ptr + r0, col, val);
+    b.out = U_hat + r0 * p->k;
+    st = mlp_batch_launch(ctx, b, true);
+  }
+  return st;
 }
 
 open_status open_mlp_loss_grad(open_mlp *p, int64_t m, const int64_t *row_ptr, const int32_t *col,

@@ -1,5 +1,5 @@
 """More rows than one launch's threads can cover (a grid holds fewer than 2^32): the column view past
-2^29 rows, of which only a few hold entries."""
+2^29 rows and the surrogate's forward pass past 2^28, of which only a few hold entries."""
 import numpy as np
 import pytest
 import torch
@@ -33,3 +33,26 @@ def test_column_view():
     assert cp.cpu().tolist() == [0, 3, 3, 6, 6, 10]
     assert np.array_equal(ri.cpu().numpy(), np.array(rows)[order])
     assert np.array_equal(cv.cpu().numpy(), val[order])
+
+
+def test_forward():
+    """Every row's output is, bit for bit, that of the same row in a small batch."""
+    m, n, k = 2 ** 28 + 1001, 40, 8
+    rows = [0, 5, 2 ** 26 - 1, 2 ** 26, 2 ** 27 + 3, 2 ** 28 - 1, 2 ** 28, 2 ** 28 + 1000]
+    r = np.random.default_rng(4)
+    col = torch.from_numpy(r.integers(0, n, size=len(rows)).astype(np.int32)).cuda()
+    val = torch.from_numpy(r.uniform(0.4, 1.0, size=len(rows)).astype(np.float32)).cuda()
+    ctx = native.Context(0)
+    net = native.Surrogate(ctx, n, k, seed=2)
+    try:
+        out = torch.full((m, k), 7.0, device="cuda")
+        net.forward(row_pointers(m, rows), col, val, out)
+        few = net.forward(row_pointers(len(rows) + 1, range(len(rows))), col, val)
+        torch.cuda.synchronize()
+    finally:
+        net.close()
+        ctx.close()
+    assert torch.equal(out[rows], few[:-1])
+    same = (out == few[-1]).all(dim=1)
+    same[rows] = True
+    assert bool(same.all())
