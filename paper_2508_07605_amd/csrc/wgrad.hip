@@ -269,17 +269,24 @@ __device__ __forceinline__ void setting_embeddings(const WgradStep &p, int q) {
     p.g[e.s + t] = x;
 }
 
-// 1024 elements of E: the applications outside the batch have zero gradient (Adam still moves
-// them by their moments)
+// blocks of other_embeddings, 1024 elements each: capped, since a grid holds fewer than 2^32 threads
+constexpr int64_t kWgMaxOther = int64_t(1) << 20;
+__host__ __device__ inline int other_blocks(int64_t m) {
+  const int64_t b = (m * kEmbD + kWgThreads - 1) / kWgThreads;
+  return (int)(b < kWgMaxOther ? b : kWgMaxOther);
+}
+// Elements of E, 1024 at a time: the applications outside the batch have zero gradient (Adam still
+// moves them by their moments)
 template <bool ADAM>
 __device__ __forceinline__ void other_embeddings(const WgradStep &p, int q) {
   const WgradEmb &e = p.emb;
-  const int64_t t = (int64_t)q * kWgThreads + threadIdx.x;
-  if (t >= e.m * kEmbD || e.mark[t / kEmbD] == p.st->tag) return;
-  if constexpr (ADAM)
-    adam_update(p, e.e + t, 0.f, p.st->c1, p.st->c2);
-  else
-    p.g[e.e + t] = 0.f;
+  for (int64_t t = (int64_t)q * kWgThreads + threadIdx.x; t < e.m * kEmbD; t += kWgMaxOther * kWgThreads) {
+    if (e.mark[t / kEmbD] == p.st->tag) continue;
+    if constexpr (ADAM)
+      adam_update(p, e.e + t, 0.f, p.st->c1, p.st->c2);
+    else
+      p.g[e.e + t] = 0.f;
+  }
 }
 
 // the batch loss, and the step state's counters (read by no other block of this launch)
@@ -312,7 +319,7 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad_step(WgradStep p) {
   int q = blockIdx.x;
   if (p.emb.G > 0) {
     const int ns = (int)(((int64_t)p.emb.n * kEmbD + kWgThreads - 1) / kWgThreads);
-    const int no = (int)((p.emb.m * kEmbD + kWgThreads - 1) / kWgThreads);
+    const int no = other_blocks(p.emb.m);
     if (q < p.emb.G) return app_embedding<ADAM>(p, q, buf);
     q -= p.emb.G;
     if (q < ns) return setting_embeddings<ADAM>(p, q);
@@ -342,8 +349,7 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad_step(WgradStep p) {
 open_status wgrad_step(open_ctx *ctx, const char *name, WgradStep p, bool adam) {
   unsigned blocks = 1;
   if (p.emb.G > 0)
-    blocks += (unsigned)(p.emb.G + ((int64_t)p.emb.n * kEmbD + kWgThreads - 1) / kWgThreads +
-                         (p.emb.m * kEmbD + kWgThreads - 1) / kWgThreads);
+    blocks += (unsigned)(p.emb.G + ((int64_t)p.emb.n * kEmbD + kWgThreads - 1) / kWgThreads + other_blocks(p.emb.m));
   for (WgradLayer &l : p.l) {
     l.S = wgrad_slices(p.B, l.M, l.N, &l.kc);
     wgrad_shape(l);

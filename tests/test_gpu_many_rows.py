@@ -1,10 +1,11 @@
 """More rows than one launch's threads can cover (a grid holds fewer than 2^32): the column view past
-2^29 rows and the surrogate's forward pass past 2^28, of which only a few hold entries."""
+2^29 rows and the surrogate's forward pass past 2^28, of which only a few hold entries, and the NCF
+model's gradient with 2^27 applications and more."""
 import numpy as np
 import pytest
 import torch
 
-from paper_2508_07605_amd import native
+from paper_2508_07605_amd import native, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +57,33 @@ def test_forward():
     same = (out == few[-1]).all(dim=1)
     same[rows] = True
     assert bool(same.all())
+
+
+def test_ncf_gradient():
+    """The gradient of a batch of a few applications out of many: theirs and the network's bit for
+    bit as in a model of those applications alone, zero for the others."""
+    m, n, d = 2 ** 27 + 4096, 3, 32
+    apps = [m - 1, 17, 2 ** 27, 2 ** 27 - 1]
+    p = synth.ncf_params(3, n, seed=1)
+    S = p.pop("S")
+    E = np.random.default_rng(6).normal(size=(len(apps), d)).astype(np.float32)
+    few = torch.from_numpy(native.ncf_pack(E, S, p)).cuda()
+    rest = few.numel() - len(apps) * d
+    many = torch.zeros(m * d + rest, device="cuda")
+    many[m * d:] = few[len(apps) * d:]
+    many[:m * d].view(m, d)[apps] = torch.from_numpy(E).cuda()
+    R = torch.full((m, n), 0.7, device="cuda")
+    ctx = native.Context(0)
+    try:
+        loss, g = native.open_ncf_loss_grad(ctx, R, many, torch.tensor(apps, device="cuda"))
+        want_loss, want = native.open_ncf_loss_grad(ctx, R[:len(apps)].contiguous(), few,
+                                                    torch.arange(len(apps), device="cuda"))
+    finally:
+        ctx.close()
+    assert loss == want_loss
+    assert np.array_equal(g[m * d:], want[len(apps) * d:]) and want[len(apps) * d:].any()
+    gE = g[:m * d].reshape(m, d)
+    assert np.array_equal(gE[apps], want[:len(apps) * d].reshape(-1, d))
+    gE[apps] = 0.0
+    for a in range(0, m, 2 ** 22):
+        assert not gE[a:a + 2 ** 22].any()
