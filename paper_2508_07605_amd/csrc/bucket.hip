@@ -31,7 +31,7 @@ __device__ __forceinline__ int row_class(int64_t cnt, int k, int64_t split_min) 
   if (cnt >= split_min) return kSplitClass;
   // primal: v = 4 (n_i - 1) / k >= 4 past one doubling; its leading bit and the two bits below it
   // (rank 64 reaches here from n_i = 33, where v is 2 or 3)
-  const int64_t v = 4 * (cnt - 1) / k;
+  const int64_t v = (4 * (cnt - 1)) >> __builtin_ctz((unsigned)k);  // k is a power of two
   if (v < 4) return kPrimalLo;
   const int o = 61 - __clzll((unsigned long long)v);  // v in [4 2^o, 8 2^o)
   const int c = kPrimalLo + 4 * o + (int)((v >> o) & 3);
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_class_place(int64_t m, const
   if constexpr (SELF_SCAN) {
     __shared__ int tot[kNumClasses], pre[kNumClasses];
     const int nblk = (int)gridDim.x, me = (int)blockIdx.x;
-    // wave w sums classes w, w + 8, w + 16: every count it needs is loaded before any is added
+    // wave w sums classes w, w + 8, w + 16, w + 24: every count it needs is loaded before any is added
     // (one round trip to L2 instead of one per class and per 64 blocks)
     constexpr int WV = kBucketThreads / kWave, CW = (kNumClasses + WV - 1) / WV, BL = kSelfScanMaxBlocks / kWave;
     const __amdgpu_buffer_rsrc_t ro = make_rsrc(offs, (uint64_t)kNumClasses * nblk * sizeof(int32_t));
@@ -242,12 +242,19 @@ __global__ __launch_bounds__(kBucketThreads) void k_class_place(int64_t m, const
     }
     __syncthreads();
     if (tid < kNumClasses) {
-      int start = 0;
-      for (int c = 0; c < tid; ++c) start += tot[c];
+      static_assert(kNumClasses <= kWave, "one lane a class");
+      const int own = tot[tid];
+      int start = own;
+#pragma unroll
+      for (int off = 1; off < kNumClasses; off <<= 1) {
+        const int x = __shfl_up(start, off, kWave);
+        start += tid >= off ? x : 0;
+      }
+      start -= own;
       run[tid] = start + pre[tid];
       if (me == 0) {
         cls[2 * tid] = start;
-        cls[2 * tid + 1] = tot[tid];
+        cls[2 * tid + 1] = own;
       }
     }
   } else {
