@@ -277,7 +277,7 @@ static open_status foldin_prepare(open_ctx *ctx, int32_t n, int32_t k, int64_t m
     OPEN_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     *nnz_split = *h;
   }
-  if ((st = bucket_rows(ctx, m, row_ptr, k, list, cls, *nnz_split >= 0 ? kSplitMin : INT64_MAX))) return st;
+  if ((st = bucket_rows(ctx, m, row_ptr, n, k, list, cls, *nnz_split >= 0 ? kSplitMin : INT64_MAX))) return st;
   return OPEN_OK;
 }
 
@@ -374,7 +374,7 @@ open_status open_foldin_noalloc(open_ctx *ctx, const float *F, int32_t n, int32_
   RowRef *list = (RowRef *)(base + kScrList);
   int32_t *hist = (int32_t *)(base + kScrHist);
   int64_t *cls = (int64_t *)(base + kScrCls);
-  if ((st = bucket_rows_into(ctx, m, row_ptr, k, hist, list, cls, INT64_MAX))) return st;
+  if ((st = bucket_rows_into(ctx, m, row_ptr, n, k, hist, list, cls, INT64_MAX))) return st;
   return rowsolve_launch(ctx, F, n, k, row_ptr, col, val, lambda, weighted, list, cls, U_out, row_status, m);
 }
 

@@ -6,7 +6,8 @@
 //   classes 1..8         dual form, system dimension padded to 4*class (n_i <= min(k, 32))
 //   classes 9..30        primal form (k x k system), four classes per doubling of n_i / k (class
 //                        9 also takes n_i in (32, 64] at rank 64): the 16 rows of a group run to
-//                        their longest, 30 % more than their mean at one class per doubling
+//                        their longest, 30 % more than their mean at one class per doubling; rows of
+//                        up to coarse_max entries one class per doubling
 //   class 31             rows long enough for the split-K path
 // Exact integer work; the resulting list is independent of scheduling.
 #include "common.h"
@@ -24,7 +25,7 @@ constexpr int kRowsPerWave = kRowsPerBlock / (kBucketThreads / kWave);  // conti
 // (each block reads kNumClasses * nblk counts from L2), so no scan launch is needed.
 constexpr int kSelfScanMaxBlocks = 512;
 
-__device__ __forceinline__ int row_class(int64_t cnt, int k, int64_t split_min) {
+__device__ __forceinline__ int row_class(int64_t cnt, int k, int coarse_max, int64_t split_min) {
   if (cnt <= 0) return 0;
   const int dmax = k < 32 ? k : 32;
   if (cnt <= dmax) return (int)((cnt + 3) >> 2);
@@ -34,7 +35,7 @@ __device__ __forceinline__ int row_class(int64_t cnt, int k, int64_t split_min) 
   const int64_t v = (4 * (cnt - 1)) >> __builtin_ctz((unsigned)k);  // k is a power of two
   if (v < 4) return kPrimalLo;
   const int o = 61 - __clzll((unsigned long long)v);  // v in [4 2^o, 8 2^o)
-  const int c = kPrimalLo + 4 * o + (int)((v >> o) & 3);
+  const int c = kPrimalLo + 4 * o + (cnt <= coarse_max ? 0 : (int)((v >> o) & 3));
   return c < kPrimalHi ? c : kPrimalHi;
 }
 
@@ -79,19 +80,19 @@ __device__ __forceinline__ void wave_rows_issue(WaveRows &r, int64_t m, const in
     for (int p = 0; p < kPasses; ++p) r.keep[p] = p * kWave + lane < nr;
   }
 }
-__device__ __forceinline__ void wave_rows_classify(WaveRows &r, int k, int64_t split_min) {
+__device__ __forceinline__ void wave_rows_classify(WaveRows &r, int k, int coarse_max, int64_t split_min) {
 #pragma unroll
   for (int p = 0; p < kPasses; ++p) {
     const int64_t n = r.end[p] - r.beg[p];
     r.cnt[p] = (int)n;
-    r.c[p] = r.keep[p] ? row_class(n, k, split_min) : -1;
+    r.c[p] = r.keep[p] ? row_class(n, k, coarse_max, split_min) : -1;
   }
 }
 __device__ __forceinline__ void load_wave_rows(WaveRows &r, int64_t m, const int64_t *__restrict__ ptr,
-                                               const uint8_t *__restrict__ mask, int k, int64_t split_min,
-                                               int64_t wbase, int lane) {
+                                               const uint8_t *__restrict__ mask, int k, int coarse_max,
+                                               int64_t split_min, int64_t wbase, int lane) {
   wave_rows_issue(r, m, ptr, mask, wbase, lane);
-  wave_rows_classify(r, k, split_min);
+  wave_rows_classify(r, k, coarse_max, split_min);
 }
 
 // the classes that occur among the wave's rows, as a bit set (the same value in every lane)
@@ -119,15 +120,15 @@ __device__ __forceinline__ int wave_class_counts(const WaveRows &r, int lane, un
 }
 
 __global__ __launch_bounds__(kBucketThreads) void k_class_count(int64_t m, const int64_t *__restrict__ ptr,
-                                                                const uint8_t *__restrict__ mask, int k,
+                                                                const uint8_t *__restrict__ mask, int k, int coarse_max,
                                                                 int64_t split_min, int32_t *__restrict__ hist) {
   __shared__ int h[kNumClasses];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   if (threadIdx.x < kNumClasses) h[threadIdx.x] = 0;
   __syncthreads();
   WaveRows r;
-  load_wave_rows(r, m, ptr, mask, k, split_min, (int64_t)blockIdx.x * kRowsPerBlock + (int64_t)w * kRowsPerWave,
-                 lane);
+  load_wave_rows(r, m, ptr, mask, k, coarse_max, split_min,
+                 (int64_t)blockIdx.x * kRowsPerBlock + (int64_t)w * kRowsPerWave, lane);
   const int mine = wave_class_counts(r, lane, wave_classes_present(r));
   if (lane < kNumClasses) atomicAdd(&h[lane], mine);
   __syncthreads();
@@ -198,7 +199,7 @@ __device__ __forceinline__ int wave_sum_i(int x) {
 // `offs` is the scanned histogram and cls was written by the scan.
 template <bool SELF_SCAN>
 __global__ __launch_bounds__(kBucketThreads) void k_class_place(int64_t m, const int64_t *__restrict__ ptr,
-                                                                const uint8_t *__restrict__ mask, int k,
+                                                                const uint8_t *__restrict__ mask, int k, int coarse_max,
                                                                 int64_t split_min, const int32_t *__restrict__ offs,
                                                                 RowRef *__restrict__ list, int64_t *__restrict__ cls) {
   __shared__ int wcnt[kBucketThreads / kWave][kNumClasses];
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_class_place(int64_t m, const
   }
   // Each wave places its own contiguous rows: first its per-class counts (lane cc holds class
   // cc), then, from its start within the block's run, the rows in order with ballot ranks.
-  wave_rows_classify(r, k, split_min);
+  wave_rows_classify(r, k, coarse_max, split_min);
   const unsigned present = wave_classes_present(r);
   const int mine = wave_class_counts(r, lane, present);
   if (lane < kNumClasses) wcnt[w][lane] = mine;
@@ -288,21 +289,30 @@ __global__ __launch_bounds__(kBucketThreads) void k_class_place(int64_t m, const
     pos += add;
   }
 }
-open_status bucket_rows_into(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int k, int32_t *hist, RowRef *list,
+// Rows of up to 32 entries at rank 8 whose factors come from memory (more settings than are staged in
+// LDS) keep one class per doubling: the fewer the classes, the more rows of a group are neighbours in
+// the matrix, which share the cache lines of their entries, and beside the factors' gathers that
+// counts for more than groups of one length.  600,000 rows, us, one class / four: of 20 to 30 entries
+// at 1920 settings 147 / 170, at 600 116 / 134; at 480 (staged) 107 / 103; at rank 16, of 17 to 32
+// entries, 225 / 224 at 1920, 184 / 169 at 480.
+static int coarse_max(int n, int k) { return k == 8 && n > kFactorLdsRows ? 32 : 0; }
+
+open_status bucket_rows_into(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int n, int k, int32_t *hist, RowRef *list,
                              int64_t *cls, int64_t split_min, const uint8_t *mask) {
+  const int coarse = coarse_max(n, k);
   const int nblk = (int)((m + kRowsPerBlock - 1) / kRowsPerBlock);
   if (m > 0) {
     OPEN_LAUNCH(ctx, "bucket_count", k_class_count, dim3(nblk), dim3(kBucketThreads), 0, m, row_ptr, mask, k,
-                split_min, hist);
+                coarse, split_min, hist);
   }
   if (m > 0 && nblk <= kSelfScanMaxBlocks) {
     OPEN_LAUNCH(ctx, "bucket_place", k_class_place<true>, dim3(nblk), dim3(kBucketThreads), 0, m, row_ptr, mask,
-                k, split_min, (const int32_t *)hist, list, cls);
+                k, coarse, split_min, (const int32_t *)hist, list, cls);
   } else {
     OPEN_LAUNCH(ctx, "bucket_scan", k_class_scan, dim3(1), dim3(1024), 0, hist, nblk, cls);
     if (m > 0) {
       OPEN_LAUNCH(ctx, "bucket_place", k_class_place<false>, dim3(nblk), dim3(kBucketThreads), 0, m, row_ptr, mask,
-                  k, split_min, (const int32_t *)hist, list, cls);
+                  k, coarse, split_min, (const int32_t *)hist, list, cls);
     }
   }
   return OPEN_OK;
@@ -313,14 +323,14 @@ int64_t bucket_hist_ints(int64_t m) {
   return (int64_t)kNumClasses * (nblk > 0 ? nblk : 1);
 }
 
-open_status bucket_rows(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int k, RowRef **list, int64_t **cls,
+open_status bucket_rows(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int n, int k, RowRef **list, int64_t **cls,
                         int64_t split_min, const uint8_t *mask) {
   void *hist = nullptr, *lst = nullptr, *c = nullptr;
   open_status st;
   if ((st = ws_get(ctx, open_ctx::WS_HIST, sizeof(int32_t) * (size_t)bucket_hist_ints(m), &hist))) return st;
   if ((st = ws_get(ctx, open_ctx::WS_LIST, sizeof(RowRef) * (size_t)(m > 0 ? m : 1), &lst))) return st;
   if ((st = ws_get(ctx, open_ctx::WS_CLS, sizeof(int64_t) * 2 * kNumClasses, &c))) return st;
-  if ((st = bucket_rows_into(ctx, m, row_ptr, k, (int32_t *)hist, (RowRef *)lst, (int64_t *)c, split_min, mask)))
+  if ((st = bucket_rows_into(ctx, m, row_ptr, n, k, (int32_t *)hist, (RowRef *)lst, (int64_t *)c, split_min, mask)))
     return st;
   *list = (RowRef *)lst;
   *cls = (int64_t *)c;

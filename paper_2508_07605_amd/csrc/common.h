@@ -231,13 +231,15 @@ constexpr int kPrimalLo = 9, kPrimalHi = 30;  // primal classes, by length
 constexpr int kNumClasses = 32;
 constexpr int kSplitClass = 31;  // rows solved by the split-K path
 constexpr int64_t kSplitMin = 1024;  // observations from which a row takes the split-K path
-open_status bucket_rows(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int k, RowRef **list, int64_t **cls,
+// (n: rows of the factor matrix that the rows are solved against.)
+open_status bucket_rows(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int n, int k, RowRef **list, int64_t **cls,
                         int64_t split_min, const uint8_t *mask = nullptr);
 // The same into caller-provided buffers: hist of bucket_hist_ints(m) ints, list of m entries,
 // cls of 2 * kNumClasses.  Every element that is read is written first (no clearing needed).
-open_status bucket_rows_into(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int k, int32_t *hist, RowRef *list,
+open_status bucket_rows_into(open_ctx *ctx, int64_t m, const int64_t *row_ptr, int n, int k, int32_t *hist, RowRef *list,
                              int64_t *cls, int64_t split_min, const uint8_t *mask = nullptr);
 int64_t bucket_hist_ints(int64_t m);
+constexpr int kFactorLdsRows = 512;  // factor rows a block of the ridge solves can stage (the fold-in has 480)
 // rows per block of the one-launch fold-in of small batches
 constexpr int kSmallRows = 128;
 // rows per block of the bucketing kernels (the per-block class counts are kNumClasses ints)

@@ -553,14 +553,14 @@ open_status open_fit(open_ctx *ctx, int64_t m, int32_t n, int32_t k, const int64
     if ((st = csr_to_csc_dev(ctx, m, n, row_ptr, col, val, cp, ri, cv))) break;
     RowRef *l;
     int64_t *c;
-    if ((st = bucket_rows(ctx, m, row_ptr, k, &l, &c, kSplitMin))) break;
+    if ((st = bucket_rows(ctx, m, row_ptr, n, k, &l, &c, kSplitMin))) break;
     if (hipMemcpyAsync(list_r, l, sizeof(RowRef) * m, hipMemcpyDeviceToDevice, ctx->stream) != hipSuccess ||
         hipMemcpyAsync(cls_r, c, sizeof(int64_t) * 2 * kNumClasses, hipMemcpyDeviceToDevice, ctx->stream) !=
             hipSuccess) {
       st = fail(ctx, OPEN_E_DEVICE, "copy");
       break;
     }
-    if ((st = bucket_rows(ctx, n, cp, k, &l, &c, kSplitMin))) break;
+    if ((st = bucket_rows(ctx, n, cp, (int)m, k, &l, &c, kSplitMin))) break;
     if (hipMemcpyAsync(list_c, l, sizeof(RowRef) * n, hipMemcpyDeviceToDevice, ctx->stream) != hipSuccess ||
         hipMemcpyAsync(cls_c, c, sizeof(int64_t) * 2 * kNumClasses, hipMemcpyDeviceToDevice, ctx->stream) !=
             hipSuccess) {

@@ -908,7 +908,7 @@ open_status open_mlp_foldin(open_mlp *p, const float *F, int64_t m, const int64_
   if (small_batch(ctx, p->n, p->k, m)) {
     if ((st = small_batch_launch(ctx, F, p->n, p->k, row_ptr, col, val, f, lambda, weighted, U_out, nullptr, m)))
       return st;
-  } else if ((st = bucket_rows(ctx, m, row_ptr, p->k, &list, &cls, INT64_MAX, f)) ||
+  } else if ((st = bucket_rows(ctx, m, row_ptr, p->n, p->k, &list, &cls, INT64_MAX, f)) ||
              (st = rowsolve_launch(ctx, F, p->n, p->k, row_ptr, col, val, lambda, weighted, list, cls, U_out, nullptr,
                                    m))) {
     return st;

@@ -814,7 +814,7 @@ extern "C" open_status open_ncf_foldin(open_ctx *ctx, const float *S, int32_t n,
   // many observation tiles
   RowRef *list = nullptr;
   int64_t *cls = nullptr;
-  if ((st = bucket_rows(ctx, m, row_ptr, kNcfD, &list, &cls, kSplitMin))) return st;
+  if ((st = bucket_rows(ctx, m, row_ptr, n, kNcfD, &list, &cls, kSplitMin))) return st;
   // two pairs per wavefront once the pairs alone give every SIMD its two wavefronts and more: at
   // 8192 applications of 4..24 observations, 30 steps, 1062 us against 1343, at 6000 1053 against
   // 1081, at 4096 (one wavefront per SIMD, longer) 755 against 648

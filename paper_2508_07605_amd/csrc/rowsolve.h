@@ -596,7 +596,6 @@ __device__ __forceinline__ void solve_group(const FRows<K, SRC> &Fr, int n, cons
 
 // LDS budget of a block (bytes) and the factor matrix staged beside the per-wave buffers.
 constexpr int kLdsBytes = 160 * 1024;
-constexpr int kFactorLdsRows = 512;  // factor rows a block can stage (the fold-in has 480)
 // the zero row, kFactorLdsRows rows at pitch K + 4, and one wave instruction (64 slots) of tail
 template <int K>
 __host__ __device__ constexpr int factor_lds_bytes() { return ((kFactorLdsRows + 1) * (K + 4) + 256) * 4; }
