@@ -1,7 +1,7 @@
 // Fold-in of a small batch in one launch: bucketing and solves together.
 //
-// A batch of at most kSmallRows rows per compute unit would spend its time on launches (two of
-// the bucketing and one per class group).  Here every block takes kSmallRows consecutive rows,
+// A batch of few rows per compute unit (small_batch) would spend its time on launches (two of the
+// bucketing and one per class group).  Here every block takes kSmallRows consecutive rows,
 // orders them in LDS by size class, and its wavefronts solve the groups, with the same
 // solve_group as the per-class kernels.
 //

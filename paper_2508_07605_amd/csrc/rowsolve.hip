@@ -71,10 +71,18 @@ static int launch_mode(const open_ctx *ctx, int k, const ClassGroup *g, int ng) 
 //    32,700   10/50  24/81    12/87 103/279   17/43 161/274
 //    65,000   16/56  47/90    23/95 203/283   32/52 317/276
 //   130,000   31/63  92/95    46/97 399/285   61/64 624/317
-// so ranks 8 and 16 take it up to two blocks per unit, rank 32 up to one.  A tuned rank keeps the
-// kernels that its table names, and rows of split-K length their own path.
+// so ranks 8 and 16 take it up to two blocks per unit, rank 32 up to one.  Where the tuning table
+// names the kernels that run, a small batch runs them too: at rank 32 in the launch mode of one
+// launch per class group (the merged launches do not read the groups' entries, which tuning on a large
+// batch sets all the same), at ranks 8 and 16 with any entry set.  Rows of split-K length have their
+// own path.
 bool small_batch(const open_ctx *ctx, int n, int k, int64_t m) {
   if (k == 64 || n >= kSplitMin || m > (int64_t)kSmallRows * (k == 32 ? 1 : 2) * ctx->num_cu) return false;
+  if (k == 32) {
+    int ng = 0;
+    const ClassGroup *g = class_groups(k, &ng);
+    return launch_mode(ctx, k, g, ng) == 0;
+  }
   for (int8_t v : ctx->tune[rank_index(k)])
     if (v) return false;
   return true;
