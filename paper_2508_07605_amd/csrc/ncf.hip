@@ -561,6 +561,13 @@ struct NcfLayout {
   }
 };
 
+// Whether the bias gradients' sums have a launch of their own (wgrad.hip): in large batches they are the
+// second launch's longest chain, unless a few applications' sums over very many settings are.  A
+// step of the training, us, in one launch / apart: 512 applications x 480 settings 1410 / 1060, 34 x
+// 480 117 / 88, 5 x 1920 72 / 59, 18 x 480 70 / 58, 3 x 4096 84 / 79, but 2 x 4096 73 / 78, 1 x 10,000
+// 126 / 131, and of few rows 24 x 120 33.7 / 33.2, 16 x 120 28.7 / 31.8, 4 x 120 25 / 29.
+static bool bias_apart(int G, int n) { return G >= 4 && (int64_t)G * n > 8192; }
+
 // Device buffers of one training call.
 struct NcfTrainBufs {
   uint16_t *X = nullptr, *h1 = nullptr, *h2 = nullptr, *d1p = nullptr, *d2p = nullptr, *dyp = nullptr;
@@ -568,9 +575,10 @@ struct NcfTrainBufs {
   double *lpart = nullptr, *loss = nullptr;
   int64_t *apps = nullptr, *mark = nullptr;
   TrainState *st = nullptr;
+  float *bias = nullptr;  // bias_apart
   void release() {
     for (uint16_t *q : {X, h1, h2, d1p, d2p, dyp}) (void)hipFree(q);
-    for (float *q : {d1, d2, dy, dX, g, am, av}) (void)hipFree(q);
+    for (float *q : {d1, d2, dy, dX, g, am, av, bias}) (void)hipFree(q);
     for (int64_t *q : {apps, mark}) (void)hipFree(q);
     (void)hipFree(lpart);
     (void)hipFree(loss);
@@ -586,7 +594,9 @@ struct NcfTrainBufs {
                     (train ? !hipMalloc(&am, pb) && !hipMalloc(&av, pb) : !hipMalloc(&g, pb)) &&
                     !hipMalloc(&lpart, sizeof(double) * (Bp / 16)) && !hipMalloc(&loss, sizeof(double) * 8) &&
                     !hipMalloc(&apps, sizeof(int64_t) * (size_t)G) &&
-                    !hipMalloc(&mark, sizeof(int64_t) * (size_t)m_off) && !hipMalloc(&st, sizeof(TrainState));
+                    !hipMalloc(&mark, sizeof(int64_t) * (size_t)m_off) && !hipMalloc(&st, sizeof(TrainState)) &&
+                    (!bias_apart(G, n) ||
+                     !hipMalloc(&bias, sizeof(float) * kWgBiasPart * (2 * kNcfH / 32 + 1)));
     if (!ok) (void)hipGetLastError();
     return ok;
   }
@@ -666,6 +676,7 @@ static open_status ncf_step(open_ctx *ctx, const NcfLayout &L, int64_t m_off, in
   w.ltotal = B;
   w.loss_d = b.loss;
   w.loss_steps = loss_steps;
+  w.bias = b.bias;
   return wgrad_step(ctx, "ncf_wgrad_adam", w, lr > 0.f);
 }
 

@@ -37,6 +37,9 @@ struct WgradEmb {
   int64_t e = 0, s = 0;      // offsets of E (m x 32) and S (n x 32) in the parameter vector
 };
 
+// floats of the partial bias sums for every 32 outputs of a layer: slices, four sums each
+constexpr int kWgBiasPart = 256 * 4 * 32;
+
 struct WgradStep {
   WgradLayer l[3];
   WgradEmb emb;
@@ -47,6 +50,8 @@ struct WgradStep {
   const double *lpart;       // partial sums of the squared errors, their number, the mean's divisor
   int nlpart;
   int64_t ltotal;
+  float *bias;               // nullable: the bias gradients' slices are summed into this by a launch of
+                             // their own (kWgBiasPart floats for every 32 outputs)
   double *loss_d;            // the batch loss (each nullable; loss_steps indexed by the Adam step)
   float *loss_f, *loss_steps;
 };

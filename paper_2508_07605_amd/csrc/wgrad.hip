@@ -173,23 +173,23 @@ static void wgrad_shape(WgradLayer &l) {
 
 // Bias gradients of kWgBias outputs: per slice four sums over the rows 32 c + 8 kg + e (kg =
 // 0..3), added in order, then the slices in order.  A thread's (slice, c) groups of eight rows
-// load four at a time: the chain of dependent reads is what this part is bound by.
+// load four at a time: the chain of dependent reads is what this part is bound by.  A block goes
+// through all slices of its outputs; with many rows that chain is the launch's longest, and the
+// slices' sums come from k_wgrad_bias, eight slices to a block.
 constexpr int kWgBias = 32;
-template <bool ADAM>
-__device__ __forceinline__ void bias_sums(const WgradStep &p, const WgradLayer &l, int q, float *buf) {
-  constexpr int PAR = kWgThreads / (4 * kWgBias);          // slices in parallel
-  constexpr int SR = kWgLdsFloats / (4 * kWgBias), G = 4;  // slices a round (all of them); groups in flight
-  static_assert(SR >= 256, "every slice has a slot");
-  const int u = threadIdx.x % kWgBias, kg = threadIdx.x / kWgBias % 4, sl = threadIdx.x / (4 * kWgBias);
-  const int m = kWgBias * q + u;
-  const int gps = l.kc / 32;                               // groups of a slice
-  const int groups = sl < l.S && m < l.M ? (l.S - sl + PAR - 1) / PAR * gps : 0;
+constexpr int kWgBiasSlices = kWgThreads / (4 * kWgBias);  // slices in parallel
+// the thread's slices s0, s0 + kWgBiasSlices, ... (ns of them): their sums to dst[slice][kg][output]
+__device__ __forceinline__ void bias_slices(const WgradStep &p, const WgradLayer &l, int q, int s0, int ns, float *dst) {
+  constexpr int G = 4;  // groups in flight
+  const int u = threadIdx.x % kWgBias, kg = threadIdx.x / kWgBias % 4, m = kWgBias * q + u;
+  const int gps = l.kc / 32;  // groups of a slice
+  const int groups = m < l.M ? ns * gps : 0;
   float x = 0.f;
   for (int g0 = 0; g0 < groups; g0 += G) {
     float d[G][8];
 #pragma unroll
     for (int c = 0; c < G; ++c) {
-      const int64_t b = (int64_t)(sl + PAR * ((g0 + c) / gps)) * l.kc + 32 * ((g0 + c) % gps) + 8 * kg;
+      const int64_t b = (int64_t)(s0 + kWgBiasSlices * ((g0 + c) / gps)) * l.kc + 32 * ((g0 + c) % gps) + 8 * kg;
 #pragma unroll
       for (int e = 0; e < 8; ++e) d[c][e] = g0 + c < groups && b + e < p.B ? l.Af[(b + e) * l.M + m] : 0.f;
     }
@@ -199,14 +199,25 @@ __device__ __forceinline__ void bias_sums(const WgradStep &p, const WgradLayer &
 #pragma unroll
         for (int e = 0; e < 8; ++e) x += d[c][e];
         if ((g0 + c + 1) % gps == 0) {
-          buf[((sl + PAR * ((g0 + c) / gps)) * 4 + kg) * kWgBias + u] = x;
+          dst[((s0 + kWgBiasSlices * ((g0 + c) / gps)) * 4 + kg) * kWgBias + u] = x;
           x = 0.f;
         }
       }
     }
   }
+}
+template <bool ADAM>
+__device__ __forceinline__ void bias_sums(const WgradStep &p, const WgradLayer &l, int q, const float *part, float *buf) {
+  static_assert(kWgBiasPart <= kWgLdsFloats, "every slice has a slot");
+  if (part) {
+    for (int i = threadIdx.x; i < l.S * 4 * kWgBias; i += kWgThreads) buf[i] = part[i];
+  } else {
+    const int sl = threadIdx.x / (4 * kWgBias);
+    bias_slices(p, l, q, sl, sl < l.S ? (l.S - sl + kWgBiasSlices - 1) / kWgBiasSlices : 0, buf);
+  }
   __syncthreads();
-  if (threadIdx.x < kWgBias && m < l.M) {
+  const int u = threadIdx.x, m = kWgBias * q + u;
+  if (u < kWgBias && m < l.M) {
     float tot = 0.f;
 #pragma unroll 4
     for (int i = 0; i < l.S; ++i) {
@@ -218,6 +229,19 @@ __device__ __forceinline__ void bias_sums(const WgradStep &p, const WgradLayer &
       adam_update(p, i, tot, p.st->c1, p.st->c2);
     else
       p.g[i] = tot;
+  }
+}
+// the slices' bias sums of all layers: block (x, y) takes slices 8 x .. 8 x + 7 of the y-th 32 outputs
+__global__ __launch_bounds__(kWgThreads) void k_wgrad_bias(WgradStep p) {
+  int q = blockIdx.y;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const int nb = (p.l[i].M + kWgBias - 1) / kWgBias;
+    if (q < nb) {
+      const int s = kWgBiasSlices * blockIdx.x + (int)threadIdx.x / (4 * kWgBias);
+      return bias_slices(p, p.l[i], q, s, s < p.l[i].S ? 1 : 0, p.bias + (int64_t)blockIdx.y * kWgBiasPart);
+    }
+    q -= nb;
   }
 }
 
@@ -327,11 +351,13 @@ __global__ __launch_bounds__(kWgThreads) void k_wgrad_step(WgradStep p) {
     if (q < no) return other_embeddings<ADAM>(p, q);
     q -= no;
   }
+  const float *part = p.bias;
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const int nb = (p.l[i].M + kWgBias - 1) / kWgBias;
-    if (q < nb) return bias_sums<ADAM>(p, p.l[i], q, buf);
+    if (q < nb) return bias_sums<ADAM>(p, p.l[i], q, part ? part + (int64_t)q * kWgBiasPart : nullptr, buf);
     q -= nb;
+    if (part) part += (int64_t)nb * kWgBiasPart;
   }
   if (q == 0) return loss_and_state<ADAM>(p, reinterpret_cast<double *>(buf));
   --q;
@@ -350,10 +376,17 @@ open_status wgrad_step(open_ctx *ctx, const char *name, WgradStep p, bool adam) 
   unsigned blocks = 1;
   if (p.emb.G > 0)
     blocks += (unsigned)(p.emb.G + ((int64_t)p.emb.n * kEmbD + kWgThreads - 1) / kWgThreads + other_blocks(p.emb.m));
+  int outputs = 0, slices = 0;  // 32 outputs each, of all layers; most slices of a layer
   for (WgradLayer &l : p.l) {
     l.S = wgrad_slices(p.B, l.M, l.N, &l.kc);
     wgrad_shape(l);
     blocks += (unsigned)(l.blocks + (l.M + kWgBias - 1) / kWgBias);
+    outputs += (l.M + kWgBias - 1) / kWgBias;
+    slices = l.S > slices ? l.S : slices;
+  }
+  if (p.bias) {
+    const dim3 grid((unsigned)((slices + kWgBiasSlices - 1) / kWgBiasSlices), (unsigned)outputs);
+    OPEN_LAUNCH(ctx, "wgrad_bias", k_wgrad_bias, grid, dim3(kWgThreads), 0, p);
   }
   if (adam) {
     OPEN_LAUNCH(ctx, name, k_wgrad_step<true>, dim3(blocks), dim3(kWgThreads), 0, p);
