@@ -20,22 +20,15 @@ namespace openk {
 constexpr int kNcfD = 32, kNcfH = 64;
 constexpr int kNcfMaxSteps = 100000;  // bounds a launch's run time
 constexpr int kNcfTwoPairs = 24;     // applications per CU above which a wavefront takes two pairs
-constexpr float kSeluAlpha = 1.6732632423543772f, kSeluLambda = 1.0507009873554805f;
 
 // both sides computed and selected: as branches, the 64 evaluations of a tile run one after the other
 __device__ __forceinline__ void selu_and_grad(float z, float &h, float &dh) {
   const float ez = __expf(z);
-  const float hn = kSeluLambda * kSeluAlpha * (ez - 1.f), dn = kSeluLambda * kSeluAlpha * ez;
-  const float hp = kSeluLambda * z;
+  const float hn = kSeluL * kSeluA * (ez - 1.f), dn = kSeluL * kSeluA * ez;
+  const float hp = kSeluL * z;
   const bool pos = z > 0.f;
   h = pos ? hp : hn;
-  dh = pos ? kSeluLambda : dn;
-}
-
-__device__ __forceinline__ float wave_sum_f(float x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, kWave);
-  return x;
+  dh = pos ? kSeluL : dn;
 }
 
 // C[j][l] = b1[l] + sum_k W1[l][d + k] S[j][k]
