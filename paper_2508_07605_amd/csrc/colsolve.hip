@@ -385,8 +385,9 @@ static open_status split_launch_k(open_ctx *ctx, const float *F, int nF, const i
                                   int64_t max_rows, int ranges, unsigned blocks) {
   OPEN_LAUNCH(ctx, "split_prefix", k_split_prefix, dim3(1), dim3(kPrefixThreads), 0, list, cls, ranges,
               (int)(blocks * kGramWaves / kXcds), start);
-  OPEN_LAUNCH(ctx, "split_gram", (far_factors(nF, K) ? k_split_gram<K, true> : k_split_gram<K, false>), dim3(blocks), dim3(64 * kGramWaves), 0, F, ri, cv, list, cls,
-              ranges, (const int64_t *)start, nF, part, pflag);
+  OPEN_LAUNCH(ctx, "split_gram", (far_factors(nF, K) ? k_split_gram<K, true> : k_split_gram<K, false>), dim3(blocks),
+              dim3(64 * kGramWaves), 0, F, ri, cv, list, cls, ranges,
+              (const int64_t *)start, nF, part, pflag);
   OPEN_LAUNCH(ctx, "split_solve", k_split_solve<K>, dim3((unsigned)max_rows), dim3(64), 0, list, cls,
               (const int64_t *)start, (const float *)part, (const int32_t *)pflag, lambda, weighted, X, status);
   return OPEN_OK;
