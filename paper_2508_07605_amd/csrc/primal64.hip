@@ -236,11 +236,12 @@ __global__ __launch_bounds__(64 * kP64Waves) __attribute__((amdgpu_waves_per_eu(
   __shared__ __attribute__((aligned(16))) float lds_all[kP64Waves][64 * kP64Pitch + 128];
   static_assert(4 * kP64Stage <= 64 * kP64Pitch, "staging lies in the matrix area");
   __shared__ int qnext;
+  const int64_t first = cls[2 * c_lo];
+  const int64_t count = cls[2 * c_hi] + cls[2 * c_hi + 1] - first;
+  if ((int64_t)blockIdx.x >= count) return;  // block has no work (uniform)
   if (threadIdx.x == 0) qnext = 2 * kP64Waves;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int i16 = lane & 15, o = lane >> 4;
-  const int64_t first = cls[2 * c_lo];
-  const int64_t count = cls[2 * c_hi] + cls[2 * c_hi + 1] - first;
   P64Gram<FAR> gram{F, idx, val, reinterpret_cast<int(*)[kP64Stage]>(lds_all[w]),
                     reinterpret_cast<float(*)[kP64Stage]>(lds_all[w] + 2 * kP64Stage)};
   if constexpr (!FAR) gram.rs = make_rsrc(F, (uint64_t)n * 64 * sizeof(float));
