@@ -821,7 +821,11 @@ extern "C" open_status open_ncf_foldin(open_ctx *ctx, const float *S, int32_t n,
   if ((st = bucket_rows(ctx, m, row_ptr, n, kNcfD, &list, &cls, kSplitMin))) return st;
   // two pairs per wavefront once the pairs alone give every SIMD its two wavefronts and more: at
   // 8192 applications of 4..24 observations, 30 steps, 1062 us against 1343, at 6000 1053 against
-  // 1081, at 4096 (one wavefront per SIMD, longer) 755 against 648
+  // 1081, at 4096 (one wavefront per SIMD, longer) 755 against 648.  Where the last tiles are more than
+  // half full only the work on a is shared, and whole rounds of wavefronts decide: with 9..16
+  // observations, 10 steps, 317 against 322 us at 6145 applications, 476 against 404 at 10,000 (two
+  // rounds of half as many), 612 against 630 at 16,384, 1192 against 1236 at 32,768; with 1..8 180
+  // against 320 at 6145.
   const int64_t cap = (int64_t)ctx->num_cu * 64;  // waves, all blocks handed out as they end
   const bool two = m > (int64_t)ctx->num_cu * kNcfTwoPairs;
   const int64_t groups = two ? (m + 3) / 4 : (m + 1) / 2;

@@ -20,12 +20,12 @@
 //            so h1 feeds the next MFMA without moving between lanes; W2 is permuted to match.
 //   layer 3: a per-lane dot product over the 32 held units, then the two halves are added.
 //
-// Bound by the matrix products (18 a tile: 258 GFLOP for 14,000,003 runs, 225 us at the rate of a
-// large product on this card) with about 270 vector operations a tile between them: moving a
-// quarter of those to products, or two to five wavefronts per SIMD, leaves the time as it is
-// within 3 %.  The features, 28 bytes a run, are read in whole lines and turned through LDS; the
-// seven strided reads a tile that this replaces, and b2 and w3 read from LDS in every tile, took
-// 9 % of the time.  14,000,003 runs: 347 -> 326 us, 500,000: 17.2 -> 15.1.
+// Bound by the vector operations, 278 a tile, which issue 78 % of the cycles, beside 18 matrix products a
+// tile (258 GFLOP for 14,000,003 runs), whose units are busy 38 %: the two overlap in part.  (Moving
+// a quarter of the vector operations to products, or two to five wavefronts per SIMD, leaves the
+// time as it is within 3 %.)  The features, 28 bytes a run, are read in whole lines and turned
+// through LDS; with the seven strided reads a tile that this replaces, and b2 and w3 read from LDS
+// in every tile, 14,000,003 runs took 322 us against 297, and 500,000 16.2 against 13.7.
 #include "common.h"
 
 namespace openk {
@@ -197,7 +197,7 @@ extern "C" open_status open_perf_predict(open_ctx *ctx, const float *X, int64_t 
   OPEN_HIP_TRY(ctx, hipSetDevice(ctx->device));
   const int64_t tiles = (n_runs + 31) / 32;
   // three wavefronts per SIMD stay resident: with four times as many, 300,000 runs took 14.8 us
-  // instead of 11.3 (the weights are laid out again by every block) and 14M as long as now
+  // instead of 10.7 (the weights are laid out again by every block) and 14M as long as now
   const int64_t cap = (int64_t)ctx->num_cu * 12;  // waves
   const int64_t waves = tiles < cap ? tiles : cap;
   OPEN_LAUNCH(ctx, "perf_predict", k_perf_predict, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, n_runs, X, mu,
