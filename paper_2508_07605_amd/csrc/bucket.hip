@@ -135,56 +135,48 @@ __global__ __launch_bounds__(kBucketThreads) void k_class_count(int64_t m, const
   if (threadIdx.x < kNumClasses) hist[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = h[threadIdx.x];
 }
 
-// Exclusive scan of the class-major histogram (one block); cls[2c] = start, cls[2c+1] = count.
-// Each thread owns a contiguous run of up to 32 entries, loaded at once.
-__global__ __launch_bounds__(1024) void k_class_scan(int32_t *__restrict__ hist, int nblk,
-                                                     int64_t *__restrict__ cls) {
-  __shared__ int64_t part[1024];
-  const int total = kNumClasses * nblk;
-  const int per = (total + 1023) / 1024;
-  const int b0 = threadIdx.x * per;
-  const int b1 = b0 + per < total ? b0 + per : total;
-  constexpr int R = 32;
-  int v[R];
-  int64_t s = 0;
-  if (per <= R) {
+// Exclusive scan over the blocks of each class's counts, in place: block c takes class c and leaves the
+// class's rows in cls[2c + 1] (k_class_place adds the classes below).  Bound by launch and latency: one
+// round of coalesced loads and a block scan per 4096 counts, 8.4M rows.
+constexpr int kScanThreads = 1024, kScanPer = 4;
+__global__ __launch_bounds__(kScanThreads) void k_class_scan(int32_t *__restrict__ hist, int nblk,
+                                                             int64_t *__restrict__ cls) {
+  __shared__ int wsum[kScanThreads / kWave];
+  const int c = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int32_t *h = hist + (int64_t)c * nblk;
+  int before = 0;  // rows of the rounds so far
+  for (int b0 = 0; b0 < nblk; b0 += kScanThreads * kScanPer) {
+    const int i = b0 + (int)threadIdx.x * kScanPer;
+    int v[kScanPer], own = 0;
 #pragma unroll
-    for (int u = 0; u < R; ++u) v[u] = b0 + u < b1 ? hist[b0 + u] : 0;
-#pragma unroll
-    for (int u = 0; u < R; ++u) s += v[u];
-  } else {
-    for (int i = b0; i < b1; ++i) s += hist[i];
-  }
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int64_t x = threadIdx.x >= (unsigned)off ? part[threadIdx.x - off] : 0;
-    __syncthreads();
-    part[threadIdx.x] += x;
-    __syncthreads();
-  }
-  const int64_t total_rows = part[1023];
-  int64_t run = threadIdx.x ? part[threadIdx.x - 1] : 0;
-  if (per <= R) {
-#pragma unroll
-    for (int u = 0; u < R; ++u) {
-      if (b0 + u < b1) hist[b0 + u] = (int32_t)run;
-      run += v[u];
+    for (int e = 0; e < kScanPer; ++e) {
+      v[e] = i + e < nblk ? h[i + e] : 0;
+      own += v[e];
     }
-  } else {
-    for (int i = b0; i < b1; ++i) {
-      const int64_t h = hist[i];
-      hist[i] = (int32_t)run;
-      run += h;
+    int run = own;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int x = __shfl_up(run, off, kWave);
+      run += lane >= off ? x : 0;
     }
+    if (lane == 63) wsum[w] = run;
+    __syncthreads();
+    run += before - own;
+#pragma unroll
+    for (int k = 0; k < kScanThreads / kWave; ++k) {
+      run += k < w ? wsum[k] : 0;
+      before += wsum[k];
+    }
+#pragma unroll
+    for (int e = 0; e < kScanPer; ++e) {
+      if (i + e < nblk) h[i + e] = run;
+      run += v[e];
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  if (threadIdx.x < kNumClasses) {
-    const int c = threadIdx.x;
-    const int64_t start = nblk > 0 ? (int64_t)hist[(int64_t)c * nblk] : 0;
-    const int64_t end = c + 1 < kNumClasses && nblk > 0 ? (int64_t)hist[(int64_t)(c + 1) * nblk] : total_rows;
-    cls[2 * c] = start;
-    cls[2 * c + 1] = end - start;
+  if (threadIdx.x == 0) {
+    cls[2 * c] = 0;
+    cls[2 * c + 1] = before;
   }
 }
 
@@ -195,22 +187,21 @@ __device__ __forceinline__ int wave_sum_i(int x) {
 }
 
 // SELF_SCAN: `offs` holds the raw class-major counts; every block sums the counts of all
-// blocks (class totals) and of the blocks before it, and block 0 writes cls.  Otherwise
-// `offs` is the scanned histogram and cls was written by the scan.
+// blocks (class totals) and of the blocks before it.  Otherwise `offs` is the histogram scanned per
+// class, and cls[2c + 1] the totals.  Block 0 completes cls.
 template <bool SELF_SCAN>
 __global__ __launch_bounds__(kBucketThreads) void k_class_place(int64_t m, const int64_t *__restrict__ ptr,
                                                                 const uint8_t *__restrict__ mask, int k, int coarse_max,
                                                                 int64_t split_min, const int32_t *__restrict__ offs,
                                                                 RowRef *__restrict__ list, int64_t *__restrict__ cls) {
   __shared__ int wcnt[kBucketThreads / kWave][kNumClasses];
-  __shared__ int run[kNumClasses];
+  __shared__ int run[kNumClasses], tot[kNumClasses], pre[kNumClasses];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   // the wave's rows first: their loads are in flight while the block derives its offsets
   const int64_t wbase = (int64_t)blockIdx.x * kRowsPerBlock + (int64_t)w * kRowsPerWave;
   WaveRows r;
   wave_rows_issue(r, m, ptr, mask, wbase, lane);
   if constexpr (SELF_SCAN) {
-    __shared__ int tot[kNumClasses], pre[kNumClasses];
     const int nblk = (int)gridDim.x, me = (int)blockIdx.x;
     // wave w sums classes w, w + 8, w + 16, w + 24: every count it needs is loaded before any is added
     // (one round trip to L2 instead of one per class and per 64 blocks)
@@ -241,25 +232,23 @@ __global__ __launch_bounds__(kBucketThreads) void k_class_place(int64_t m, const
         pre[c] = p;
       }
     }
-    __syncthreads();
-    if (tid < kNumClasses) {
-      static_assert(kNumClasses <= kWave, "one lane a class");
-      const int own = tot[tid];
-      int start = own;
+  }
+  __syncthreads();
+  if (tid < kNumClasses) {
+    static_assert(kNumClasses <= kWave, "one lane a class");
+    const int own = SELF_SCAN ? tot[tid] : (int)cls[2 * tid + 1];
+    int start = own;
 #pragma unroll
-      for (int off = 1; off < kNumClasses; off <<= 1) {
-        const int x = __shfl_up(start, off, kWave);
-        start += tid >= off ? x : 0;
-      }
-      start -= own;
-      run[tid] = start + pre[tid];
-      if (me == 0) {
-        cls[2 * tid] = start;
-        cls[2 * tid + 1] = own;
-      }
+    for (int off = 1; off < kNumClasses; off <<= 1) {
+      const int x = __shfl_up(start, off, kWave);
+      start += tid >= off ? x : 0;
     }
-  } else {
-    if (tid < kNumClasses) run[tid] = offs[(int64_t)tid * gridDim.x + blockIdx.x];
+    start -= own;
+    run[tid] = start + (SELF_SCAN ? pre[tid] : offs[(int64_t)tid * gridDim.x + blockIdx.x]);
+    if (blockIdx.x == 0) {
+      cls[2 * tid] = start;
+      if constexpr (SELF_SCAN) cls[2 * tid + 1] = own;
+    }
   }
   // Each wave places its own contiguous rows: first its per-class counts (lane cc holds class
   // cc), then, from its start within the block's run, the rows in order with ballot ranks.
@@ -309,7 +298,7 @@ open_status bucket_rows_into(open_ctx *ctx, int64_t m, const int64_t *row_ptr, i
     OPEN_LAUNCH(ctx, "bucket_place", k_class_place<true>, dim3(nblk), dim3(kBucketThreads), 0, m, row_ptr, mask,
                 k, coarse, split_min, (const int32_t *)hist, list, cls);
   } else {
-    OPEN_LAUNCH(ctx, "bucket_scan", k_class_scan, dim3(1), dim3(1024), 0, hist, nblk, cls);
+    OPEN_LAUNCH(ctx, "bucket_scan", k_class_scan, dim3(kNumClasses), dim3(kScanThreads), 0, hist, nblk, cls);
     if (m > 0) {
       OPEN_LAUNCH(ctx, "bucket_place", k_class_place<false>, dim3(nblk), dim3(kBucketThreads), 0, m, row_ptr, mask,
                   k, coarse, split_min, (const int32_t *)hist, list, cls);
