@@ -18,6 +18,7 @@ constexpr int kSplitStage = 256;   // entries staged per wavefront, twice
 constexpr int kSplitFlush = 1024;  // entries summed in one accumulator
 constexpr int kXcds = 8;           // accelerator complex dies of the MI355X, each with its own L2
 constexpr int64_t kMaxRangeRows = 4096;  // rows of a matrix whose parts follow the XCDs' factor ranges
+constexpr float kSplitSum = 4.0f;  // entries that cost as much as adding a part
 constexpr int kPrefixThreads = 1024;
 constexpr int kGramWaves = 4;      // wavefronts of a block
 
@@ -47,9 +48,14 @@ static int split_part_floats(int k) {
 // Parts.  Where the factor matrix does not fit an XCD's L2 (`ranges`), a row has 8 s parts and XCD x
 // takes parts x s .. x s + s - 1: the entries are sorted by index, so it gathers from one
 // eighth of the factors.  Otherwise a row has one part per kSplitFlush entries.  `len`: part
-// length aimed at (ranges only), so that the parts of an XCD fill its wavefronts evenly.
+// length aimed at (ranges only), so that the parts of an XCD fill its wavefronts evenly.  Few rows
+// would then have hundreds of parts each, which one wavefront has to add up: a part costs that about
+// as much as kSplitSum entries cost the products, so sqrt(kSplitSum cnt) is the least of both (one row
+// of 100,000 entries, us, with 696 parts / now: rank 8 102 / 69, 32 166 / 92, 64 319 / 178).
 __device__ __forceinline__ int split_parts(int cnt, bool ranges, int64_t len) {
   if (!ranges) return (cnt + kSplitFlush - 1) / kSplitFlush;
+  const int64_t own = (int64_t)__builtin_sqrtf(kSplitSum * (float)cnt);
+  len = len > own ? len : own;
   const int64_t s = (cnt + 8 * len - 1) / (8 * len);
   return (int)(8 * (s < 1 ? 1 : s));
 }
@@ -280,7 +286,9 @@ __global__ __launch_bounds__(64 * kGramWaves, 2) void k_split_gram(const float *
 // c of the symmetric matrix in registers (lanes past K repeat), the pivot row passed through
 // LDS, forward substitution fused in; back substitution by lane reads.  Bound by the chain of K
 // pivots: 7 us for 480 rows at rank 32, 80 us for 5000 rows at rank 64 (27 and 400 us with the
-// matrix in LDS, a barrier between every step and three times the partial sums).
+// matrix in LDS, a barrier between every step and three times the partial sums).  Where a row has
+// many parts, by their sum: several parts' loads go out together (one row of 696 parts at rank 32,
+// whole pass, 267 -> 166 us).
 template <int K>
 __global__ __launch_bounds__(64) void k_split_solve(const RowRef *__restrict__ list, const int64_t *__restrict__ cls,
                                                     const int64_t *__restrict__ start,
@@ -302,15 +310,32 @@ __global__ __launch_bounds__(64) void k_split_solve(const RowRef *__restrict__ l
 #pragma unroll
   for (int q = 0; q < NB; ++q) gs[q] = f4{0.f, 0.f, 0.f, 0.f};
   int flags = 0;
-  for (int64_t g = g0; g < g1; ++g) {
-    flags |= pflag[g];
-    const float *src = part + g * G::PST;
+  // U parts' loads together; added in part order
+  auto add = [&](int64_t g, auto Un) {
+    constexpr int U = decltype(Un)::value;
+    f4 x[U][NB];
+    float y[U];
 #pragma unroll
-    for (int q = 0; q < NB; ++q)
+    for (int u = 0; u < U; ++u) {
+      const float *src = part + (g + u) * G::PST;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) gs[q][e] += src[(4 * q + e) * 64 + lane];
-    b += src[G::GRAM + lane % K];
-  }
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[u][q][e] = src[(4 * q + e) * 64 + lane];
+      y[u] = src[G::GRAM + lane % K];
+      flags |= pflag[g + u];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int q = 0; q < NB; ++q) gs[q] += x[u][q];
+      b += y[u];
+    }
+  };
+  constexpr int U = K == 64 ? 2 : K == 32 ? 4 : 8;
+  int64_t g = g0;
+  for (; g + U <= g1; g += U) add(g, std::integral_constant<int, U>{});
+  for (; g < g1; ++g) add(g, std::integral_constant<int, 1>{});
   // lane (i16, o) holds, of block (b1, b2), column KB i16 + b2 and rows KB (4 o + e) + b1
   {
     int q = 0;

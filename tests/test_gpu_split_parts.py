@@ -1,5 +1,5 @@
 """Split-K parts of many thousand entries: the right-hand side, like the Gram matrix, is summed in
-pieces of 1024 entries, so its error does not grow with the part.
+pieces of 1024 entries, so its error does not grow with the part.  And rows of many parts.
 
 Every row observes all 262,144 factor rows, whose columns are those of a Hadamard matrix (entries
 +-1, exactly orthogonal): the Gram matrix is 262,144 I without rounding, and the solution is the
@@ -46,3 +46,30 @@ def test_right_hand_side_of_long_parts(k, m):
     rel = np.abs(U - want).max(axis=1) / want[0]
     print("k %d: max error %.2e of the solution" % (k, rel.max()))
     assert rel.max() <= (256 + 32 + 4 + 8 + 8) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("k", [8, 16, 32, 64])
+@pytest.mark.parametrize("counts", [[100_000], [1024, 149_999, 30_000], [150_000] * 5 + [9_000]])
+def test_rows_of_many_parts(k, counts):
+    """Few rows of very different lengths, cut into many parts each: per-row relative error against
+    float64 at most 1e-4, the bound of the other ridge tests, and the same bits again."""
+    n = 150_000
+    r = np.random.default_rng([k, len(counts)])
+    rp = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    col = np.concatenate([np.sort(r.choice(n, size=c, replace=False)) for c in counts]).astype(np.int32)
+    val = r.uniform(0.4, 1.0, size=len(col)).astype(np.float32)
+    F = (0.3 * r.normal(size=(n, k))).astype(np.float32)
+    dev = [torch.from_numpy(a).cuda() for a in (F, rp, col, val)]
+    ctx = native.Context(0)
+    try:
+        st = torch.full((len(counts),), -7, dtype=torch.int32, device="cuda")
+        U = native.open_foldin(ctx, *dev, 0.05, True, row_status=st).cpu().numpy()
+        again = native.open_foldin(ctx, *dev, 0.05, True).cpu().numpy()
+        assert (st == 0).all()
+    finally:
+        ctx.close()
+    assert np.array_equal(U, again)
+    for i, c in enumerate(counts):
+        A, b = F[col[rp[i]:rp[i + 1]]].astype(np.float64), val[rp[i]:rp[i + 1]].astype(np.float64)
+        ref = np.linalg.solve(A.T @ A + 0.05 * c * np.eye(k), A.T @ b)
+        assert np.linalg.norm(U[i] - ref) <= 1e-4 * np.linalg.norm(ref)
