@@ -245,7 +245,7 @@ constexpr int kSmallRows = 128;
 // rows per block of the bucketing kernels (the per-block class counts are kNumClasses ints)
 constexpr int kBucketRowsPerBlock = 2048;
 // Column view on the device (stable counting sort); entries with a column outside [0, n) are dropped.
-open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, const int64_t *row_ptr, const int32_t *col,
+open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, int64_t nnz, const int64_t *row_ptr, const int32_t *col,
                            const float *val, int64_t *col_ptr, int32_t *row_idx, float *cval);
 // Ridge solve of all rows given a bucketing.
 open_status rowsolve_launch(open_ctx *ctx, const float *F, int n, int k, const int64_t *row_ptr, const int32_t *col,

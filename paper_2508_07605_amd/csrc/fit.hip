@@ -20,18 +20,26 @@ namespace openk {
 // The place kernel puts a chunk's entries in order in LDS first, so that neighbouring lanes store
 // neighbouring entries of a column (17 in a run at 480 columns, 2.6 at 1920); consecutive chunks,
 // which write next to each other, are dealt to one XCD's L2.  Bound by the latency of its steps,
-// one block of 16 wavefronts per CU.  12.7M entries, 200,003 x 480: count 28, scan 14, place
+// one or two blocks of 16 wavefronts per CU.  12.7M entries, 200,003 x 480: count 28, scan 14, place
 // 128 us; stored entry by entry as ranked 358 us, and with chunks of 256 rows per wavefront that
 // walked its rows one by one 109, 15 and 860.  19.5M entries, 500,009 x 1920: place 278 us, stored
 // as ranked 577.  Every window ranks all of the chunk's entries again, so a chunk of more than
 // kCscMaxWins windows stores them as ranked, once: whole view of full rows, windows against as
 // ranked, 50,000 x 1920 (24 windows) 9.2 and 4.9 ms, 3000 x 4096 (94) 32 and 2.0, 100,000 x 960
 // (12) 4.7 and 4.4, 50,000 rows of 900 in 1920 (11) 2.33 and 2.46, 100,000 x 480 (6) 1.5 and 2.0.
+// Chunks of few entries need no large window: where there are more chunks than CUs and the window of
+// two blocks that share a CU holds the mean chunk, that window is taken, and the exceptional chunk,
+// which then has the CU's wavefronts to wait for, is stored as ranked past kCscPairWins windows.  Whole
+// view, one block per CU with the scan's walk by one thread per column against now: 2M rows of 0 to 2
+// in 2 columns 283 and 175 us, 10M 1261 and 712, 2M of 0 to 4 in 120 320 and 223; 1M rows of 2 in 480
+// but for 128 full ones 409 and 311, with 12 windows allowed 486.
 constexpr int kCscRows = 128;          // rows of a chunk: two 64-bit masks per column
 constexpr int kCscThreads = 512;
 constexpr int kCscPlaceThreads = 1024;
 constexpr int kCscWin = 10240;         // entries put in order in LDS at a time (fewer for many columns)
 constexpr int kCscMaxWins = 12;        // more of them in a chunk: its entries are stored as ranked
+constexpr int kCscPairLds = 79 * 1024; // LDS of a place block when two share a CU
+constexpr int kCscPairWins = 4;        // and its most windows
 constexpr int kCscSeg = 64;            // chunks of a scan segment
 // chunks of a launch: a grid holds fewer than 2^32 threads, which 2^31 rows would pass
 constexpr int kCscLaunchChunks = 1 << 21;
@@ -116,20 +124,25 @@ __global__ __launch_bounds__(256) void k_csc_segments(int n, int nchunk, int seg
   seg[(int64_t)sg * n + j] = run;
 }
 
-// seg[s][j] -> position of segment s's first entry of column j; col_ptr.  One block; thread t owns
-// columns t, t + 1024, ...
+// seg[s][j] -> position of segment s's first entry of column j; col_ptr.  One block.  Thread t owns
+// columns t, t + 1024, ...; SPLIT (at most 512 columns): 1024 / n threads share a column, each with a
+// stretch of its segments, as a single thread's walk over them is a serial chain: at 10M rows x 2
+// columns 1221 segments, 8 loads at a time and twice.
+template <bool SPLIT>
 __global__ __launch_bounds__(1024) void k_csc_bases(int n, int nseg, int64_t *__restrict__ seg,
                                                     int64_t *__restrict__ col_ptr) {
   __shared__ int64_t scan[1024];
+  const int P = SPLIT ? 1024 / n : 1, per = (nseg + P - 1) / P;
   int64_t before = 0;  // entries of the columns before this round's
   for (int j0 = 0; j0 < n; j0 += 1024) {
-    const int j = j0 + (int)threadIdx.x;
+    const int j = j0 + (int)threadIdx.x / P;
+    const int s0 = SPLIT ? (int)threadIdx.x % P * per : 0, s1 = SPLIT && s0 + per < nseg ? s0 + per : nseg;
     int64_t tot = 0;
     if (j < n)
-      for (int s = 0; s < nseg; s += 8) {
+      for (int s = s0; s < s1; s += 8) {
         int64_t v[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = s + e < nseg ? seg[(int64_t)(s + e) * n + j] : 0;
+        for (int e = 0; e < 8; ++e) v[e] = s + e < s1 ? seg[(int64_t)(s + e) * n + j] : 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) tot += v[e];
       }
@@ -144,14 +157,14 @@ __global__ __launch_bounds__(1024) void k_csc_bases(int n, int nseg, int64_t *__
     int64_t run = before + scan[threadIdx.x] - tot;
     before += scan[1023];
     if (j < n) {
-      col_ptr[j] = run;
-      for (int s = 0; s < nseg; s += 8) {
+      if (s0 == 0) col_ptr[j] = run;
+      for (int s = s0; s < s1; s += 8) {
         int64_t v[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = s + e < nseg ? seg[(int64_t)(s + e) * n + j] : 0;
+        for (int e = 0; e < 8; ++e) v[e] = s + e < s1 ? seg[(int64_t)(s + e) * n + j] : 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          if (s + e < nseg) seg[(int64_t)(s + e) * n + j] = run;
+          if (s + e < s1) seg[(int64_t)(s + e) * n + j] = run;
           run += v[e];
         }
       }
@@ -167,7 +180,7 @@ __global__ __launch_bounds__(1024) void k_csc_bases(int n, int nseg, int64_t *__
 __global__ __launch_bounds__(kCscPlaceThreads) void k_csc_place(int64_t m, int n, const int64_t *__restrict__ ptr,
                                                                 const int32_t *__restrict__ col,
                                                                 const float *__restrict__ val, int chunk0, int count,
-                                                                int win,
+                                                                int win, int max_wins,
                                                                 const int32_t *__restrict__ hist,
                                                                 const int64_t *__restrict__ seg,
                                                                 int32_t *__restrict__ row_idx,
@@ -215,7 +228,7 @@ __global__ __launch_bounds__(kCscPlaceThreads) void k_csc_place(int64_t m, int n
     const unsigned long long below = (1ull << (r & 63)) - 1ull;
     return r < 64 ? __popcll(lo & below) : __popcll(lo) + __popcll(hi & below);
   };
-  if (total > kCscMaxWins * win) {
+  if (total > max_wins * win) {
     __syncthreads();
 #pragma unroll 4
     for (int t = threadIdx.x; t < c.len; t += TH) {
@@ -275,8 +288,8 @@ static open_status check_cols(open_ctx *ctx, int64_t nnz, const int32_t *col, in
   return OPEN_OK;
 }
 
-open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, const int64_t *row_ptr, const int32_t *col,
-                                   const float *val, int64_t *col_ptr, int32_t *row_idx, float *cval) {
+open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, int64_t nnz, const int64_t *row_ptr, const int32_t *col,
+                           const float *val, int64_t *col_ptr, int32_t *row_idx, float *cval) {
   const int nchunk = (int)((m + kCscRows - 1) / kCscRows);
   const int nseg = (nchunk + kCscSeg - 1) / kCscSeg;
   void *hist, *seg;
@@ -288,7 +301,12 @@ open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, const int64_t *row_p
   const size_t lds = sizeof(unsigned long long) * 2 * (size_t)n;
   const size_t cols = (2 * sizeof(unsigned long long) + sizeof(int64_t) + sizeof(int)) * (size_t)n;
   const size_t room = (size_t)(156 * 1024 - cols) / sizeof(uint2);  // n <= kMaxCols: at least 5632
-  const int win = room < (size_t)kCscWin ? (int)room : kCscWin;
+  int win = room < (size_t)kCscWin ? (int)room : kCscWin, max_wins = kCscMaxWins;
+  const int64_t pair = cols < (size_t)kCscPairLds ? (int64_t)((kCscPairLds - cols) / sizeof(uint2)) : 0;
+  if (nchunk > ctx->num_cu && pair * nchunk >= nnz) {
+    win = pair < win ? (int)pair : win;
+    max_wins = kCscPairWins;
+  }
   auto launch_chunks = [&](int c0) { return nchunk - c0 < kCscLaunchChunks ? nchunk - c0 : kCscLaunchChunks; };
   auto launch_blocks = [](int count) { return dim3(8 * (unsigned)((count + 7) / 8)); };
   for (int c0 = 0; c0 < nchunk; c0 += launch_chunks(c0)) {
@@ -298,12 +316,12 @@ open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, const int64_t *row_p
     OPEN_LAUNCH(ctx, "csc_segments", k_csc_segments, dim3((unsigned)((n + 255) / 256), (unsigned)segs), dim3(256), 0, n,
                 nchunk, c0 / kCscSeg, (int32_t *)hist, (int64_t *)seg);
   }
-  OPEN_LAUNCH(ctx, "csc_bases", k_csc_bases, dim3(1), dim3(1024), 0, n, nseg, (int64_t *)seg, col_ptr);
+  OPEN_LAUNCH(ctx, "csc_bases", (n <= 512 ? k_csc_bases<true> : k_csc_bases<false>), dim3(1), dim3(1024), 0, n, nseg, (int64_t *)seg, col_ptr);
   for (int c0 = 0; c0 < nchunk; c0 += launch_chunks(c0)) {
     const int count = launch_chunks(c0);
     OPEN_LAUNCH(ctx, "csc_place", k_csc_place, launch_blocks(count), dim3(kCscPlaceThreads),
-                cols + sizeof(uint2) * (size_t)win, m, n, row_ptr, col, val, c0, count, win, (const int32_t *)hist,
-                (const int64_t *)seg, row_idx, cval);
+                cols + sizeof(uint2) * (size_t)win, m, n, row_ptr, col, val, c0, count, win, max_wins,
+                (const int32_t *)hist, (const int64_t *)seg, row_idx, cval);
   }
   return OPEN_OK;
 }
@@ -449,7 +467,7 @@ open_status open_csr_to_csc(open_ctx *ctx, int64_t m, int32_t n, const int64_t *
   }
   open_status st = check_cols(ctx, nnz, col, n);
   if (st) return st;
-  return csr_to_csc_dev(ctx, m, n, row_ptr, col, val, col_ptr, row_idx, cval);
+  return csr_to_csc_dev(ctx, m, n, nnz, row_ptr, col, val, col_ptr, row_idx, cval);
 }
 
 open_status open_objective(open_ctx *ctx, int64_t m, int32_t n, int32_t k, const int64_t *row_ptr,
@@ -470,7 +488,7 @@ open_status open_objective(open_ctx *ctx, int64_t m, int32_t n, int32_t k, const
   if ((st = ws_get(ctx, open_ctx::WS_CSC_PTR, sizeof(int64_t) * (n + 1), &cp))) return st;
   if ((st = ws_get(ctx, open_ctx::WS_CSC_IDX, sizeof(int32_t) * (size_t)(nnz > 0 ? nnz : 1), &ri))) return st;
   if ((st = ws_get(ctx, open_ctx::WS_CSC_VAL, sizeof(float) * (size_t)(nnz > 0 ? nnz : 1), &cv))) return st;
-  if ((st = csr_to_csc_dev(ctx, m, n, row_ptr, col, val, (int64_t *)cp, (int32_t *)ri, (float *)cv))) return st;
+  if ((st = csr_to_csc_dev(ctx, m, n, nnz, row_ptr, col, val, (int64_t *)cp, (int32_t *)ri, (float *)cv))) return st;
   double *h;
   if ((st = pinned_get(ctx, 64, (void **)&h))) return st;
   void *d;
@@ -550,7 +568,7 @@ open_status open_fit(open_ctx *ctx, int64_t m, int32_t n, int32_t k, const int64
   }
   do {
     if ((st = check_cols(ctx, nnz, col, n))) break;
-    if ((st = csr_to_csc_dev(ctx, m, n, row_ptr, col, val, cp, ri, cv))) break;
+    if ((st = csr_to_csc_dev(ctx, m, n, nnz, row_ptr, col, val, cp, ri, cv))) break;
     RowRef *l;
     int64_t *c;
     if ((st = bucket_rows(ctx, m, row_ptr, n, k, &l, &c, kSplitMin))) break;
