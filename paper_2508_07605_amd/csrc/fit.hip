@@ -20,9 +20,9 @@ namespace openk {
 // The place kernel puts a chunk's entries in order in LDS first, so that neighbouring lanes store
 // neighbouring entries of a column (17 in a run at 480 columns, 2.6 at 1920); consecutive chunks,
 // which write next to each other, are dealt to one XCD's L2.  Bound by the latency of its steps,
-// one or two blocks of 16 wavefronts per CU.  12.7M entries, 200,003 x 480: count 28, scan 14, place
-// 128 us; stored entry by entry as ranked 358 us, and with chunks of 256 rows per wavefront that
-// walked its rows one by one 109, 15 and 860.  19.5M entries, 500,009 x 1920: place 278 us, stored
+// one or two blocks of 16 wavefronts per CU.  12.7M entries, 200,003 x 480: count 28, scan 15, place
+// 94 us (118 with one block per CU); stored entry by entry as ranked 358 us, and with chunks of 256 rows per wavefront that
+// walked its rows one by one 109, 15 and 860.  19.5M entries, 500,009 x 1920: place 272 us, stored
 // as ranked 577.  Every window ranks all of the chunk's entries again, so a chunk of more than
 // kCscMaxWins windows stores them as ranked, once: whole view of full rows, windows against as
 // ranked, 50,000 x 1920 (24 windows) 9.2 and 4.9 ms, 3000 x 4096 (94) 32 and 2.0, 100,000 x 960
