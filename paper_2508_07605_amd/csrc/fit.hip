@@ -125,9 +125,9 @@ __global__ __launch_bounds__(256) void k_csc_segments(int n, int nchunk, int seg
 }
 
 // seg[s][j] -> position of segment s's first entry of column j; col_ptr.  One block.  Thread t owns
-// columns t, t + 1024, ...; SPLIT (at most 512 columns): 1024 / n threads share a column, each with a
-// stretch of its segments, as a single thread's walk over them is a serial chain: at 10M rows x 2
-// columns 1221 segments, 8 loads at a time and twice.
+// columns t, t + 1024, ...; SPLIT (at most 512 columns, and more segments than a thread loads at once):
+// 1024 / n threads share a column, each with a stretch of its segments, as a single thread's walk over
+// them is a serial chain: at 10M rows x 2 columns 1221 segments, 8 loads at a time and twice.
 template <bool SPLIT>
 __global__ __launch_bounds__(1024) void k_csc_bases(int n, int nseg, int64_t *__restrict__ seg,
                                                     int64_t *__restrict__ col_ptr) {
@@ -316,7 +316,7 @@ open_status csr_to_csc_dev(open_ctx *ctx, int64_t m, int n, int64_t nnz, const i
     OPEN_LAUNCH(ctx, "csc_segments", k_csc_segments, dim3((unsigned)((n + 255) / 256), (unsigned)segs), dim3(256), 0, n,
                 nchunk, c0 / kCscSeg, (int32_t *)hist, (int64_t *)seg);
   }
-  OPEN_LAUNCH(ctx, "csc_bases", (n <= 512 ? k_csc_bases<true> : k_csc_bases<false>), dim3(1), dim3(1024), 0, n, nseg, (int64_t *)seg, col_ptr);
+  OPEN_LAUNCH(ctx, "csc_bases", (n <= 512 && nseg > 8 ? k_csc_bases<true> : k_csc_bases<false>), dim3(1), dim3(1024), 0, n, nseg, (int64_t *)seg, col_ptr);
   for (int c0 = 0; c0 < nchunk; c0 += launch_chunks(c0)) {
     const int count = launch_chunks(c0);
     OPEN_LAUNCH(ctx, "csc_place", k_csc_place, launch_blocks(count), dim3(kCscPlaceThreads),

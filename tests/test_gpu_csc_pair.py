@@ -1,7 +1,8 @@
 """Column view of many chunks of few entries, whose place blocks share a CU: both sides of the rule (more
 chunks of 128 rows than CUs; a mean chunk that fits half a CU's LDS, 9692 entries at 120 columns, 4
 at 2888), chunks of more and of fewer than the 4 windows of such a block, and the scan of at most 512
-columns, shared by 1024 / n threads.  Equal to the stable sort by column, exactly."""
+columns, shared by 1024 / n threads from 9 segments of 64 chunks on.  Equal to the stable sort by
+column, exactly."""
 import numpy as np
 import pytest
 import torch
@@ -18,6 +19,7 @@ CUS = 256
     (128 * (CUS + 9), 77, 77, 128 * (CUS + 9)), (128 * (CUS + 9), 284, 2, 200), (128 * (CUS + 9), 285, 2, 200),
     (128 * (CUS + 9), 1920, 2, 30),
     (128 * (CUS + 9), 2888, 0, 1), (128 * (CUS + 9), 2889, 1, 5),
+    (65536, 480, 2, 0), (65537, 480, 2, 0), (65537, 512, 2, 0),
     (300001, 1, 1, 0), (300001, 2, 2, 0), (300001, 3, 3, 0), (100003, 511, 2, 3), (100003, 512, 2, 3),
     (100003, 513, 2, 3), (63, 512, 5, 1), (1, 1, 1, 1), (1100003, 7, 2, 300)])
 def test_sparse_chunks(m, n, hi, full):
